@@ -228,13 +228,15 @@ ap_status ap_gemv_list_batch(const ap_gemv_list_item *items, int count, int batc
 ap_status ap_dequantize(const ap_matrix *h, int b, void *w_dev, void *stream);
 
 /*
- * y = x * W_b^T for any batch >= 1 through the dequantise + dense GEMM path (the paper's route for
- * batch above ~16): ap_dequantize into work_dev, then one FP16 GEMM with binary32 accumulation
- * from rocBLAS, which is loaded on first use (AP_ERR_HIP if it cannot be loaded or fails).
+ * y = x * W_b^T for any batch >= 1 (the paper's route for batch above ~16).  Batches of up to 256 (384 at b = 4 and 5, 512
+ * at b = 3) with a 16-byte aligned x run on a kernel that dequantises into the matrix instructions; everything else is
+ * ap_dequantize into work_dev, then one FP16 GEMM with binary32 accumulation from rocBLAS, which is loaded on first use
+ * (AP_ERR_HIP if it cannot be loaded or fails).
  *   x_dev     device, batch*K binary16 row-major;  y_dev  device, batch*M binary16 row-major
- *   work_dev  device, >= ap_gemm_workspace_size bytes (M*K*2), 16-byte aligned, caller-owned
- * The first call on a process creates the rocBLAS handle (that call allocates and is not
- * capturable in a graph); later calls only enqueue work on `stream`.
+ *   work_dev  device, >= ap_gemm_workspace_size bytes (M*K*2), 16-byte aligned, caller-owned; holds nothing of
+ *             use to the caller after the call
+ * The first call of a process that needs rocBLAS creates its handle (that call allocates and is not
+ * capturable in a graph); every other call only enqueues work on `stream`.
  */
 ap_status ap_gemm_workspace_size(const ap_matrix *h, size_t *bytes);
 ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,
@@ -244,15 +246,15 @@ ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int
  * ap_gemm for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same result contract as ap_gemm (binary32 accumulation,
  * binary16 output, the tolerance of ap_gemv), but the call allocates nothing and calls no library that
- * might: the dequantised weights go to a device array built into this library, AP_GEMM_STATIC_MAX_BYTES
+ * might: its workspace is a device array built into this library, AP_GEMM_STATIC_MAX_BYTES
  * large (each GPU the library runs on holds its own copy until the process ends), and the product is
- * computed by a kernel of this library.  The array's device address is looked up once per device, by
+ * computed by kernels of this library at every batch.  The array's device address is looked up once per device, by
  * ap_pack / ap_attach or else by the first call here.
  *   x_dev   device, batch*K binary16 row-major, 16-byte aligned;  y_dev  device, batch*M binary16
  *   AP_ERR_BUFFER_TOO_SMALL if M*K*2 > AP_GEMM_STATIC_MAX_BYTES (use ap_gemm with your own workspace)
  * All calls on one GPU share the one array: calls that may overlap in time on the same GPU (different
- * streams, or threads) race on it and must be serialised by the caller.  The array keeps the last
- * call's weights; every call rewrites all it reads, so nothing needs clearing.
+ * streams, or threads) race on it and must be serialised by the caller.  Every call rewrites all it
+ * reads, so nothing needs clearing.
  */
 #define AP_GEMM_STATIC_MAX_BYTES (32u << 20)
 ap_status ap_gemm_static(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,

@@ -406,6 +406,13 @@ extern "C" ap_status ap_gemm_workspace_size(const ap_matrix *h, size_t *bytes)
     return AP_OK;
 }
 
+// Largest batch of ap_gemm that runs on the fused kernel; above it the weights are dequantised once into the workspace and
+// rocBLAS computes the product.  The fused kernel dequantises once per 64 batch rows, at b = 3 for half the cost.  Measured,
+// us, dequantise + rocBLAS / fused, batch 256 / 384 / 512: 8192x8192 b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111,
+// b = 8 115/68 108/97 118/126; 11008x4096 b = 3 69/38 69/54 75/66, b = 5 72/48 72/70 77/85, b = 8 74/57 76/84 81/101;
+// 4096x11008 b = 8 81/52 89/82 101/87.
+static int fused_max_batch(int b) { return b == 3 ? kMaxFusedBatch : b <= 5 ? 384 : 256; }
+
 extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,
                              void *work_dev, size_t work_bytes, void *stream)
 {
@@ -418,8 +425,14 @@ extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void 
         reinterpret_cast<uintptr_t>(y_dev) % 2)
         return AP_ERR_INVALID_ARG;
     if (work_bytes < (size_t)a.M * (size_t)a.K * 2) return AP_ERR_BUFFER_TOO_SMALL;
-    a.y = static_cast<uint16_t *>(work_dev);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    a.x = static_cast<const uint16_t *>(x_dev);
+    a.y = static_cast<uint16_t *>(y_dev);
+    a.batch = batch;
+    a.work = work_dev;
+    a.work_bytes = work_bytes;
+    if (batch <= fused_max_batch(b) && gemm_fused_ok(a)) return launch_gemv(a, st) == hipSuccess ? AP_OK : AP_ERR_HIP;
+    a.y = static_cast<uint16_t *>(work_dev);
     if (launch_dequantize(a, st) != hipSuccess) return AP_ERR_HIP;
     return dense_gemm_f16(work_dev, x_dev, y_dev, a.M, a.K, batch, st) ? AP_OK : AP_ERR_HIP;
 }

@@ -1,0 +1,471 @@
+// Large-batch product y = x W_b^T without the dense detour (Section 6.2, "Matrix-Matrix Multiplication Performance": above a
+// batch of about 16 the engine dequantises with a separate kernel and runs a dense GEMM).  Writing and reading back 2 bytes
+// per weight costs more than the product itself up to a batch of a few hundred, so here the lanes that dequantise feed
+// v_mfma_f32_16x16x32_f16 directly.
+//
+//  * A workgroup owns 64 rows (16 groups of 4) x up to 64 batch rows; its waves split the columns.  A step of a wave is 4
+//    chunks (128 columns): lane (i, kg) = (l % 16, l / 16) holds the 16-byte units of row group i, chunk kg, and supplies, for
+//    r = 0..3 and run t, row r of its group as operand A of one instruction (16 groups x 32 columns) per 16 batch rows.  So a
+//    fragment of the activations serves 4 instructions, a dequantised one up to 4, and there is no waste in the result.
+//  * The units are loaded 4 lanes to 64 contiguous bytes and change to that order through a wave-private LDS buffer (one
+//    ds_write_b128 + ds_read_b128 per slice).  Loaded directly in the instruction's order every lane is a cache access of its
+//    own, and the vector L1 then bounds the kernel: 28672 x 8192, b = 4, batch 64: 74 -> 59 us.
+//  * Activations: up to 48 batch rows take the same way through LDS.  Beyond that a small kernel first copies x to
+//    the caller's workspace in fragment order, and the waves read their fragments as whole lines (3 us for the copy; the
+//    exchange of 4 tiles would cost as much LDS time as the lookups).
+//  * Tables: 32 lanes of an LDS clock = 16 row groups x 2 lane groups, each with a bank of its own: two copies per row, the rows
+//    2 rp and 2 rp + 1 of a group in the halves of one dword, entries 256 bytes apart, so that one v_perm_b32 of the index byte
+//    and the lane's base makes an address (64 KB at 8 bits, 8 KB at 4 and 5).  b = 3 looks up pairs.
+//  * Lookups of run t + 1 are issued before the instructions of run t, loads two runs and one step ahead: at two waves per
+//    SIMD there is nobody else to hide them.  In the steady state VALU (350 instructions per step) and matrix instructions
+//    (64 x 16 cycles) take turns on a SIMD; neither HBM nor LDS is the limit.
+#include <type_traits>
+#include "device_common.h"
+#include "launchers.h"
+
+namespace apgemv {
+
+// Tables of 64 rows in LDS.  Bank of a dword = copy * 16 + row group.
+template <int B> struct BlockTable {
+    static constexpr bool kPair = (B == 3);
+    static constexpr uint32_t kMask = kPair ? 0xFCu : Table<B>::addr_mask(); // index bits inside a merged byte
+    static constexpr int kLow = (kMask & 1) ? 0 : (kMask & 2) ? 1 : 2;       // lowest of them
+    static constexpr uint32_t kClean = (kMask >> kLow) * 0x01010101u;        // index bits of the rotated words
+    static constexpr int kEntries = (int)(kMask >> kLow) + 1;                // entry slots (b = 4 uses 16 of 24)
+    static constexpr int kBytes = kEntries * 256 * (kPair ? 2 : 1);
+    // slot of the entry stored at position p of a row (lut_stored_pos order; pair index for B = 3)
+    __device__ static constexpr uint32_t slot_of(uint32_t p)
+    {
+        return (kPair ? p << 2 : B == 4 ? (((p & 8u) << 3) | ((p & 7u) << 2)) : p << kLow) >> kLow;
+    }
+    // byte offset, from a lane's entry, of row r of its group
+    __device__ static constexpr int row_off(int r) { return kPair ? (r & 1) * 128 + (r >> 1) * (kEntries * 256) : (r & 1) * 2 + (r >> 1) * 128; }
+    // LDS address of the entry selected by byte J of the index word w, for a lane with base `lanebase` (< 128)
+    template <int J> __device__ static __forceinline__ uint32_t addr(uint32_t w, uint32_t lanebase)
+    {
+        return __builtin_amdgcn_perm(lanebase, w, 0x0c0c0004u | ((uint32_t)J << 8));
+    }
+};
+
+// LDS operations of a wave execute in order; this keeps the compiler from moving them across
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+struct FusedArgs {
+    const uint8_t *slices;
+    size_t slice_bytes;
+    const uint16_t *lut, *x; // XF: x in fragment order
+    uint16_t *y;
+    float *partial; // parts > 1: [part][batch row][row]
+    int M, K, batch, ntiles, parts;
+};
+
+// B bits, NJ tiles of 16 batch rows per workgroup, W waves (4 or 8).  blockIdx.y: part of the columns (the parts of a row
+// block are summed by reduce_parts_kernel).
+template <int B, int NJ, int W, bool XF>
+__global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
+{
+    using BT = BlockTable<B>;
+    const uint8_t *__restrict__ slices = a.slices;
+    const size_t slice_bytes = a.slice_bytes;
+    const uint16_t *__restrict__ lut = a.lut;
+    const uint16_t *__restrict__ x = a.x;
+    uint16_t *__restrict__ y = a.y;
+    const int M = a.M, K = a.K, batch = a.batch, ntiles = a.ntiles;
+    constexpr int kRows = 64, kGroups = 16, kStepChunks = 4, kNT = 16 * NJ;
+    constexpr int kRedRow = 16 * 16 + 16;               // bytes of one batch row of partial sums: 16 groups x 4 rows
+    constexpr int kRedTiles = NJ <= 4 ? NJ : 4;         // tiles of 16 batch rows summed at a time
+    constexpr int kRedBytes = W * kRedTiles * 16 * kRedRow;
+    constexpr int kBounceSlices = B <= 4 ? B : (B + 1) / 2;
+    constexpr int kBounce = (!XF && NJ > kBounceSlices ? NJ : kBounceSlices) * 1024;
+    constexpr int kMain = BT::kBytes + W * kBounce;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[kMain > kRedBytes ? kMain : kRedBytes];
+    uint8_t *tab = smem;
+    const int tid = threadIdx.x;
+    constexpr int nth = 64 * W;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    uint8_t *bounce = smem + BT::kBytes + wave * kBounce;
+
+    // workgroup -> (row block, batch tile): the batch tiles of a row block on one XCD (ids equal mod 8), next to each other
+    const int blocks = (M + kRows - 1) / kRows;
+    int rb, nt;
+    const int part = blockIdx.y;
+    {
+        const int id = blockIdx.x, per = 8 * ntiles, full = blocks / 8 * per;
+        if (id < full) {
+            rb = id / per * 8 + id % 8;
+            nt = id % per / 8;
+        } else {
+            const int rest = blocks % 8;
+            rb = blocks / 8 * 8 + (id - full) % rest;
+            nt = (id - full) / rest;
+        }
+    }
+    const int groups = (M + kRowsPerGroup - 1) / kRowsPerGroup;
+    const int g0 = rb * kGroups, row0 = rb * kRows, n0 = nt * kNT;
+    const int nrows = batch - n0 < kNT ? batch - n0 : kNT; // batch rows of this tile
+    const int chunks = K / kChunkSlots;
+    const int lastspan = (chunks - 1) / kSpanLanes;
+    const int ragged = chunks - lastspan * kSpanLanes;
+    const int nsteps = (chunks + kStepChunks - 1) / kStepChunks;
+    const int nfull = chunks / kStepChunks;
+
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, 0xffffffffu, kBufferRsrcWord3);
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(x + (size_t)n0 * K), 0, (uint32_t)nrows * (uint32_t)K * 2u, kBufferRsrcWord3);
+    const int i = lane & 15, kg = lane >> 4; // row group and chunk in the matrix instruction's order
+    const int p = lane & 3, ln = lane >> 2;  // chunk and row group / batch row in load order: 4 lanes read 64 contiguous bytes
+    const int gi = g0 + ln < groups ? ln : groups - 1 - g0;
+    const uint32_t soff = (uint32_t)(gi * chunks + p) * 16u;
+    const uint32_t bw = (uint32_t)(4 * ln + (p ^ ((ln >> 1) & 3))) * 16u, br = (uint32_t)(4 * i + (kg ^ ((i >> 1) & 3))) * 16u;
+    const uint32_t lanebase = (uint32_t)(lane & 31) << 2;
+    uint32_t xoff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) xoff[j] = 16 * j + ln < nrows ? (uint32_t)(16 * j + ln) * (uint32_t)K * 2u + (uint32_t)p * 16u : 0x80000000u;
+
+    const __amdgpu_buffer_rsrc_t xfrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(x + (size_t)nt * NJ * 512), 0, 0xffffffffu, kBufferRsrcWord3);
+    u32x4 Q[B], X[2][NJ];
+    auto load_q = [&](int st) {
+        const int left = chunks - st * kStepChunks;
+        const uint32_t off = p < left ? soff : soff - (uint32_t)(p - (left - 1)) * 16u;
+        const uint32_t sst = (uint32_t)st * (kStepChunks * 16u);
+#pragma unroll
+        for (int s = 0; s < B; ++s) Q[s] = __builtin_amdgcn_raw_buffer_load_b128(srsrc, off, sst + (uint32_t)s * (uint32_t)slice_bytes, 0);
+    };
+    auto load_x = [&](int st, int t) {
+        if constexpr (XF) {
+            const uint32_t xs = (uint32_t)((st * 4 + t) * ntiles * NJ) * 1024u;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) X[t & 1][j] = __builtin_amdgcn_raw_buffer_load_b128(xfrsrc, (uint32_t)lane * 16u, xs + j * 1024u, 0);
+            return;
+        }
+        const int span = st / (kSpanLanes / kStepChunks);
+        const int nl = span == lastspan ? ragged : kSpanLanes;
+        const uint32_t xs = (uint32_t)span * (kSpanCols * 2u) + (uint32_t)(st % (kSpanLanes / kStepChunks)) * (kStepChunks * 16u) + (uint32_t)(t * 16 * nl);
+        const bool in = p < chunks - st * kStepChunks;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) X[t & 1][j] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, in ? xoff[j] : 0x80000000u, xs, 0);
+    };
+
+    float4_t acc[NJ][kRowsPerGroup];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < kRowsPerGroup; ++r) acc[j][r] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+    // the waves split the row's steps evenly; a wave may get none (short rows)
+    const int slot = part * W + wave, slots = a.parts * W;
+    int st = (int)((long long)nsteps * slot / slots);
+    const int st1 = (int)((long long)nsteps * (slot + 1) / slots);
+    const bool any = st < st1;
+
+    // ---- tables: bank = copy * 16 + group; all loads go out before the slice loads
+    if constexpr (BT::kPair) {
+        // thread (bank, row r, parity of the entry): 32 pair entries from the row's 8 centroids
+        static_assert(nth >= 256, "4 rows x 32 banks x 2 parities");
+        const int bank = tid & 31, r = (tid >> 5) & 3, e0 = (tid >> 7) & 1;
+        const int row = row0 + (bank & 15) * 4 + r;
+        const u32x4 c = *reinterpret_cast<const u32x4 *>(lut + (size_t)(row < M ? row : M - 1) * 8);
+        if (any) { load_q(st); load_x(st, 0); load_x(st, 1); }
+        uint32_t ev[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ev[k] = e0 ? c[k] >> 16 : c[k] & 0xffffu;
+        uint8_t *dst = tab + e0 * 256 + bank * 4 + (r & 1) * 128 + (r >> 1) * (BT::kEntries * 256);
+        const int m0 = nth == 512 ? (tid >> 8) * 16 : 0; // wave-uniform
+        auto fill = [&](auto first) {
+#pragma unroll
+            for (int m = decltype(first)::value; m < decltype(first)::value + (nth == 512 ? 16 : 32); ++m) {
+                const int even = pair3_even(2 * m), odd = pair3_odd(2 * m); // the thread's parity is bit 0 of the even code
+                const uint32_t hi = (odd & 1) ? c[odd >> 1] & 0xffff0000u : c[odd >> 1] << 16;
+                *reinterpret_cast<uint32_t *>(dst + m * 512) = ev[even >> 1] | hi;
+            }
+        };
+        if (m0 == 0) fill(std::integral_constant<int, 0>{});
+        else fill(std::integral_constant<int, 16>{});
+    } else {
+        constexpr int kPieces = (2 << B) / 16; // 8 entries each
+        constexpr int kTasks = 64 * kPieces, kPer = (kTasks + nth - 1) / nth;
+        u32x4 lo[kPer], hi[kPer];
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const int k = tid + m * nth, bank = k & 31, rp = (k >> 5) & 1, pc = k >> 6 < kPieces ? k >> 6 : kPieces - 1;
+            const int ra = row0 + (bank & 15) * 4 + rp * 2, rlo = ra < M ? ra : M - 1, rhi = ra + 1 < M ? ra + 1 : M - 1;
+            lo[m] = reinterpret_cast<const u32x4 *>(lut + ((size_t)rlo << B))[pc];
+            hi[m] = reinterpret_cast<const u32x4 *>(lut + ((size_t)rhi << B))[pc];
+        }
+        if (any) { load_q(st); load_x(st, 0); load_x(st, 1); }
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const int k = tid + m * nth, bank = k & 31, rp = (k >> 5) & 1, pc = k >> 6;
+            uint8_t *dst = tab + rp * 128 + bank * 4;
+            if (kTasks % nth == 0 || k < kTasks)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<uint32_t *>(dst + BT::slot_of(8 * pc + e) * 256) =
+                        (e & 1) ? (lo[m][e >> 1] >> 16) | (hi[m][e >> 1] & 0xffff0000u) : (lo[m][e >> 1] & 0xffffu) | (hi[m][e >> 1] << 16);
+        }
+    }
+    __syncthreads();
+
+    // a wave's private exchange of 16-byte pieces from load order to the matrix instruction's order
+    auto exchange = [&](auto &v, int first, int n) {
+#pragma unroll
+        for (int k = 0; k < n; ++k) *reinterpret_cast<u32x4 *>(bounce + k * 1024 + bw) = v[first + k];
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < n; ++k) v[first + k] = *reinterpret_cast<const u32x4 *>(bounce + k * 1024 + br);
+        wave_lds_fence();
+    };
+    auto exchange_q = [&]() {
+        exchange(Q, 0, kBounceSlices);
+        if constexpr (B > kBounceSlices) exchange(Q, kBounceSlices, B - kBounceSlices);
+    };
+    uint32_t Wd[kRowsPerGroup][8]; // index words of the current step
+    u32x4 P[kRowsPerGroup];        // packed centroid pairs of the current run
+    auto merge = [&]() {
+#pragma unroll
+        for (int r = 0; r < kRowsPerGroup; ++r) {
+            uint32_t q[B];
+#pragma unroll
+            for (int s = 0; s < B; ++s) q[s] = Q[s][r];
+            merge_words<B, BT::kLow>(q, Wd[r]);
+            if constexpr (B < 8) {
+#pragma unroll
+                for (int u = 0; u < 8; u += BT::kPair ? 2 : 1) Wd[r][u] &= BT::kClean;
+            }
+        }
+    };
+    constexpr int kH = BT::kPair ? 1 : 2;
+    uint32_t R[kRowsPerGroup][kH][4]; // table entries of the next run
+    auto lookup = [&](int t) {
+#pragma unroll
+        for (int r = 0; r < kRowsPerGroup; ++r) {
+            const uint8_t *tr = tab + BT::row_off(r);
+#pragma unroll
+            for (int h = 0; h < kH; ++h) {
+                const uint32_t v = Wd[r][2 * t + h];
+                const uint32_t ad[4] = {BT::template addr<0>(v, lanebase), BT::template addr<1>(v, lanebase),
+                                        BT::template addr<2>(v, lanebase), BT::template addr<3>(v, lanebase)};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (BT::kPair) R[r][h][j] = *reinterpret_cast<const uint32_t *>(tr + ad[j]);
+                    else R[r][h][j] = *reinterpret_cast<const uint16_t *>(tr + ad[j]);
+                }
+            }
+        }
+    };
+    auto pack = [&]() {
+#pragma unroll
+        for (int r = 0; r < kRowsPerGroup; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (BT::kPair) P[r][j] = R[r][0][j];
+                else P[r][j] = R[r][0][j] | (R[r][1][j] << 16);
+            }
+    };
+    auto products = [&](int t) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < kRowsPerGroup; ++r)
+                acc[j][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, P[r]), __builtin_bit_cast(half8_t, X[t & 1][j]),
+                                                                   acc[j][r], 0, 0, 0);
+    };
+    if (any) {
+        exchange_q();
+        merge();
+        load_q(st + 1 < st1 ? st + 1 : st);
+        lookup(0);
+        if constexpr (!XF) exchange(X[0], 0, NJ);
+        pack();
+    }
+    const int stf = st1 < nfull ? st1 : nfull;
+    for (; st < stf; ++st) {
+        const int next = st + 1 < st1 ? st + 1 : st;    // the last pass loads and looks up its own step again
+        const int next2 = st + 2 < st1 ? st + 2 : next;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (t == 2) exchange_q();
+            if (t == 3) {
+                merge();
+                load_q(next2);
+            }
+            lookup((t + 1) & 3);
+            products(t);
+            load_x(t < 2 ? st : next, (t + 2) & 3);
+            if constexpr (!XF) exchange(X[(t + 1) & 1], 0, NJ);
+            pack();
+        }
+    }
+    if (st < st1) { // the ragged step: chunks past the row count for nothing
+        const uint32_t keep = kg < chunks - st * kStepChunks ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int r = 0; r < kRowsPerGroup; ++r) P[r] &= u32x4{keep, keep, keep, keep};
+            if (t < 3) lookup(t + 1);
+            products(t);
+            if (t < 2) load_x(st, t + 2);
+            if (t < 3) {
+                if constexpr (!XF) exchange(X[(t + 1) & 1], 0, NJ);
+                pack();
+            }
+        }
+    }
+
+    // ---- waves are added in fixed order, one tile of 16 batch rows at a time: element q of acc[j][r] is row group
+    // 4 kg + q (row r of it), batch row 16 j + i
+    const bool wide = M % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+#pragma unroll
+    for (int j0 = 0; j0 < NJ; j0 += kRedTiles) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kRedTiles; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4_t *>(smem + ((wave * kRedTiles + j) * 16 + i) * kRedRow + (4 * kg + q) * 16) =
+                    float4_t{acc[j0 + j][0][q], acc[j0 + j][1][q], acc[j0 + j][2][q], acc[j0 + j][3][q]};
+        __syncthreads();
+        for (int o = tid; o < 256 * kRedTiles; o += nth) {
+            const int nn = o >> 4, g = o & 15, n = 16 * j0 + nn;
+            float4_t s = *reinterpret_cast<const float4_t *>(smem + nn * kRedRow + g * 16);
+#pragma unroll
+            for (int w = 1; w < W; ++w) s += *reinterpret_cast<const float4_t *>(smem + (w * kRedTiles * 16 + nn) * kRedRow + g * 16);
+            const int row = row0 + 4 * g;
+            if (n < nrows && row < M && a.parts > 1) {
+                float *dst = a.partial + ((size_t)part * batch + n0 + n) * M + row;
+                if (M % 4 == 0) *reinterpret_cast<float4_t *>(dst) = s;
+                else
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (row + r < M) dst[r] = s[r];
+            } else if (n < nrows && row < M) {
+                uint16_t *dst = y + (size_t)(n0 + n) * M + row;
+                uint16_t hv[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) hv[r] = __builtin_bit_cast(uint16_t, __float2half_rn(s[r]));
+                if (wide) *reinterpret_cast<u32x2 *>(dst) = u32x2{hv[0] | ((uint32_t)hv[1] << 16), hv[2] | ((uint32_t)hv[3] << 16)};
+                else
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (row + r < M) dst[r] = hv[r];
+            }
+        }
+    }
+}
+
+
+// x (batch x K) in the order of the matrix instruction's B operand: 1 KB per (step of 4 chunks, run, 16 batch rows), zeros
+// for batch rows and chunks that do not exist.  A wave per step and tile of batch rows writes whole lines.
+__global__ __launch_bounds__(256) void fragment_x_kernel(const uint16_t *__restrict__ x, u32x4 *__restrict__ xf, int K, int batch, int tiles)
+{
+    const int chunks = K / kChunkSlots, steps = (chunks + 3) / 4;
+    const int st = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, tile = blockIdx.y;
+    if (st >= steps) return;
+    const int n = tile * 16 + (lane & 15), c = st * 4 + (lane >> 4);
+    const int span = c / kSpanLanes, rem = chunks - span * kSpanLanes, nl = rem < kSpanLanes ? rem : kSpanLanes;
+    const uint16_t *src = x + (size_t)n * K + (size_t)span * kSpanCols + (c % kSpanLanes) * 8;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        u32x4 v = {0, 0, 0, 0};
+        if (n < batch && c < chunks) v = *reinterpret_cast<const u32x4 *>(src + t * 8 * nl);
+        xf[((size_t)(st * 4 + t) * tiles + tile) * 64 + lane] = v;
+    }
+}
+
+// y = sum of the parts, in order (n = batch * M values each)
+__global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restrict__ partial, uint16_t *__restrict__ y, size_t n, int parts)
+{
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    if (n % 4 == 0) {
+        float4_t s = *reinterpret_cast<const float4_t *>(partial + i);
+        for (int p = 1; p < parts; ++p) s += *reinterpret_cast<const float4_t *>(partial + p * n + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[i + e] = __builtin_bit_cast(uint16_t, __float2half_rn(s[e]));
+    } else {
+        for (int e = 0; e < 4 && i + e < n; ++e) {
+            float s = partial[i + e];
+            for (int p = 1; p < parts; ++p) s += partial[p * n + i + e];
+            y[i + e] = __builtin_bit_cast(uint16_t, __float2half_rn(s));
+        }
+    }
+}
+
+template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, int blocks, uint8_t *work, size_t work_bytes, hipStream_t stream)
+{
+    constexpr bool kXF = NJ >= 4;
+    const int steps = (a.K / kChunkSlots + 3) / 4;
+    if (kXF) {
+        const int tiles = a.ntiles * NJ;
+        const size_t bytes = (size_t)steps * 4 * tiles * 1024;
+        hipLaunchKernelGGL(fragment_x_kernel, dim3((steps + 3) / 4, tiles), dim3(256), 0, stream, a.x, reinterpret_cast<u32x4 *>(work), a.K,
+                           a.batch, tiles);
+        a.x = reinterpret_cast<const uint16_t *>(work);
+        work += bytes;
+        work_bytes -= bytes;
+    }
+    // Parts: as many as give every CU one workgroup, a step or more per wave.  Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5
+    // batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3 batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096
+    // batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups costs more than idle CUs.
+    int parts = 256 / (blocks * a.ntiles);
+    if (parts > steps / W) parts = steps / W;
+    const size_t part_bytes = (size_t)a.batch * a.M * 4;
+    if (parts > 1 && (size_t)parts * part_bytes > work_bytes) parts = (int)(work_bytes / part_bytes);
+    a.parts = parts > 1 ? parts : 1;
+    a.partial = reinterpret_cast<float *>(work);
+    hipLaunchKernelGGL((gemm_fused_kernel<B, NJ, W, kXF>), dim3(blocks * a.ntiles, a.parts), dim3(64 * W), 0, stream, a);
+    if (a.parts > 1) {
+        const size_t n = (size_t)a.M * a.batch;
+        hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, a.partial, a.y, n, a.parts);
+    }
+    return hipGetLastError();
+}
+
+// 8 waves per workgroup when every workgroup has a CU of its own, else 4 (two workgroups per CU): 28672 x 8192 b = 4 batch 64
+// 65 -> 59 us with 4, 11008 x 4096 b = 4 batch 32 17.3 -> 20.3.
+template <int B, int NJ> static hipError_t launch_fused_nj(FusedArgs &a, uint8_t *work, size_t work_bytes, hipStream_t stream)
+{
+    const int blocks = (a.M + 63) / 64;
+    if ((long long)blocks * a.ntiles <= 256) return launch_fused_w<B, NJ, 8>(a, blocks, work, work_bytes, stream);
+    return launch_fused_w<B, NJ, 4>(a, blocks, work, work_bytes, stream);
+}
+
+template <int B> static hipError_t launch_fused_b(FusedArgs &a, int nj, uint8_t *work, size_t work_bytes, hipStream_t stream)
+{
+    switch (nj) {
+    case 1: return launch_fused_nj<B, 1>(a, work, work_bytes, stream);
+    case 2: return launch_fused_nj<B, 2>(a, work, work_bytes, stream);
+    case 3: return launch_fused_nj<B, 3>(a, work, work_bytes, stream);
+    }
+    return launch_fused_nj<B, 4>(a, work, work_bytes, stream);
+}
+
+hipError_t launch_gemm_fused(const GemvArgs &g, hipStream_t stream)
+{
+    if (!gemm_fused_ok(g)) return hipErrorInvalidValue;
+    int ntiles, nj;
+    fused_tiles(g.batch, &ntiles, &nj);
+    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, ntiles, 1};
+    uint8_t *w = static_cast<uint8_t *>(g.work);
+    const size_t work_bytes = g.work_bytes;
+    switch (g.b) {
+    case 3: return launch_fused_b<3>(a, nj, w, work_bytes, stream);
+    case 4: return launch_fused_b<4>(a, nj, w, work_bytes, stream);
+    case 5: return launch_fused_b<5>(a, nj, w, work_bytes, stream);
+    case 6: return launch_fused_b<6>(a, nj, w, work_bytes, stream);
+    case 7: return launch_fused_b<7>(a, nj, w, work_bytes, stream);
+    case 8: return launch_fused_b<8>(a, nj, w, work_bytes, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+} // namespace apgemv

@@ -24,7 +24,29 @@ struct GemvArgs {
                            // 7 / 8 = two row groups per workgroup at batch 1 whenever possible / never;
                            // 9 / 10 = the 16-row-tile matrix-core kernel (batch >= 2, K % 256 == 0) with one /
                            //          two tiles per workgroup
+    void *work = nullptr;  // not null = the fused large-batch kernel, with this scratch (device, 16-byte aligned)
+    size_t work_bytes = 0;
 };
+
+// The fused large-batch kernel (gemm_fused.hip) takes a product of up to kMaxFusedBatch batch rows straight from the packed form.
+constexpr int kMaxFusedBatch = 512;
+// Its tiling of the batch: `ntiles` tiles of up to 64 rows, evenly filled with `nj` times 16 rows.
+inline void fused_tiles(int batch, int *ntiles, int *nj)
+{
+    *ntiles = (batch + 63) / 64;
+    *nj = ((batch + 15) / 16 + *ntiles - 1) / *ntiles;
+}
+// Whether it takes the call with a.work_bytes of scratch (always for 48 rows of an aligned x): 16-byte loads of x, whose rows are
+// multiples of 64 bytes; from 49 rows on a copy of x in the scratch.
+inline bool gemm_fused_ok(const GemvArgs &a)
+{
+    if (reinterpret_cast<uintptr_t>(a.x) % 16 || a.batch < 1 || a.batch > kMaxFusedBatch) return false;
+    int ntiles, nj;
+    fused_tiles(a.batch, &ntiles, &nj);
+    if (nj < 4) return true;
+    const size_t copy = (size_t)((a.K / 32 + 3) / 4) * 4 * ntiles * nj * 1024;
+    return copy <= a.work_bytes && copy < 0xffffffffu;
+}
 
 constexpr int kMaxMulti = 8;
 struct MultiArgs { // passed by value as the kernel argument of a fused launch
@@ -67,8 +89,8 @@ hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t st
 hipError_t launch_dequantize(const GemvArgs &a, hipStream_t stream);
 hipError_t launch_probe_read(const void *dev_buf, size_t bytes, hipStream_t stream);
 hipError_t launch_probe_issue(int kind, int passes, hipStream_t stream);
-// Looks up, once per device, the device address of the static array ap_gemm_static writes the dense
-// weights to (the current device's copy); called where a matrix is set up on a device.
+// Looks up, once per device, the device address of the static array ap_gemm_static uses as
+// its workspace (the current device's copy); called where a matrix is set up on a device.
 bool static_scratch_setup();
 
 } // namespace apgemv

@@ -76,3 +76,60 @@ def test_gemm_path_llama_shape_sampled_rows(B):
     sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     assert B.lib.ap_gemm(pm.handle, 4, xd.data_ptr(), xd.data_ptr(), batch, work.data_ptr(), 1024, sp) == 5
     pm.close()
+
+
+# sizes at the edges of the fused kernel: tiles of 64 rows (16 groups of 4), steps of 4 chunks (128 columns) with a ragged
+# one, rows shorter than a step, several column parts (few row blocks, long rows), 1..4 tiles of 16 batch rows and several
+# batch tiles; M not a multiple of 4
+@pytest.mark.parametrize("M,K", [(1, 32), (63, 96), (65, 128), (130, 2048 + 160), (37, 9 * 2048 + 32), (260, 4096)])
+@pytest.mark.parametrize("batch", [1, 16, 17, 48, 49, 64, 65, 130])
+def test_fused_gemm_tile_edges(B, M, K, batch):
+    import torch
+    idx, luts, x = inputs.make_case(42, M, K, batch=batch)
+    pm = B.ap_pack(idx, luts)
+    guard = 64
+    xd = torch.from_numpy(x).cuda()
+    work = torch.empty(M * K * 2, dtype=torch.uint8, device="cuda")   # the smallest workspace the call accepts
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for b in ALL_BITS:
+        for static in (False, True):
+            buf = torch.full((guard + batch * M + guard,), -7.0, dtype=torch.float16, device="cuda")
+            yp = buf.data_ptr() + 2 * guard
+            if static:
+                assert B.lib.ap_gemm_static(pm.handle, b, xd.data_ptr(), yp, batch, sp) == 0
+            else:
+                assert B.lib.ap_gemm(pm.handle, b, xd.data_ptr(), yp, batch, work.data_ptr(), work.numel(), sp) == 0
+            torch.cuda.synchronize()
+            out = buf.cpu().numpy()
+            assert np.all(out[:guard] == -7.0) and np.all(out[-guard:] == -7.0)
+            check_against_oracle(out[guard:-guard].reshape(batch, M), idx, luts[b], b, x)
+    pm.close()
+
+
+def test_fused_gemm_non_finite_values_stay_where_they_are(B):
+    # infinities in a table (b = 3, 8) and in one activation reach exactly the outputs that use them, also next to the ragged
+    # last step; an x that is not 16-byte aligned gives the same values by the other route
+    import torch
+    M, K, batch = 70, 2048 + 160, 20
+    idx, luts, x = inputs.make_case(43, M, K, batch=batch)
+    x[3, K - 1] = np.float16(np.inf)
+    for b in (3, 8):
+        lut = luts[b].copy()
+        lut[5, :] = np.abs(lut[5, :])
+        lut[5, (1 << b) - 1] = np.float16(np.inf)
+        w = lut[np.arange(M)[:, None], idx >> (8 - b)].astype(np.float64)
+        with np.errstate(invalid="ignore"):
+            ref = (x.astype(np.float64)[:, None, :] * w[None]).sum(axis=2)
+        pm = B.ap_pack(idx, {b: lut})
+        xd = torch.from_numpy(x).cuda()
+        shifted = torch.empty(batch * K + 1, dtype=torch.float16, device="cuda")[1:].view(batch, K)
+        shifted.copy_(xd)
+        ys = [B.ap_gemm(pm, b, xd), B.ap_gemm(pm, b, shifted)]
+        torch.cuda.synchronize()
+        for y in ys:
+            got = y.cpu().numpy().astype(np.float64)
+            finite = np.isfinite(ref)
+            assert np.array_equal(np.isnan(got), np.isnan(ref))
+            assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+            assert np.allclose(got[finite], ref[finite], rtol=2e-3, atol=1e-3 * np.abs(ref[finite]).max())
+        pm.close()
