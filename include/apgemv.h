@@ -109,8 +109,8 @@ ap_status ap_unpack(const ap_matrix *h, uint8_t *idx_host_out, void *stream);
  *   x_dev  device, batch*K binary16 row-major, 16-byte aligned
  *   y_dev  device, batch*M binary16 row-major, 2-byte aligned; must not overlap x_dev or the blob
  *   batch  1..16 (the paper switches to a dequantise + dense GEMM path above about 16, Section 6.2).
- *          The kernels take up to 8 activation rows; batches 9..16 run as two passes on the stream, the
- *          first over rows 0..7, and cost what the two batches cost separately
+ *          Batches 9..16 run as one launch on matrices of about 1024 rows or more, else (and with a tuning override) as
+ *          two passes on the stream, the first over rows 0..7
  * Products are exact in binary32, accumulation is binary32, the result is rounded to binary16
  * (round to nearest even).  Asynchronous on `stream`; allocates nothing, synchronises nothing,
  * never repacks; the bit-width is chosen per call.  Results are deterministic (no atomics).
@@ -138,7 +138,7 @@ ap_status ap_gemv(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int
  *                             AP_VARIANT_PAIR / AP_VARIANT_NO_PAIR = at batch 1: the kernel with two
  *                             groups of 4 rows per workgroup whenever every span has its own wave
  *                             (2048 < K <= 16384) / never (the default);
- *                             AP_VARIANT_TILE / AP_VARIANT_TILE2 = at batch >= 2, K % 256 == 0: the
+ *                             AP_VARIANT_TILE / AP_VARIANT_TILE2 = at batch 2..8, K % 256 == 0: the
  *                             matrix-core kernel that works on tiles of 16 rows, with one / two
  *                             tiles per workgroup
  * AP_ERR_INVALID_ARG for an unknown option or a value outside its range.

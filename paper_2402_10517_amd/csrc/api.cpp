@@ -187,14 +187,7 @@ extern "C" ap_status ap_gemv(const ap_matrix *h, int b, const void *x_dev, void 
     a.row_groups_per_wg = h->row_groups_per_wg;
     a.mfma_min_batch = h->mfma_min_batch;
     a.variant = h->variant;
-    // the kernels take up to 8 activation rows: larger batches in passes of 8 rows
-    for (int first = 0; first < batch; first += AP_MAX_MULTI_BATCH) {
-        a.x = static_cast<const uint16_t *>(x_dev) + (size_t)first * a.K;
-        a.y = static_cast<uint16_t *>(y_dev) + (size_t)first * a.M;
-        a.batch = batch - first < AP_MAX_MULTI_BATCH ? batch - first : AP_MAX_MULTI_BATCH;
-        if (launch_gemv(a, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
-    }
-    return AP_OK;
+    return launch_gemv(a, static_cast<hipStream_t>(stream)) == hipSuccess ? AP_OK : AP_ERR_HIP;
 }
 
 static ap_status fill_args(const ap_matrix *h, int b, GemvArgs *a)

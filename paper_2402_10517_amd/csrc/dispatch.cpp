@@ -5,6 +5,29 @@
 
 namespace apgemv {
 
+// Whether the matrix-core kernel on tiles of 16 rows is the fastest for a call without tuning overrides.  Time of the kernels below
+// (batch 9 and more: in two passes) over its time, at M x K and b = 3 / 5 / 8:
+//   batch 9       1024x4096 1.30/1.23/1.09  1024x20480 0.97/0.91/0.85  512x1024 1.80/1.26/1.47  2048x20480 1.32/1.23/1.15
+//   batch 16      1024x11008 1.37/1.25/1.08  1024x4192 1.27/1.02/0.93  4096x4096 1.58/1.62/1.68  28000x4192 3.59/3.16/2.36
+//   batch 5       1024x4096 1.08/0.92/0.77  2048x1024 1.25/0.92/0.94  2048x4192 1.13/0.95/0.78  2048x8224 1.16/0.95/0.79
+//                 3072x1024 1.32/0.96/1.01  3072x4096 1.60/1.38/1.18  4099x2208 1.42/1.13/0.99  28000x2208 2.52/2.02/1.50
+//   batch 3, 4    2048x11008 1.00/1.01/0.78  3072x4096 1.15/1.03/0.96  3072x11008 1.33/1.38/1.03  3072x20480 1.22/1.34/0.97
+//                 4096x4096 1.25/1.10/1.02  4096x11008 1.91/1.72/1.51  4099x4192 0.92/0.74/0.70  4099x8224 1.30/1.17/1.03
+//                 8192x2208 1.15/1.03/0.85  8192x4192 1.19/1.01/0.82  13824x8224 1.79/1.68/1.18  28000x4192 1.31/1.14/0.81
+//   batch 2       4096x4096 1.01/0.95/0.92  6144x11008 0.77/0.77/0.77
+// At batch 3 and 4, rows below 8192 columns and a multiple of 256: from 2048 row groups on it wins by 5 to 40 % over the
+// matrix-core kernels below at every b.
+static bool tile_pays(const GemvArgs &a)
+{
+    const int groups = padded_rows(a.M) / kRowsPerGroup;
+    if (a.batch >= 9) return groups >= 512 || (groups >= 256 && a.b <= 5 && a.K <= 12288) || (groups >= 128 && a.K <= 1024);
+    if (a.batch >= 5) return groups >= 768 || (groups >= 512 && a.b == 3);
+    if (a.batch < 3) return false;
+    if (a.K >= 8192) return groups >= 768;
+    if (a.K % 256 == 0) return groups >= 2048 || (groups >= 768 && a.b <= 4 && a.K >= 4096);
+    return groups >= 2048 && a.b == 3;
+}
+
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
 {
     if (a.b < 3 || a.b > 8) return hipErrorInvalidValue;
@@ -14,22 +37,24 @@ hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
     // and 8 copies of every table; measured slower than the shared-table kernel on every Llama shape
     // (b = 8: 8.2 / 17.7 / 19.6 us against 6.8 / 12.0 / 12.7 us on the 7B shapes), so only on request.
     if (a.batch == 1 && B >= 7 && a.variant == 5) return launch_quad(a, stream);
-    // The matrix-core kernel on tiles of 16 rows (K % 256 == 0).  Measured on the 7B, 13B and 70B shapes at
-    // batch 2, 3, 4, 6, 8 against the kernels below: at batch >= 5 it wins on every matrix with at least
-    // 1024 groups of rows (5 to 60 %, most at small b and long rows); at batch 3 and 4 it wins by 5 to
-    // 40 % on matrices with at least 2048 groups of rows and on rows of 16384 columns or more (level at
-    // b = 5, 6 on 28672 x 8192) and loses on smaller ones; at batch 2, and on 1024 x 8192 at every
-    // batch, the ALU kernels are faster.
-    // variant: 9 / 10 = this kernel with one / two tiles per workgroup whenever the shape allows; any
-    // other tuning override keeps the call away from it.
-    if (a.batch >= 2 && a.K % 256 == 0) {
-        const int groups = padded_rows(a.M) / kRowsPerGroup;
-        const bool tuned = a.row_groups_per_wg >= 0 || a.mfma_min_batch != 0 || a.waves_per_group != 0;
-        const bool pays = a.variant == 0 && !tuned && groups >= 1024 &&
-                          (a.batch >= 5 || (a.batch >= 3 && (a.K >= 16384 || groups >= 2048)));
-        if (a.variant == 9 || a.variant == 10 || pays) return launch_matrix_tile(a, stream);
+    // variant: 9 / 10 = the kernel on tiles of 16 rows with one / two tiles per workgroup at K % 256 == 0; any other tuning
+    // override keeps the call away from it.
+    const bool tuned = a.variant != 0 || a.row_groups_per_wg >= 0 || a.mfma_min_batch != 0 || a.waves_per_group != 0;
+    const bool forced = (a.variant == 9 || a.variant == 10) && a.K % 256 == 0;
+    if (a.batch > kMaxMulti) {
+        if (!tuned && tile_pays(a)) return launch_matrix_tile(a, stream);
+        // the other kernels take up to 8 activation rows: two passes
+        GemvArgs pass = a;
+        pass.batch = kMaxMulti;
+        const hipError_t e = launch_gemv(pass, stream);
+        if (e != hipSuccess) return e;
+        pass.x = a.x + (size_t)kMaxMulti * a.K;
+        pass.y = a.y + (size_t)kMaxMulti * a.M;
+        pass.batch = a.batch - kMaxMulti;
+        return launch_gemv(pass, stream);
     }
-    // What is left for batch >= 2 (K not a multiple of 256, smaller matrices, batch 2..4) was settled by
+    if (a.batch >= 2 && (forced || (!tuned && tile_pays(a)))) return launch_matrix_tile(a, stream);
+    // What is left for batch >= 2 (smaller matrices, batch 2..4) was settled by
     // measurement on the 70B shapes (8192x8192, 28672x8192, 8192x28672; all b):
     //  * batch 2: the plain kernel (one group of rows per workgroup) wins everywhere;
     //  * batch 5..8 with >= 2048 groups of rows: the matrix-core kernel with in-wave exchange, every b

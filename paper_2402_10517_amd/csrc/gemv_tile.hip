@@ -25,6 +25,9 @@
 //     halves multiply one quad's weights with the other quad's activations and are dropped, so each
 //     quad has its own accumulator and the final sum takes column n of one and n + 8 of the other.
 //     Batch rows that do not exist read zeros (their buffer offset is out of range: no memory traffic).
+//   * Batch 9..16 (WIDE): every quad of chunks has activations of its own (two loads per run, 16 batch rows x 64 contiguous bytes
+//     each), and all 16 columns of both products count.  Against two passes of 8 rows, batch 16, b = 4: 4096 x 4096 11.8 -> 7.0 us,
+//     11008 x 4096 20.3 -> 15.4, 28672 x 8192 68 -> 43.
 //   * One instruction takes one run of 8 consecutive columns: their indices are the bytes of the
 //     merged words of the run's even and odd slots, the activations the lane's 16 bytes of that run.
 //   * The LDS serves 32 lanes per clock, here 16 rows x 2 lane groups, so every (row, lane group
@@ -43,7 +46,9 @@
 //     alternating runs at batch 8: 28672 x 8192 46 -> 39 us, 8192 x 8192 16 -> 13.5, 8192 x 28672
 //     46 -> 36), once the table build is cheap (below); in the batch-1 kernel, where all 64 lanes gather
 //     from one row's 256 dwords, the bank conflicts eat the gain.
-// Requires K % 256 == 0 (an octet is entirely inside or outside a ragged last span) and batch <= 8.
+// Rows that are not a multiple of 256 columns end with an octet of fewer chunks (RAG: chunks that do not exist load the last
+// one again, their centroids are masked to zero before the matrix instruction and their activations read as zeros; one fast
+// operation per pair of columns).
 #include <type_traits>
 #include "device_common.h"
 #include "launchers.h"
@@ -75,8 +80,9 @@ template <int B> struct TileTable {
     }
 };
 
-// `wg` = index of the workgroup within its matrix (R tiles each).
-template <int B, int R, int MAXT>
+// `wg` = index of the workgroup within its matrix (R tiles each).  RAG: K is not a multiple of 256 (the last octet holds fewer than 8
+// chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.
+template <int B, int R, int MAXT, bool RAG, bool WIDE>
 __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut,
                                                const uint16_t *__restrict__ x, uint16_t *__restrict__ y, int M, int K, int batch,
                                                int wg)
@@ -130,10 +136,13 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // the end with any scalar offset).  This lane then takes batch row i & 7, chunk 4 (i >> 3) + kg.
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(x), 0, (uint32_t)batch * (uint32_t)K * 2u, kBufferRsrcWord3);
-    const uint32_t xoff_lane = (lane >> 3) < batch ? (uint32_t)(lane >> 3) * (uint32_t)K * 2u +
-                                                         (uint32_t)((lane & 7) ^ ((lane >> 5) << 1)) * 16u
-                                                   : 0x80000000u;
-    const int xperm_src = (((i & 7) << 3) | ((i >> 3) << 2) | (kg ^ (((i >> 2) & 1) << 1))) << 2; // byte address of the source lane
+    // WIDE: one load per quad of chunks instead, lane 4 n + p with batch row n, chunk p ^ 2 (n / 8) of the quad (4 lanes = 64
+    // contiguous bytes); this lane takes batch row i, chunk kg of either quad, and column i of both products counts.
+    constexpr int kXSets = WIDE ? 2 : 1;
+    const int xn = WIDE ? lane >> 2 : lane >> 3, xc = WIDE ? (lane & 3) ^ ((lane >> 5) << 1) : (lane & 7) ^ ((lane >> 5) << 1);
+    const uint32_t xoff_lane = xn < batch ? (uint32_t)xn * (uint32_t)K * 2u + (uint32_t)xc * 16u : 0x80000000u;
+    const int xperm_src = (WIDE ? (i << 2) | (kg ^ ((i >> 3) << 1))
+                                : ((i & 7) << 3) | ((i >> 3) << 2) | (kg ^ (((i >> 2) & 1) << 1))) << 2; // byte address of the source lane
     const uint32_t rowbase = ((uint32_t)i << 2) | ((uint32_t)(kg & 1) << 6);
     uint32_t seven = 7; // shift amount of the 4-bit pair path's addresses, kept in a register (SDWA operand)
     asm("" : "+v"(seven));
@@ -148,30 +157,38 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // wait before the arithmetic leaves exactly the newer loads in flight: a row with an odd number of
     // octets gets one more whose activations are read as zeros (offset out of range), and the loads
     // issued in the last pass for the pass after it repeat a valid octet and are dropped.
-    auto issue = [&](int o, bool real, u32x4 (&X)[4], uint32_t (&Q)[R][2][B]) {
+    auto issue = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B]) {
         const int span = o >> 3, oi = o & 7;
         const int rem = chunks - span * kSpanLanes;
         const int nl = rem < kSpanLanes ? rem : kSpanLanes;
         const uint32_t xs = (uint32_t)span * (kSpanCols * 2u) + (uint32_t)oi * 128u;
-        const uint32_t xoff = real ? xoff_lane : 0x80000000u;
+        const int left = chunks - o * 8; // chunks of this octet and beyond
 #pragma unroll
-        for (int t = 0; t < 4; ++t) X[t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl), 0);
+        for (int q = 0; q < kXSets; ++q) {
+            const uint32_t xoff = real && (!RAG || xc + 4 * q < left) ? xoff_lane : 0x80000000u;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl + q * 64), 0);
+        }
         const uint32_t soct = (uint32_t)o * 128u;
+        const uint32_t back = RAG && lc >= left ? (uint32_t)(lc - (left - 1)) * 16u : 0u; // chunks that do not exist: the last one again
 #pragma unroll
         for (int tile = 0; tile < R; ++tile)
 #pragma unroll
             for (int s = 0; s < B; ++s)
 #pragma unroll
                 for (int half = 0; half < 2; ++half)
-                    Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane[tile][half],
+                    Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane[tile][half] - back,
                                                                             soct + (uint32_t)s * (uint32_t)slice_bytes, kBufferNonTemporal);
     };
-    auto compute = [&](const u32x4 (&Xl)[4], const uint32_t (&Q)[R][2][B]) {
-        u32x4 X[4];
+    auto compute = [&](const u32x4 (&Xl)[kXSets][4], const uint32_t (&Q)[R][2][B], int o) {
+        u32x4 X[kXSets][4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int q = 0; q < kXSets; ++q)
 #pragma unroll
-            for (int d = 0; d < 4; ++d) X[t][d] = (uint32_t)__builtin_amdgcn_ds_bpermute(xperm_src, (int)Xl[t][d]);
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) X[q][t][d] = (uint32_t)__builtin_amdgcn_ds_bpermute(xperm_src, (int)Xl[q][t][d]);
+        const uint32_t keep[2] = {kg < chunks - o * 8 ? 0xffffffffu : 0u, kg + 4 < chunks - o * 8 ? 0xffffffffu : 0u}; // RAG
 #pragma unroll
         for (int tile = 0; tile < R; ++tile) {
             const uint8_t *tt = tab + tile * TT::kTileBytes;
@@ -249,22 +266,29 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 #pragma unroll
                         for (int j = 0; j < 4; ++j) P[h][j] = we[h][j] | (wo[h][j] << 16);
                 }
-                // both quads against the same B: columns 0..7 of the first product and 8..15 of the second count
+                if constexpr (RAG) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) P[h][j] &= keep[h];
+                }
+                // both quads against the same B: columns 0..7 of the first product and 8..15 of the second count (WIDE: each quad
+                // against its own, all columns count)
                 const u32x4 a0 = {P[0][0], P[0][1], P[0][2], P[0][3]}, a1 = {P[1][0], P[1][1], P[1][2], P[1][3]};
-                acc[tile][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, X[t]),
+                acc[tile][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, X[0][t]),
                                                                       acc[tile][0], 0, 0, 0);
-                acc[tile][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, X[t]),
+                acc[tile][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, X[kXSets - 1][t]),
                                                                       acc[tile][1], 0, 0, 0);
             }
         }
     };
 
-    const int nocts = chunks >> 3; // K % 256 == 0
+    const int nocts = (chunks + 7) >> 3;
     const int npairs = (nocts + 1) >> 1;
     const int p1 = (int)((long long)npairs * (wave + 1) / nwaves);
-    u32x4 XA[4], XB[4];
+    u32x4 XA[kXSets][4], XB[kXSets][4];
     uint32_t QA[R][2][B], QB[R][2][B];
-    int p = (int)((long long)npairs * wave / nwaves); // < p1: the launcher starts no more waves than pairs
+    int p = (int)((long long)npairs * wave / nwaves); // < npairs (a wave without pairs loads one and drops it)
     // ---- tables of the R tiles into LDS (rows past the matrix repeat the last row; never stored).
     // Thread (row = tid % 16, copy = (tid / 16) % 2, part = tid / 32) writes the entries of the pieces
     // part, part + nparts, ... of its row and copy: the 32 lanes of an LDS clock hit 32 different banks
@@ -392,12 +416,13 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 
     for (; p < p1; ++p) {
         const bool second = 2 * p + 1 < nocts;
-        issue(second ? 2 * p + 1 : 2 * p, second, XB, QB);
+        const int o1 = second ? 2 * p + 1 : 2 * p;
+        issue(o1, second, XB, QB);
         __builtin_amdgcn_sched_barrier(0); // keep the loads ahead of the arithmetic they overlap with
-        compute(XA, QA);
+        compute(XA, QA, 2 * p);
         issue(p + 1 < p1 ? 2 * p + 2 : 2 * p, true, XA, QA);
         __builtin_amdgcn_sched_barrier(0);
-        compute(XB, QB);
+        compute(XB, QB, o1);
     }
 
     // ---- acc[tile][h][r] of lane (i, kg): output row 4 kg + r of the tile over the wave's columns of quad
@@ -407,12 +432,15 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][tile][4 * kg + r][i] = i < 8 ? acc[tile][0][r] : acc[tile][1][r];
+        for (int r = 0; r < 4; ++r)
+            red[wave][tile][4 * kg + r][i] = WIDE ? acc[tile][0][r] + acc[tile][1][r] : i < 8 ? acc[tile][0][r] : acc[tile][1][r];
     __syncthreads();
-    for (int o = tid; o < R * kTileRows * 8; o += nth) {
-        const int n = o & 7, r = o >> 3; // r = row inside the workgroup's R tiles
+    constexpr int kCols = WIDE ? 16 : 8;
+    for (int o = tid; o < R * kTileRows * kCols; o += nth) {
+        const int n = o % kCols, r = o / kCols; // r = row inside the workgroup's R tiles
         float s = 0.f;
-        for (int w = 0; w < nwaves; ++w) s += red[w][r >> 4][r & 15][n] + red[w][r >> 4][r & 15][n + 8];
+        for (int w = 0; w < nwaves; ++w)
+            s += WIDE ? red[w][r >> 4][r & 15][n] : red[w][r >> 4][r & 15][n] + red[w][r >> 4][r & 15][(n + 8) & 15];
         const int row = row0 + r;
         if (row < M && n < batch) {
             const __half hv = __float2half_rn(s);
@@ -421,12 +449,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     }
 }
 
-template <int B, int R, int MAXT>
+template <int B, int R, int MAXT, bool RAG, bool WIDE>
 __global__ __launch_bounds__(MAXT) void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
                                                          const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
                                                          uint16_t *__restrict__ y, int M, int K, int batch)
 {
-    gemv_tile_body<B, R, MAXT>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x);
+    gemv_tile_body<B, R, MAXT, RAG, WIDE>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x);
 }
 
 // Several matrices of equal row length at one bit-width and batch in one launch (the projections of a
@@ -439,7 +467,7 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a)
 #pragma unroll
     for (int i = 1; i < kMaxMulti; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) m = i;
-    gemv_tile_body<B, 1, MAXT>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
+    gemv_tile_body<B, 1, MAXT, false, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
                                (int)blockIdx.x - a.group_begin[m]);
 }
 
@@ -452,19 +480,29 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int ba
     for (int i = 1; i < kMaxListItems; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) it = i;
     const ListItem &I = a.item[it];
-    gemv_tile_body<B, 1, MAXT>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it]);
+    gemv_tile_body<B, 1, MAXT, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it]);
 }
 
-template <int B, int R> static hipError_t launch_tile_r(const GemvArgs &a, hipStream_t stream)
+template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArgs &a, hipStream_t stream)
 {
     constexpr int kMaxWaves = 8;
-    const int npairs = (a.K / (8 * kChunkSlots) + 1) / 2;
-    // short rows: 4 waves, so that a wave still runs several passes of its loop
-    int nw = a.waves_per_group > 0 ? a.waves_per_group : a.K >= 12288 ? kMaxWaves : 4;
-    if (nw > npairs) nw = npairs;
+    const int npairs = ((a.K + 255) / 256 + 1) / 2;
     const int tiles = (a.M + 15) / 16;
-    hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves>), dim3((tiles + R - 1) / R), dim3(64 * nw), 0, stream, a.slices,
-                       a.slice_bytes, a.lut, a.x, a.y, a.M, a.K, a.batch);
+    // 4 waves, so that a wave still runs several passes of its loop; 8 on long rows, and where a tile has a CU (nearly) to
+    // itself: 4096 x 11008 b = 4 batch 4 11.7 -> 9.3 us, 4096 x 4096 6.2 -> 5.4, 4099 x 2208 b = 7 batch 5 9.4 -> 8.8, but
+    // 8192 x 8192 b = 4 batch 8 11.9 -> 12.2.  At 9 to 16 batch rows 4 stay ahead (4096 x 4096 7.3 against 7.9).  A handle
+    // that asks for this kernel keeps the rule of the fused launches, with which it promises equal bits.
+    int nw = !WIDE && (a.K >= 12288 || (a.variant == 0 && tiles <= 320)) ? kMaxWaves : 4;
+    if (a.waves_per_group > 0) nw = a.waves_per_group;
+    if (nw > npairs) nw = npairs;
+    if (nw < 4 && a.waves_per_group == 0) nw = 4; // short rows: waves without columns help to build the tables (512 x 512 b = 4: 14.0 -> 4.3)
+    const dim3 grid((tiles + R - 1) / R), block(64 * nw);
+    if (a.K % 256)
+        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, true, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
+                           a.y, a.M, a.K, a.batch);
+    else
+        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, false, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
+                           a.y, a.M, a.K, a.batch);
     return hipGetLastError();
 }
 
@@ -475,9 +513,12 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
     // arithmetic) on matrices tall enough to fill the device with half as many workgroups (28672 x 8192 at
     // batch 4 and 8: 29-34 -> 28 us; 8192 x 8192: 11.8 -> 12.5, so not there)
     const int tiles = (a.M + 15) / 16;
-    const int r = a.variant == 9 ? 1 : a.variant == 10 ? 2 : (a.K >= 16384 || (B == 3 && tiles >= 1536)) ? 2 : 1;
-    if (r == 2) return launch_tile_r<B, 2>(a, stream);
-    return launch_tile_r<B, 1>(a, stream);
+    const bool two = a.variant == 10 || (a.variant != 9 && ((a.K >= 16384 && tiles >= 512) || (B == 3 && tiles >= 1536)));
+    if (a.batch <= 8) return two ? launch_tile_r<B, 2, false>(a, stream) : launch_tile_r<B, 1, false>(a, stream);
+    // with twice the activations two tiles take about 0.8 of the time per tile, unless that leaves the CUs more unevenly
+    // loaded: 28672 x 8192 b = 4 batch 16 57.1 -> 43.2 us, 8192 x 8192 18.0 -> 15.2, 11008 x 4096 b = 8 22.2 -> 24.0
+    const bool wide_two = tiles >= 448 && 1.6 * ((tiles + 511) / 512) < (tiles + 255) / 256;
+    return wide_two ? launch_tile_r<B, 2, true>(a, stream) : launch_tile_r<B, 1, true>(a, stream);
 }
 
 template <int B> static hipError_t launch_tile_multi_b(MultiArgs &m, int total_tiles, hipStream_t stream)
@@ -541,7 +582,7 @@ hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t st
     return hipErrorInvalidValue;
 }
 
-// batch <= 8, K % 256 == 0 (the dispatcher checks)
+// batch 2..16
 hipError_t launch_matrix_tile(const GemvArgs &a, hipStream_t stream)
 {
     switch (a.b) {

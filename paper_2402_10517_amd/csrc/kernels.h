@@ -22,7 +22,7 @@ struct GemvArgs {
                            // 3 = that kernel whenever the shape allows it (batch >= 2, K % 128 == 0);
                            // 5 = the bank-per-lane kernel at batch 1, b >= 7;
                            // 7 / 8 = two row groups per workgroup at batch 1 whenever possible / never;
-                           // 9 / 10 = the 16-row-tile matrix-core kernel (batch >= 2, K % 256 == 0) with one /
+                           // 9 / 10 = the 16-row-tile matrix-core kernel (batch 2..8, K % 256 == 0) with one /
                            //          two tiles per workgroup
     void *work = nullptr;  // not null = the fused large-batch kernel, with this scratch (device, 16-byte aligned)
     size_t work_bytes = 0;

@@ -619,3 +619,43 @@ def test_issue_probe_runs_every_kind(B):
         assert B.lib.ap_probe_issue(kind, 3, None) == 0
     torch.cuda.synchronize()
 
+
+
+@pytest.mark.parametrize("batch", [3, 5, 8, 9, 13, 16])
+def test_tile_kernel_on_ragged_rows_and_at_batch_nine_to_sixteen(B, batch):
+    # matrices tall enough for the dispatcher to choose the kernel by itself: rows of fewer chunks than an octet, an octet
+    # of 1, 4 or 7 chunks at the end, an odd number of octets, whole octets (batch 9 and more), a last tile of fewer than
+    # 16 rows and one or two tiles per workgroup; canaries around y.  An infinity in the table of one row and in the last
+    # column of x reaches exactly the outputs that use it.
+    import ctypes
+    import torch
+    shapes = [(8195, 32), (3073, 8192 + 32), (4099, 8192 + 128 + 96), (8196, 256 + 224), (4100, 512), (15363, 768)]
+    for (M, K) in shapes:
+        rows = np.unique(np.concatenate([np.arange(20), np.random.default_rng(M).integers(0, M, size=60), np.arange(M - 20, M)]))
+        idx, luts, x = inputs.make_case(44, M, K, batch=batch, sigma=0.01)
+        guard = 64
+        sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        for b in ALL_BITS:
+            pm = B.ap_pack(idx, {b: luts[b]})
+            xd = torch.from_numpy(x).cuda()
+            ybuf = torch.full((guard + batch * M + guard,), -7.0, dtype=torch.float16, device="cuda")
+            assert B.lib.ap_gemv(pm.handle, b, xd.data_ptr(), ybuf.data_ptr() + 2 * guard, batch, sp) == 0
+            torch.cuda.synchronize()
+            out = ybuf.cpu().numpy()
+            assert np.all(out[:guard] == -7.0) and np.all(out[-guard:] == -7.0)
+            check_against_oracle(out[guard:-guard].reshape(batch, M), idx, luts[b], b, x, rows=rows)
+            pm.close()
+    M, K, b = 3073, 8192 + 32, 5
+    idx, luts, x = inputs.make_case(45, M, K, batch=batch, bit_widths=[b])
+    luts[b][7, :] = np.abs(luts[b][7, :])
+    luts[b][7, 31] = np.float16(np.inf)
+    x[1, K - 1] = np.float16(-np.inf)
+    pm = B.ap_pack(idx, luts)
+    got = run_gemv(pm, b, x).astype(np.float64)
+    w = luts[b][np.arange(64)[:, None], idx[:64] >> (8 - b)].astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = (x.astype(np.float64)[:, None, :] * w[None]).sum(axis=2)
+    assert np.array_equal(np.isnan(got[:, :64]), np.isnan(ref))
+    assert np.array_equal(got[:, :64][np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.all(np.isfinite(got[:, 64:]) | (np.arange(batch) == 1)[:, None])
+    pm.close()
