@@ -141,8 +141,15 @@ def ap_read_extent(M, K, n, mask, b):
     return tuple(a.value for a in v)
 
 
+# The current stream's address without a Stream object around it: torch.cuda.current_stream() takes 2.7 us, a third of the host
+# time of a small call (ap_gemv on 512 x 512: 9.0 -> 6.6 us), this 0.2 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if torch is not None else None
+
+
 def _stream_ptr(stream):
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device()), None
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream), stream
 
