@@ -403,7 +403,8 @@ extern "C" ap_status ap_gemm_workspace_size(const ap_matrix *h, size_t *bytes)
 // rocBLAS computes the product.  The fused kernel dequantises once per 64 batch rows, at b = 3 for half the cost.  Measured,
 // us, dequantise + rocBLAS / fused, batch 256 / 384 / 512: 8192x8192 b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111,
 // b = 8 115/68 108/97 118/126; 11008x4096 b = 3 69/38 69/54 75/66, b = 5 72/48 72/70 77/85, b = 8 74/57 76/84 81/101;
-// 4096x11008 b = 8 81/52 89/82 101/87.
+// 4096x11008 b = 8 81/52 89/82 101/87.  Up to 16 batch rows the kernels of ap_gemv are ahead of it too: batch 16, fused / ap_gemv,
+// 11008x4096 b = 4 15.8/15.4, 28672x8192 46/43, 4096x4096 b = 5 batch 12 11.3/7.5.
 static int fused_max_batch(int b) { return b == 3 ? kMaxFusedBatch : b <= 5 ? 384 : 256; }
 
 extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,
@@ -422,6 +423,13 @@ extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void 
     a.x = static_cast<const uint16_t *>(x_dev);
     a.y = static_cast<uint16_t *>(y_dev);
     a.batch = batch;
+    if (batch <= AP_MAX_BATCH && reinterpret_cast<uintptr_t>(x_dev) % 16 == 0) { // as ap_gemv on a handle without options
+        a.waves_per_group = 0;
+        a.row_groups_per_wg = -1;
+        a.mfma_min_batch = 0;
+        a.variant = AP_VARIANT_AUTO;
+        return launch_gemv(a, st) == hipSuccess ? AP_OK : AP_ERR_HIP;
+    }
     a.work = work_dev;
     a.work_bytes = work_bytes;
     if (batch <= fused_max_batch(b) && gemm_fused_ok(a)) return launch_gemv(a, st) == hipSuccess ? AP_OK : AP_ERR_HIP;

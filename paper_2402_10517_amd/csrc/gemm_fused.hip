@@ -442,7 +442,7 @@ template <int B, int NJ> static hipError_t launch_fused_nj(FusedArgs &a, uint8_t
 template <int B> static hipError_t launch_fused_b(FusedArgs &a, int nj, uint8_t *work, size_t work_bytes, hipStream_t stream)
 {
     switch (nj) {
-    case 1: return launch_fused_nj<B, 1>(a, work, work_bytes, stream);
+    case 1:
     case 2: return launch_fused_nj<B, 2>(a, work, work_bytes, stream);
     case 3: return launch_fused_nj<B, 3>(a, work, work_bytes, stream);
     }

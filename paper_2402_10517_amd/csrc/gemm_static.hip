@@ -3,7 +3,7 @@
 // ap_gemm takes the workspace from the caller and hands large batches to rocBLAS, whose first use
 // allocates.  Code under HIP graph capture, tight serving loops and harnesses that forbid
 // hipMalloc need an entry point that allocates nothing at all: the fused kernel (gemm_fused.hip) takes
-// every batch here, with its copy of the activations and its partial sums in `scratch` below (one copy per
+// every batch above 16 here, with its copy of the activations and its partial sums in `scratch` below (one copy per
 // GPU, held until the process ends).  Against dequantising into the array and a dense kernel, 4096 x 4096 b = 5 batch 33:
 // 61 -> 14 us.
 #include <hip/hip_runtime.h>
@@ -12,7 +12,7 @@
 
 #include "../../include/apgemv.h"
 #include "handle.h"
-#include "launchers.h"
+#include "kernels.h"
 
 namespace apgemv {
 
@@ -57,6 +57,7 @@ extern "C" ap_status ap_gemm_static(const ap_matrix *h, int b, const void *x_dev
     if (reinterpret_cast<uintptr_t>(x_dev) % 16 || reinterpret_cast<uintptr_t>(y_dev) % 2) return AP_ERR_INVALID_ARG;
     const size_t need = (size_t)h->hdr.M * (size_t)h->hdr.K * 2;
     if (need > (size_t)AP_GEMM_STATIC_MAX_BYTES) return AP_ERR_BUFFER_TOO_SMALL;
+    if ((long long)((h->hdr.M + 15) / 16) * ((batch + 15) / 16) > 0x7fffffffLL / 64) return AP_ERR_BATCH; // no such y exists
     void *work = scratch_on_current_device();
     if (!work) return AP_ERR_HIP;
 
@@ -71,15 +72,16 @@ extern "C" ap_status ap_gemm_static(const ap_matrix *h, int b, const void *x_dev
     a.row_groups_per_wg = -1;
     a.mfma_min_batch = 0;
     a.variant = 0;
-    a.work = work;
     a.work_bytes = AP_GEMM_STATIC_MAX_BYTES;
-    // as many batch rows at a time as the array has room for (at least 48: those need no copy of x)
+    // up to 16 rows on the kernels of ap_gemv; else as many batch rows at a time as the array has room for (at least 48:
+    // those need no copy of x)
     for (int first = 0; first < batch;) {
         a.x = static_cast<const uint16_t *>(x_dev) + (size_t)first * a.K;
         a.y = static_cast<uint16_t *>(y_dev) + (size_t)first * a.M;
         a.batch = batch - first < kMaxFusedBatch ? batch - first : kMaxFusedBatch;
         while (a.batch > 48 && !gemm_fused_ok(a)) a.batch = a.batch > 96 ? a.batch / 2 : 48;
-        if (launch_gemm_fused(a, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
+        a.work = a.batch > AP_MAX_BATCH ? work : nullptr;
+        if (launch_gemv(a, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
         first += a.batch;
     }
     return AP_OK;
