@@ -544,7 +544,7 @@ def main():
         del idx, luts
         copies = [pm, pm.clone(), pm.clone()]
         small = []
-        for batch in (2, 4, 8, 16):   # 16 = two passes of 8 rows
+        for batch in (2, 4, 8, 16):   # 16: one launch of the tile kernel
             xd = torch.from_numpy(np.concatenate([x, x])[:batch].copy()).to(dev)
             yd = torch.empty((batch, 28672), dtype=torch.float16, device=dev)
             for b in bits:
