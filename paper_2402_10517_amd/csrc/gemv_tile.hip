@@ -155,8 +155,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // evenly.  The loads of an octet are issued before the arithmetic of the octet before it (two
     // register sets).  Every pass of the loop issues the same loads and has no exit in the middle, so the
     // wait before the arithmetic leaves exactly the newer loads in flight: a row with an odd number of
-    // octets gets one more whose activations are read as zeros (offset out of range), and the loads
-    // issued in the last pass for the pass after it repeat a valid octet and are dropped.
+    // octets gets one more (the last one again, activations out of range), and the loads issued in the
+    // last pass for the pass after it repeat a valid octet and are dropped.  The products of that padding
+    // octet do not count (its centroids are real ones, and infinity x 0 is not 0): masked centroids in the
+    // RAG instances, the sums of before it in the others (0 to 1 % of the call; a branch around its
+    // arithmetic cost 7 % on rows without such an octet: b = 3, 4 then schedule with 78 registers
+    // instead of 107).
     auto issue = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B]) {
         const int span = o >> 3, oi = o & 7;
         const int rem = chunks - span * kSpanLanes;
@@ -414,6 +418,9 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     }
     __syncthreads();
 
+    float4_t before[R][2]; // the sums ahead of the wave's last octet
+#pragma unroll
+    for (int tile = 0; tile < R; ++tile) before[tile][0] = before[tile][1] = float4_t{0.f, 0.f, 0.f, 0.f};
     for (; p < p1; ++p) {
         const bool second = 2 * p + 1 < nocts;
         const int o1 = second ? 2 * p + 1 : 2 * p;
@@ -422,7 +429,17 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         compute(XA, QA, 2 * p);
         issue(p + 1 < p1 ? 2 * p + 2 : 2 * p, true, XA, QA);
         __builtin_amdgcn_sched_barrier(0);
-        compute(XB, QB, o1);
+        if constexpr (RAG) {
+            compute(XB, QB, 2 * p + 1); // the padding octet has no chunks: all centroids masked
+        } else {
+#pragma unroll
+            for (int tile = 0; tile < R; ++tile) { before[tile][0] = acc[tile][0]; before[tile][1] = acc[tile][1]; }
+            compute(XB, QB, o1);
+        }
+    }
+    if (!RAG && (nocts & 1) && p1 == npairs) { // the padding octet does not count
+#pragma unroll
+        for (int tile = 0; tile < R; ++tile) { acc[tile][0] = before[tile][0]; acc[tile][1] = before[tile][1]; }
     }
 
     // ---- acc[tile][h][r] of lane (i, kg): output row 4 kg + r of the tile over the wave's columns of quad

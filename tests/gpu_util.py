@@ -40,3 +40,30 @@ def check_against_oracle(y_gpu, idx, lut, b, x, n=8, rows=None):
     worst = float(np.max(err / tol))
     assert worst <= 1.0, "max err/tol = %.3f at %s" % (worst, np.unravel_index(np.argmax(err / tol), err.shape))
     return worst
+
+
+def plant_infinities(idx, lut, b, x, cells, n=8):
+    """Infinite weights that meet no other: makes the top entry of the table of each cell's row +inf (or the bottom
+    one -inf, for cells with sign -1) and the cell (row, column, sign) the only weight of the row that uses it; x is
+    moved away from zero in those columns.  In place.  One cell per row, so an output is infinite, never NaN."""
+    assert len({r for r, _, _ in cells}) == len(cells)
+    low = n - b
+    for r, c, sign in cells:
+        e = (1 << b) - 1 if sign > 0 else 0
+        near = e - 1 if sign > 0 else 1
+        uses = (idx[r] >> low) == e
+        idx[r, uses] = near << low
+        idx[r, c] = e << low
+        lut[r, e] = np.float16(sign * np.inf)
+        x[:, c] = np.where(x[:, c] < 0, np.float16(-1.5), np.float16(1.5))
+
+
+def check_planted(y_gpu, idx, lut, b, x, cells, rows, n=8):
+    """Rows with an infinite weight: exactly the infinity of its sign times the sign of its activation, in every batch
+    row; the other `rows`: against the oracle."""
+    got = y_gpu.astype(np.float64)
+    want = np.stack([np.sign(x[:, c].astype(np.float64)) * sign * np.inf for _, c, sign in cells], axis=1)
+    assert np.all(np.isinf(want))
+    planted = [r for r, _, _ in cells]
+    assert np.array_equal(got[:, planted], want), "rows %s: %s instead of %s" % (planted, got[:, planted], want)
+    check_against_oracle(y_gpu, idx, lut, b, x, n=n, rows=[r for r in rows if r not in planted])

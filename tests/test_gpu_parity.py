@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2402_10517_amd import inputs
-from gpu_util import check_against_oracle, run_gemv
+from gpu_util import check_against_oracle, check_planted, plant_infinities, run_gemv
 
 pytestmark = pytest.mark.gpu
 ALL_BITS = list(range(3, 9))
@@ -645,17 +645,68 @@ def test_tile_kernel_on_ragged_rows_and_at_batch_nine_to_sixteen(B, batch):
             assert np.all(out[:guard] == -7.0) and np.all(out[-guard:] == -7.0)
             check_against_oracle(out[guard:-guard].reshape(batch, M), idx, luts[b], b, x, rows=rows)
             pm.close()
+    # one infinite weight in the row's single ragged chunk, an infinity in the last column of x
     M, K, b = 3073, 8192 + 32, 5
     idx, luts, x = inputs.make_case(45, M, K, batch=batch, bit_widths=[b])
-    luts[b][7, :] = np.abs(luts[b][7, :])
-    luts[b][7, 31] = np.float16(np.inf)
-    x[1, K - 1] = np.float16(-np.inf)
+    cells = [(7, K - 5, 1)]
+    plant_infinities(idx, luts[b], b, x, cells)
     pm = B.ap_pack(idx, luts)
-    got = run_gemv(pm, b, x).astype(np.float64)
-    w = luts[b][np.arange(64)[:, None], idx[:64] >> (8 - b)].astype(np.float64)
+    check_planted(run_gemv(pm, b, x), idx, luts[b], b, x, cells, rows=range(64))
+    w = luts[b][np.arange(64), idx[:64, K - 1] >> (8 - b)].astype(np.float64)
+    assert np.all(w != 0)
+    x[1, K - 1] = np.float16(-np.inf)
+    got = run_gemv(pm, b, x)
+    keep = np.arange(batch) != 1
+    check_planted(got[keep], idx, luts[b], b, x[keep], cells, rows=range(64))
     with np.errstate(invalid="ignore"):
-        ref = (x.astype(np.float64)[:, None, :] * w[None]).sum(axis=2)
-    assert np.array_equal(np.isnan(got[:, :64]), np.isnan(ref))
-    assert np.array_equal(got[:, :64][np.isinf(ref)], ref[np.isinf(ref)])
-    assert np.all(np.isfinite(got[:, 64:]) | (np.arange(batch) == 1)[:, None])
+        expect = -np.inf * w
+        expect[7] += np.inf * x[1, K - 5].astype(np.float64)
+    assert np.array_equal(got[1, :64].astype(np.float64), expect, equal_nan=True)
     pm.close()
+
+
+def _octet_cells(M, K):
+    """One cell per row: columns of the last octet of 256 columns (its first and last chunk, the first and the last of
+    its four runs) and of the first one; rows of different tiles."""
+    span0 = (K - 1) // 2048 * 2048
+    nl = (K - span0) // 32                        # chunks of the last span; chunk c holds columns span0 + 8 nl t + 8 c .. + 7
+    first, last = 8 * ((nl - 1) // 8), nl - 1
+    cols = [span0 + 8 * nl * t + 8 * c + 3 * t % 8 for c in (first, last) for t in (0, 3)] + [0]
+    rows = [0, 5, 18, M // 2, M - 1, 40]
+    return [(r, c, sign) for r, c, sign in zip(rows, cols + [K - 1], (1, -1, 1, 1, -1, 1))]
+
+
+# Odd and even numbers of octets, whole and ragged, at sizes that the dispatcher gives to the tile kernel with one and with two
+# tiles per workgroup: an octet that only pads a row to a pair of them must not reach the result, and infinity x 0 would.
+@pytest.mark.parametrize("M,K,bits", [(8190, 32, [3, 4, 5, 8]), (8190, 256, [3, 4, 5, 8]), (8190, 544, [3, 4, 5, 8]),
+                                      (8190, 768, [3, 4, 5, 8]), (8190, 800, [3, 4, 5, 8]), (8190, 1024, [3, 4, 5, 8]),
+                                      (3073, 8192 + 32, [3, 6]), (3073, 8192 + 256, [4, 7]), (24577, 768, [3, 8])])
+@pytest.mark.parametrize("batch", [3, 8, 16])
+def test_infinite_centroid_in_the_last_octet(B, M, K, bits, batch):
+    import ctypes
+    import torch
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    cells = _octet_cells(M, K)
+    rows = np.unique(np.concatenate([np.arange(48), np.random.default_rng(M).integers(0, M, size=40), np.arange(M - 20, M)]))
+    idx0, luts, x = inputs.make_case(46, M, K, batch=batch, sigma=0.01, bit_widths=bits)
+    for b in bits:
+        idx = idx0.copy()
+        plant_infinities(idx, luts[b], b, x, cells)
+        pm = B.ap_pack(idx, luts)
+        pm2 = pm.clone()
+        xd = torch.from_numpy(x).cuda()
+        outs = [B.ap_gemv(pm, b, xd), B.ap_gemm(pm, b, xd)]
+        if M * K * 2 <= 32 << 20:
+            y = torch.empty((batch, M), dtype=torch.float16, device="cuda")
+            assert B.lib.ap_gemm_static(pm.handle, b, xd.data_ptr(), y.data_ptr(), batch, sp) == 0
+            outs.append(y)
+        if batch <= 8:
+            ys = [torch.empty((batch, M), dtype=torch.float16, device="cuda") for _ in range(4)]
+            B.ap_gemv_list_batch([(pm, b, xd, ys[0]), (pm2, b, xd, ys[1])], batch)
+            B.ap_gemv_multi([(pm, xd, ys[2]), (pm2, xd, ys[3])], b)
+            outs += ys
+        torch.cuda.synchronize()
+        for y in outs:
+            check_planted(y.cpu().numpy(), idx, luts[b], b, x, cells, rows)
+        pm.close()
+        pm2.close()
