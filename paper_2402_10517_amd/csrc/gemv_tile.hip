@@ -466,12 +466,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     }
 }
 
-// With one tile the tables limit a CU to 4 workgroups of 4 waves at b = 4 (33 KB each), so the compiler may use the registers of 4 waves per
-// SIMD: left alone it settles at 76 for b = 4 in list launches and spreads the loads less (decoder layer, batch 4 33.1 -> 32.7
-// us with 108 registers; 18662 x 2464 b = 4 batch 8 16.2 -> 15.7, other single calls level).
-#define AP_TILE_WAVES __attribute__((amdgpu_waves_per_eu(2, 4)))
+// No bound on the waves per SIMD: with at most 4 the b = 3, 4 instances of one tile take 107 registers instead of 74..80 and
+// workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
+// b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9, decoder layer b = 4 batch 4 33.0 / 32.6; 650 calls
+// on whole rows 1.000 to 1.010 by bit-width, 180 on ragged rows 1.000 to 1.036.
 template <int B, int R, int MAXT, bool RAG, bool WIDE>
-__global__ __launch_bounds__(MAXT) AP_TILE_WAVES void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
+__global__ __launch_bounds__(MAXT) void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
                                                          const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
                                                          uint16_t *__restrict__ y, int M, int K, int batch)
 {
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(MAXT) AP_TILE_WAVES void gemv_tile_kernel(const uin
 // decoder layer that share their input): workgroup -> (matrix, tile) through the prefix sums of the
 // tile counts, which the launcher puts into group_begin.
 template <int B, int MAXT>
-__global__ __launch_bounds__(MAXT) AP_TILE_WAVES void gemv_tile_multi_kernel(MultiArgs a)
+__global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a)
 {
     int m = 0;
 #pragma unroll
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(MAXT) AP_TILE_WAVES void gemv_tile_multi_kernel(Mul
 
 // A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.
 template <int B, int MAXT>
-__global__ __launch_bounds__(MAXT) AP_TILE_WAVES void gemv_tile_list_kernel(ListArgs a, int batch)
+__global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int batch)
 {
     int it = 0;
 #pragma unroll
