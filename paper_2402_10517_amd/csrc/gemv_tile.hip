@@ -504,19 +504,38 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int ba
     gemv_tile_body<B, 1, MAXT, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it]);
 }
 
+// Waves per workgroup of a single call that no option decides.  From 9270 calls (14 heights, 23 row lengths, every b, batch 3..8);
+// time with 4 waves over the time with the number chosen, or the other way round where the rule says 4:
+//   8 (a wave per pair of octets on shorter rows) on rows of 12288 columns or more, so that a wave still runs several passes, and where
+//   every tile has a CU of its own: 4096x11008 b = 4 batch 4 1.21, 4096x8192 b = 8 1.09, 4096x2208 b = 5 batch 8 1.14.  From the 257th
+//   tile on a CU gets two tiles while others idle, and 4 are ahead: 4112x5120 b = 8 batch 8 1.14, b = 3 1.10; except for rows of
+//   5 pairs, which 4 waves take in two rounds (4112x2208 b = 7 1.07), and b = 5 on long rows (5120x8192 1.04).
+//   With 5 to 7 waves the 4-bit pair tables are built by the general loop: 4096x3072 1.18 with 4.  10 to 12 pairs are two rounds of 8
+//   waves or three of 4: 4096x6144 b = 8 1.07 with 4, at b = 3, 4 0.97.  Nine batch rows and more: 4 (4096x4096 7.3 against 7.9 us).
+//   Rows of fewer than 4 pairs: waves without columns help to build the large tables (b = 3, 4, 8; 8192x512 b = 4 3.05, b = 3 1.42, b = 8
+//   1.08, 20480x512 b = 8 1.30, but 16384x512 b = 8, four tiles per CU, 0.92), the others lose by them (28672x512 b = 6 1.65, 4096x1024 b = 5 1.08 without).
+static int tile_waves(const GemvArgs &a, int tiles, int npairs, bool wide)
+{
+    const bool eight = a.K >= 12288 || (tiles <= 256 && !(a.b >= 5 && npairs >= 10 && npairs <= 12)) ||
+                       (tiles <= 320 && (npairs == 5 || (a.b == 5 && a.K >= 8192)));
+    int nw = !wide && eight ? 8 : 4;
+    if (nw > npairs) nw = npairs;
+    if (a.b == 4 && nw < 8) nw = 4;
+    const bool helpers = a.b <= 4 || (a.b == 8 && (tiles < 768 || tiles > 1024)) || (a.b == 7 && npairs == 1 && tiles <= 256);
+    return nw < 4 && helpers ? 4 : nw;
+}
+
 template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArgs &a, hipStream_t stream)
 {
     constexpr int kMaxWaves = 8;
     const int npairs = ((a.K + 255) / 256 + 1) / 2;
     const int tiles = (a.M + 15) / 16;
-    // 4 waves, so that a wave still runs several passes of its loop; 8 on long rows, and where a tile has a CU (nearly) to
-    // itself: 4096 x 11008 b = 4 batch 4 11.7 -> 9.3 us, 4096 x 4096 6.2 -> 5.4, 4099 x 2208 b = 7 batch 5 9.4 -> 8.8, but
-    // 8192 x 8192 b = 4 batch 8 11.9 -> 12.2.  At 9 to 16 batch rows 4 stay ahead (4096 x 4096 7.3 against 7.9).  A handle
-    // that asks for this kernel keeps the rule of the fused launches, with which it promises equal bits.
-    int nw = !WIDE && (a.K >= 12288 || (a.variant == 0 && tiles <= 320)) ? kMaxWaves : 4;
-    if (a.waves_per_group > 0) nw = a.waves_per_group;
-    if (nw > npairs) nw = npairs;
-    if (nw < 4 && a.waves_per_group == 0) nw = 4; // short rows: waves without columns help to build the tables (512 x 512 b = 4: 14.0 -> 4.3)
+    int nw;
+    if (a.waves_per_group > 0) nw = a.waves_per_group < npairs ? a.waves_per_group : npairs;
+    else if (a.variant == 0) nw = tile_waves(a, tiles, npairs, WIDE);
+    else { // a handle that asks for this kernel: the rule of the fused launches, with which it promises equal bits
+        nw = a.K >= 12288 ? kMaxWaves : 4; // (waves beyond the row's pairs add nothing to the sums)
+    }
     const dim3 grid((tiles + R - 1) / R), block(64 * nw);
     if (a.K % 256)
         hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, true, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
