@@ -551,9 +551,14 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
     // two tiles per workgroup re-read and re-arrange the activations half as often, at more registers:
     // measured faster on rows of 16384 columns or more, and at 3 bits (where the loads outweigh the
     // arithmetic) on matrices tall enough to fill the device with half as many workgroups (28672 x 8192 at
-    // batch 4 and 8: 29-34 -> 28 us; 8192 x 8192: 11.8 -> 12.5, so not there)
+    // batch 4 and 8: 29-34 -> 28 us; 8192 x 8192: 11.8 -> 12.5, so not there).  On long rows, one tile over two tiles: from
+    // 512 tiles on 8192x20480 b = 3 batch 8 1.24, b = 5 1.05; with 257 to 511, where half as many workgroups leave CUs idle, 6144x20480
+    // b = 3 1.14 to 1.23, b = 4 1.05 to 1.16, b = 5 to 8 0.94 at batch 3 and 1.01 to 1.04 at 8; up to 256 4096x28672 0.6.  Rows that are not
+    // whole octets mask their centroids: 8192x16512 b = 5 0.82 to 0.90, b = 8 0.80 (ALU kernel over two tiles 0.90), 13824x16512
+    // b = 5 0.94 to 1.02, b = 3 1.26.
     const int tiles = (a.M + 15) / 16;
-    const bool two = a.variant == 10 || (a.variant != 9 && ((a.K >= 16384 && tiles >= 512) || (B == 3 && tiles >= 1536)));
+    const bool long_rows = a.K >= 16384 && (a.K % 256 == 0 ? tiles >= 512 || (tiles > 256 && (B <= 4 || a.batch >= 7)) : tiles >= 512 && B <= 4);
+    const bool two = a.variant == 10 || (a.variant != 9 && (long_rows || (B == 3 && tiles >= 1536)));
     if (a.batch <= 8) return two ? launch_tile_r<B, 2, false>(a, stream) : launch_tile_r<B, 1, false>(a, stream);
     // with twice the activations two tiles take about 0.8 of the time per tile, unless that leaves the CUs more unevenly
     // loaded: 28672 x 8192 b = 4 batch 16 57.1 -> 43.2 us, 8192 x 8192 18.0 -> 15.2, 11008 x 4096 b = 8 22.2 -> 24.0
