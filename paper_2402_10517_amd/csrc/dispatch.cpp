@@ -6,26 +6,42 @@
 namespace apgemv {
 
 // Whether the matrix-core kernel on tiles of 16 rows is the fastest for a call without tuning overrides.  Time of the kernels below
-// (batch 9 and more: in two passes) over its time, at M x K and b = 3 / 5 / 8:
-//   batch 9       1024x4096 1.30/1.23/1.09  1024x20480 0.97/0.91/0.85  512x1024 1.80/1.26/1.47  2048x20480 1.32/1.23/1.15
+// (batch 9 and more: in two passes) over its time, at M x K and b = 3 / 5 / 8, from 9270 calls at batch 3..8 (14 heights, 23 row
+// lengths) and 5500 at 9..16:
+//   batch 9       1024x4096 1.30/1.23/1.09  1024x8192 1.04/0.95/-  1024x20480 0.97/0.91/0.85  512x1024 1.80/1.26/1.47  2048x20480 1.32/1.23/1.15
 //   batch 16      1024x11008 1.37/1.25/1.08  1024x4192 1.27/1.02/0.93  4096x4096 1.58/1.62/1.68  28000x4192 3.59/3.16/2.36
 //   batch 5       1024x4096 1.08/0.92/0.77  2048x1024 1.25/0.92/0.94  2048x4192 1.13/0.95/0.78  2048x8224 1.16/0.95/0.79
-//                 3072x1024 1.32/0.96/1.01  3072x4096 1.60/1.38/1.18  4099x2208 1.42/1.13/0.99  28000x2208 2.52/2.02/1.50
-//   batch 3, 4    2048x11008 1.00/1.01/0.78  3072x4096 1.15/1.03/0.96  3072x11008 1.33/1.38/1.03  3072x20480 1.22/1.34/0.97
-//                 4096x4096 1.25/1.10/1.02  4096x11008 1.91/1.72/1.51  4099x4192 0.92/0.74/0.70  4099x8224 1.30/1.17/1.03
-//                 8192x2208 1.15/1.03/0.85  8192x4192 1.19/1.01/0.82  13824x8224 1.79/1.68/1.18  28000x4192 1.31/1.14/0.81
+//                 3072x1024 1.32/0.96/1.01  3072x4096 1.60/1.38/1.18  5120x2208 1.38/1.22/0.95  28000x2208 2.52/2.02/1.50
+//   batch 3, 4    3072x4096 1.14/1.01/0.95  3072x8192 1.06/0.92/0.88  3072x11008 1.31/1.36/1.04  3072x16384 1.15/1.27/0.95
+//                 4096x4096 1.24/1.08/1.04  4096x8192 1.19/1.06/1.02  4096x11008 1.88/1.69/1.47  4096x12416 1.32/1.48/0.98
+//                 5120x4096 0.96/0.86/0.83  5120x8192 0.94/0.80/0.78  5120x11008 1.33/1.32/1.05  5120x13824 1.10/1.30/0.86
+//                 6144x4096 1.07/0.94/0.94  6144x8192 1.02/0.89/0.88  6144x11008 1.50/1.52/1.16  6144x13824 1.45/1.52/1.12
+//                 8192x4096 1.18/1.16/1.28  8192x4224 1.21/1.06/1.06  8192x8192 1.21/1.09/1.20  8192x16384 1.63/1.76/1.25
 //   batch 2       4096x4096 1.01/0.95/0.92  6144x11008 0.77/0.77/0.77
-// At batch 3 and 4, rows below 8192 columns and a multiple of 256: from 2048 row groups on it wins by 5 to 40 % over the
-// matrix-core kernels below at every b.
+// At batch 3 and 4 below 2048 row groups the ALU kernel is close, and two things decide: the CUs that the last round of tiles leaves
+// idle (5120 rows are 320 tiles, 1.25 rounds), and the last span of the ALU kernel's rows (whole at 8192 and 16384 columns; at
+// b >= 7 rows of more than 6 spans).  b = 4 always wins there (1.0 to 2.4).
 static bool tile_pays(const GemvArgs &a)
 {
     const int groups = padded_rows(a.M) / kRowsPerGroup;
-    if (a.batch >= 9) return groups >= 512 || (groups >= 256 && a.b <= 5 && a.K <= 12288) || (groups >= 128 && a.K <= 1024);
-    if (a.batch >= 5) return groups >= 768 || (groups >= 512 && a.b == 3);
+    if (a.batch >= 9)
+        return groups >= 512 || (groups >= 256 && a.b <= 5 && a.K <= 12288 && (a.b <= 4 || a.K <= 4096 || a.batch >= 13)) ||
+               (groups >= 128 && a.K <= 1024);
+    // tiles of the last round: at least 3/4, 4/5 of the CUs busy on average over the rounds
+    const int tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
+    const bool most = tiles >= 192 * rounds, full = tiles >= 205 * rounds;
+    if (a.batch >= 5) {
+        if (a.b == 8 && a.K % 256 && a.K > 2048 && a.K < 3072 && groups < 2048 && !most) return false;
+        return groups >= 768 || (groups >= 512 && a.b == 3);
+    }
     if (a.batch < 3) return false;
-    if (a.K >= 8192) return groups >= 768;
-    if (a.K % 256 == 0) return groups >= 2048 || (groups >= 768 && a.b <= 4 && a.K >= 4096);
-    return groups >= 2048 && a.b == 3;
+    if (groups >= 2048) return a.K >= 8192 || a.K % 256 == 0 || a.b == 3;
+    if (groups < 768 || a.K < 4096 || (a.K < 8192 && (a.K % 256 || a.b > 4))) return false;
+    if (a.b == 4) return true;
+    if (a.b == 3) return a.K > 8192 || most;
+    if (a.b <= 6) return a.K > 8192 || full;
+    if (a.K <= 8192) return full;
+    return a.K <= 12288 || (rounds > 1 ? most : full);
 }
 
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
