@@ -399,13 +399,34 @@ extern "C" ap_status ap_gemm_workspace_size(const ap_matrix *h, size_t *bytes)
     return AP_OK;
 }
 
-// Largest batch of ap_gemm that runs on the fused kernel; above it the weights are dequantised once into the workspace and
-// rocBLAS computes the product.  The fused kernel dequantises once per 64 batch rows, at b = 3 for half the cost.  Measured,
-// us, dequantise + rocBLAS / fused, batch 256 / 384 / 512: 8192x8192 b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111,
-// b = 8 115/68 108/97 118/126; 11008x4096 b = 3 69/38 69/54 75/66, b = 5 72/48 72/70 77/85, b = 8 74/57 76/84 81/101;
-// 4096x11008 b = 8 81/52 89/82 101/87.  Up to 16 batch rows the kernels of ap_gemv are ahead of it too: batch 16, fused / ap_gemv,
-// 11008x4096 b = 4 15.8/15.4, 28672x8192 46/43, 4096x4096 b = 5 batch 12 11.3/7.5.
-static int fused_max_batch(int b) { return b == 3 ? kMaxFusedBatch : b <= 5 ? 384 : 256; }
+// Whether a product of ap_gemm runs on the fused kernel rather than as ap_dequantize and one rocBLAS product.  The fused kernel
+// dequantises once per 64 batch rows, at b = 3 for half the cost.  The lines come from 14 000 calls (18 heights 64..28672, 12 row
+// lengths 256..28672, 15 batches 17..512, every b); on the calls given to it it is 1.0 to 4.6 times as fast, on 0.7 % of them 3 to 17 %
+// slower (worst 300 x 8192 at batch 160..192).  Dequantise + rocBLAS / fused, us:
+//   batch, by b   8192x8192 batch 256 / 384 / 512  b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111, b = 8 115/68 108/97 118/126
+//   tall, short   the dense weights stay in the last-level cache: 28672x1024 b = 8 batch 128 / 256 38/37 43/58, b = 5 batch 320 41/49,
+//                 b = 3 batch 512 47/61; 28672x8192 b = 8 batch 256 255/215
+//   column parts  a workspace without room for the partial sums leaves few workgroups with all columns: 64x8192 b = 8 batch 64 (no part
+//                 of 8) 16/32, batch 65 16/14 (no copy of x); 512x4096 b = 5 batch 384 (1 of 4) 18/23, batch 320 (2 of 4) 18/19
+//   small         the tables of 64 rows weigh as much as their columns: 512x256 b = 8 batch 256 9.4/11.7, 512x1056 b = 8 batch 128 13/15
+static bool gemm_fused_pays(const GemvArgs &a)
+{
+    const FusedPlan p = fused_plan(a);
+    const int M = a.M, K = a.K;
+    int most = a.b == 3 ? kMaxFusedBatch : a.b <= 5 ? 384 : 256;
+    if (a.b == 3 && M >= 24576 && K <= 2048) most = 384;
+    if ((a.b == 4 || a.b == 5) && M >= 12288 && K < 8192) most = M >= 24576 && K <= 2048 ? 256 : 320;
+    if (a.b == 7 && M >= 24576 && K <= 1024) most = 128;
+    if (a.b == 8 && M >= 12288 && K <= 1024) most = M >= 20480 ? 128 : 192;
+    if (a.b == 8 && M >= 24576 && K > 1024 && K <= 2048) most = 192;
+    if (a.batch > most) return false;
+    const int wanted = fused_parts_wanted(p), parts = fused_parts(p, a);
+    if (parts < wanted && ((4 * parts <= wanted && K <= 16384) || (a.b > 3 && parts == 1))) return false;
+    if (p.nj == 4 && a.b >= 7 && M <= 768 && K > 1024 && K <= (a.b == 8 ? 4096 : 1536)) return false;
+    if (p.nj == 4 && K < 512 && M <= (a.b == 8 ? 2048 : 1024) && (a.b >= 7 || (a.b >= 4 && a.batch > 128)))
+        return M > 128 && M < 256; // rocBLAS is slow between its tiles: 200 x 256 b = 8 batch 192 25/12
+    return true;
+}
 
 extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,
                              void *work_dev, size_t work_bytes, void *stream)
@@ -432,7 +453,7 @@ extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void 
     }
     a.work = work_dev;
     a.work_bytes = work_bytes;
-    if (batch <= fused_max_batch(b) && gemm_fused_ok(a)) return launch_gemv(a, st) == hipSuccess ? AP_OK : AP_ERR_HIP;
+    if (gemm_fused_ok(a) && gemm_fused_pays(a)) return launch_gemv(a, st) == hipSuccess ? AP_OK : AP_ERR_HIP;
     a.y = static_cast<uint16_t *>(work_dev);
     if (launch_dequantize(a, st) != hipSuccess) return AP_ERR_HIP;
     return dense_gemm_f16(work_dev, x_dev, y_dev, a.M, a.K, batch, st) ? AP_OK : AP_ERR_HIP;

@@ -400,29 +400,18 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restri
     }
 }
 
-template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, int blocks, uint8_t *work, size_t work_bytes, hipStream_t stream)
+template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
 {
     constexpr bool kXF = NJ >= 4;
-    const int steps = (a.K / kChunkSlots + 3) / 4;
     if (kXF) {
-        const int tiles = a.ntiles * NJ;
-        const size_t bytes = (size_t)steps * 4 * tiles * 1024;
-        hipLaunchKernelGGL(fragment_x_kernel, dim3((steps + 3) / 4, tiles), dim3(256), 0, stream, a.x, reinterpret_cast<u32x4 *>(work), a.K,
+        const int tiles = p.ntiles * NJ;
+        hipLaunchKernelGGL(fragment_x_kernel, dim3((p.steps + 3) / 4, tiles), dim3(256), 0, stream, a.x, reinterpret_cast<u32x4 *>(work), a.K,
                            a.batch, tiles);
         a.x = reinterpret_cast<const uint16_t *>(work);
-        work += bytes;
-        work_bytes -= bytes;
+        work += p.copy_bytes;
     }
-    // Parts: as many as give every CU one workgroup, a step or more per wave.  Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5
-    // batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3 batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096
-    // batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups costs more than idle CUs.
-    int parts = 256 / (blocks * a.ntiles);
-    if (parts > steps / W) parts = steps / W;
-    const size_t part_bytes = (size_t)a.batch * a.M * 4;
-    if (parts > 1 && (size_t)parts * part_bytes > work_bytes) parts = (int)(work_bytes / part_bytes);
-    a.parts = parts > 1 ? parts : 1;
     a.partial = reinterpret_cast<float *>(work);
-    hipLaunchKernelGGL((gemm_fused_kernel<B, NJ, W, kXF>), dim3(blocks * a.ntiles, a.parts), dim3(64 * W), 0, stream, a);
+    hipLaunchKernelGGL((gemm_fused_kernel<B, NJ, W, kXF>), dim3(p.blocks * p.ntiles, a.parts), dim3(64 * W), 0, stream, a);
     if (a.parts > 1) {
         const size_t n = (size_t)a.M * a.batch;
         hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, a.partial, a.y, n, a.parts);
@@ -430,40 +419,34 @@ template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, i
     return hipGetLastError();
 }
 
-// 8 waves per workgroup when every workgroup has a CU of its own, else 4 (two workgroups per CU): 28672 x 8192 b = 4 batch 64
-// 65 -> 59 us with 4, 11008 x 4096 b = 4 batch 32 17.3 -> 20.3.
-template <int B, int NJ> static hipError_t launch_fused_nj(FusedArgs &a, uint8_t *work, size_t work_bytes, hipStream_t stream)
+template <int B, int NJ> static hipError_t launch_fused_nj(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
 {
-    const int blocks = (a.M + 63) / 64;
-    if ((long long)blocks * a.ntiles <= 256) return launch_fused_w<B, NJ, 8>(a, blocks, work, work_bytes, stream);
-    return launch_fused_w<B, NJ, 4>(a, blocks, work, work_bytes, stream);
+    return p.waves == 8 ? launch_fused_w<B, NJ, 8>(a, p, work, stream) : launch_fused_w<B, NJ, 4>(a, p, work, stream);
 }
 
-template <int B> static hipError_t launch_fused_b(FusedArgs &a, int nj, uint8_t *work, size_t work_bytes, hipStream_t stream)
+template <int B> static hipError_t launch_fused_b(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
 {
-    switch (nj) {
+    switch (p.nj) {
     case 1:
-    case 2: return launch_fused_nj<B, 2>(a, work, work_bytes, stream);
-    case 3: return launch_fused_nj<B, 3>(a, work, work_bytes, stream);
+    case 2: return launch_fused_nj<B, 2>(a, p, work, stream);
+    case 3: return launch_fused_nj<B, 3>(a, p, work, stream);
     }
-    return launch_fused_nj<B, 4>(a, work, work_bytes, stream);
+    return launch_fused_nj<B, 4>(a, p, work, stream);
 }
 
 hipError_t launch_gemm_fused(const GemvArgs &g, hipStream_t stream)
 {
     if (!gemm_fused_ok(g)) return hipErrorInvalidValue;
-    int ntiles, nj;
-    fused_tiles(g.batch, &ntiles, &nj);
-    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, ntiles, 1};
+    const FusedPlan p = fused_plan(g);
+    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, p.ntiles, fused_parts(p, g)};
     uint8_t *w = static_cast<uint8_t *>(g.work);
-    const size_t work_bytes = g.work_bytes;
     switch (g.b) {
-    case 3: return launch_fused_b<3>(a, nj, w, work_bytes, stream);
-    case 4: return launch_fused_b<4>(a, nj, w, work_bytes, stream);
-    case 5: return launch_fused_b<5>(a, nj, w, work_bytes, stream);
-    case 6: return launch_fused_b<6>(a, nj, w, work_bytes, stream);
-    case 7: return launch_fused_b<7>(a, nj, w, work_bytes, stream);
-    case 8: return launch_fused_b<8>(a, nj, w, work_bytes, stream);
+    case 3: return launch_fused_b<3>(a, p, w, stream);
+    case 4: return launch_fused_b<4>(a, p, w, stream);
+    case 5: return launch_fused_b<5>(a, p, w, stream);
+    case 6: return launch_fused_b<6>(a, p, w, stream);
+    case 7: return launch_fused_b<7>(a, p, w, stream);
+    case 8: return launch_fused_b<8>(a, p, w, stream);
     }
     return hipErrorInvalidValue;
 }

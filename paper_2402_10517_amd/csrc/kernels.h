@@ -30,21 +30,48 @@ struct GemvArgs {
 
 // The fused large-batch kernel (gemm_fused.hip) takes a product of up to kMaxFusedBatch batch rows straight from the packed form.
 constexpr int kMaxFusedBatch = 512;
-// Its tiling of the batch: `ntiles` tiles of up to 64 rows, evenly filled with `nj` times 16 rows.
-inline void fused_tiles(int batch, int *ntiles, int *nj)
+// How it divides a product: `ntiles` tiles of up to 64 batch rows, evenly filled with `nj` times 16 rows; blocks of 64 rows;
+// `waves` per workgroup; with nj = 4 a copy of x in the scratch.
+struct FusedPlan {
+    int ntiles, nj, blocks, waves, steps;
+    size_t copy_bytes;
+};
+inline FusedPlan fused_plan(const GemvArgs &a)
 {
-    *ntiles = (batch + 63) / 64;
-    *nj = ((batch + 15) / 16 + *ntiles - 1) / *ntiles;
+    FusedPlan p;
+    p.ntiles = (a.batch + 63) / 64;
+    p.nj = ((a.batch + 15) / 16 + p.ntiles - 1) / p.ntiles;
+    p.blocks = (a.M + 63) / 64;
+    // 8 waves per workgroup when every workgroup has a CU of its own, else 4 (two workgroups per CU): 28672 x 8192 b = 4 batch 64
+    // 65 -> 59 us with 4, 11008 x 4096 b = 4 batch 32 17.3 -> 20.3.
+    p.waves = (long long)p.blocks * p.ntiles <= 256 ? 8 : 4;
+    p.steps = (a.K / 32 + 3) / 4;
+    p.copy_bytes = p.nj < 4 ? 0 : (size_t)p.steps * 4 * p.ntiles * p.nj * 1024;
+    return p;
+}
+// Column parts (workgroups that share a row block's columns): as many as give every CU one workgroup, a step or more per wave.
+// Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5 batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3
+// batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096 b = 4 batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups
+// costs more than idle CUs.
+inline int fused_parts_wanted(const FusedPlan &p)
+{
+    const int fill = (int)(256 / ((long long)p.blocks * p.ntiles));
+    const int parts = fill < p.steps / p.waves ? fill : p.steps / p.waves;
+    return parts > 1 ? parts : 1;
+}
+// As many of them as the scratch has room for partial sums of (besides the copy of x).
+inline int fused_parts(const FusedPlan &p, const GemvArgs &a)
+{
+    const int wanted = fused_parts_wanted(p);
+    const size_t room = (a.work_bytes - p.copy_bytes) / ((size_t)a.batch * a.M * 4);
+    return room >= (size_t)wanted ? wanted : room > 1 ? (int)room : 1;
 }
 // Whether it takes the call with a.work_bytes of scratch (always for 48 rows of an aligned x): 16-byte loads of x, whose rows are
-// multiples of 64 bytes; from 49 rows on a copy of x in the scratch.
+// multiples of 64 bytes; room for the copy of x.
 inline bool gemm_fused_ok(const GemvArgs &a)
 {
     if (reinterpret_cast<uintptr_t>(a.x) % 16 || a.batch < 1 || a.batch > kMaxFusedBatch) return false;
-    int ntiles, nj;
-    fused_tiles(a.batch, &ntiles, &nj);
-    if (nj < 4) return true;
-    const size_t copy = (size_t)((a.K / 32 + 3) / 4) * 4 * ntiles * nj * 1024;
+    const size_t copy = fused_plan(a).copy_bytes;
     return copy <= a.work_bytes && copy < 0xffffffffu;
 }
 
