@@ -513,7 +513,8 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int ba
 //   With 5 to 7 waves the 4-bit pair tables are built by the general loop: 4096x3072 1.18 with 4.  10 to 12 pairs are two rounds of 8
 //   waves or three of 4: 4096x6144 b = 8 1.07 with 4, at b = 3, 4 0.97.  Nine batch rows and more: 4 (4096x4096 7.3 against 7.9 us).
 //   Rows of fewer than 4 pairs: waves without columns help to build the large tables (b = 3, 4, 8; 8192x512 b = 4 3.05, b = 3 1.42, b = 8
-//   1.08, 20480x512 b = 8 1.30, but 16384x512 b = 8, four tiles per CU, 0.92), the others lose by them (28672x512 b = 6 1.65, 4096x1024 b = 5 1.08 without).
+//   1.08, 20480x512 b = 8 1.30, but 16384x512 b = 8, four tiles per CU, 0.92; at batch 9 to 16
+//   1.10 there), the others lose by them (28672x512 b = 6 1.65, 4096x1024 b = 5 1.08 without).
 static int tile_waves(const GemvArgs &a, int tiles, int npairs, bool wide)
 {
     const bool eight = a.K >= 12288 || (tiles <= 256 && !(a.b >= 5 && npairs >= 10 && npairs <= 12)) ||
@@ -521,7 +522,7 @@ static int tile_waves(const GemvArgs &a, int tiles, int npairs, bool wide)
     int nw = !wide && eight ? 8 : 4;
     if (nw > npairs) nw = npairs;
     if (a.b == 4 && nw < 8) nw = 4;
-    const bool helpers = a.b <= 4 || (a.b == 8 && (tiles < 768 || tiles > 1024)) || (a.b == 7 && npairs == 1 && tiles <= 256);
+    const bool helpers = a.b <= 4 || (a.b == 8 && (wide || tiles < 768 || tiles > 1024)) || (a.b == 7 && npairs == 1 && tiles <= 256);
     return nw < 4 && helpers ? 4 : nw;
 }
 
