@@ -413,7 +413,7 @@ static bool gemm_fused_pays(const GemvArgs &a)
 {
     const FusedPlan p = fused_plan(a);
     const int M = a.M, K = a.K;
-    int most = a.b == 3 ? kMaxFusedBatch : a.b <= 5 ? 384 : 256;
+    int most = a.b == 3 ? 512 : a.b <= 5 ? 384 : 256;
     if (a.b == 3 && M >= 24576 && K <= 2048) most = 384;
     if ((a.b == 4 || a.b == 5) && M >= 12288 && K < 8192) most = M >= 24576 && K <= 2048 ? 256 : 320;
     if (a.b == 7 && M >= 24576 && K <= 1024) most = 128;

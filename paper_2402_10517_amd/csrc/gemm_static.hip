@@ -2,10 +2,10 @@
 //
 // ap_gemm takes the workspace from the caller and hands large batches to rocBLAS, whose first use
 // allocates.  Code under HIP graph capture, tight serving loops and harnesses that forbid
-// hipMalloc need an entry point that allocates nothing at all: the fused kernel (gemm_fused.hip) takes
-// every batch above 16 here, with its copy of the activations and its partial sums in `scratch` below (one copy per
-// GPU, held until the process ends).  Against dequantising into the array and a dense kernel, 4096 x 4096 b = 5 batch 33:
-// 61 -> 14 us.
+// hipMalloc need an entry point that allocates nothing at all: the fused kernel (gemm_fused.hip) takes batches above 16
+// here, with its copy of the activations and its partial sums in `scratch` below (one copy per GPU, held until the process
+// ends).  Against dequantising into the array and the dense kernel below, 4096 x 4096 b = 5 batch 33: 61 -> 13 us.  The
+// dense kernel keeps products of few columns.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -40,6 +40,59 @@ void *scratch_on_current_device()
     return g_scratch_ptr[dev];
 }
 
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// The product over dequantised weights, where the tables of 64 rows that every workgroup of the fused kernel builds outweigh the
+// columns they serve.  y[t][i] = sum_k w[i][k] * x[t][k]: one wave per tile of 16 output rows x 16 batch rows.  In
+// v_mfma_f32_16x16x16_f16 lane l supplies A[l % 16][4 (l / 16) .. + 3] and B[4 (l / 16) .. + 3][l % 16]
+// and receives D[4 (l / 16) .. + 3][l % 16].  Which four k a lane group contributes is free as long
+// as A and B agree, so group g takes the 8 consecutive k of a 16-byte load in two instructions.
+// K % 32 == 0 (guaranteed by the packed format).
+__global__ __launch_bounds__(256) void dense_gemm_kernel(const uint16_t *__restrict__ w, const uint16_t *__restrict__ x,
+                                                         uint16_t *__restrict__ y, int M, int K, int batch, int row_tiles,
+                                                         int tiles)
+{
+    const int tile = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    if (tile >= tiles) return; // whole waves
+    const int rt = tile % row_tiles, bt = tile / row_tiles;
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int row = rt * 16 + r, t = bt * 16 + r;
+    const u32x4 *wp = reinterpret_cast<const u32x4 *>(w + (size_t)(row < M ? row : M - 1) * K) + g;
+    const u32x4 *xp = reinterpret_cast<const u32x4 *>(x + (size_t)(t < batch ? t : batch - 1) * K) + g;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < K / 8; k += 4) {
+        const u32x4 a = wp[k], b = xp[k];
+        const u32x2 a0 = {a[0], a[1]}, a1 = {a[2], a[3]}, b0 = {b[0], b[1]}, b1 = {b[2], b[3]};
+        acc = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a0), __builtin_bit_cast(f16x4, b0), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a1), __builtin_bit_cast(f16x4, b1), acc, 0, 0, 0);
+    }
+    if (t < batch) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int orow = rt * 16 + 4 * g + j;
+            if (orow < M) {
+                const _Float16 h = (_Float16)acc[j];
+                y[(size_t)t * M + orow] = __builtin_bit_cast(uint16_t, h);
+            }
+        }
+    }
+}
+
+// Dequantise + this kernel over the fused kernel, us, b = 3 / 5 / 8: 64x32 batch 256 5.5/8.2 5.9/8.1 6.1/9.7, 300x256 batch 128
+// 7.4/8.7 8.1/10.0 8.2/11.8, batch 1024 9.1/9.0 9.8/10.3 9.9/12.1, 1024x256 batch 512 10.1/8.9 10.5/10.2 10.9/11.9, 300x512 batch 512
+// 10.1/9.5 10.5/10.8 10.8/13.6; up to 48 batch rows, which need no copy of x, the fused kernel is level or ahead (64x256 batch 33 1.30
+// to 0.95).  Every wave of this one reads its 16 rows and 16 batch rows for itself, so its time grows with their product (28672x32
+// b = 5 batch 64 20/9).
+bool dense_pays(const GemvArgs &a)
+{
+    const long long waves = (long long)((a.M + 15) / 16) * ((a.batch + 15) / 16);
+    if (a.b >= 7) return a.batch > 48 && a.K <= 512 && a.M <= 4096 && waves * a.K <= 1 << 19;
+    return a.batch > 48 && a.K <= 256 && a.M <= 2048 && waves * a.K <= 1 << 18;
+}
+
 } // namespace
 
 bool static_scratch_setup() { return scratch_on_current_device() != nullptr; }
@@ -72,16 +125,35 @@ extern "C" ap_status ap_gemm_static(const ap_matrix *h, int b, const void *x_dev
     a.row_groups_per_wg = -1;
     a.mfma_min_batch = 0;
     a.variant = 0;
+    a.x = static_cast<const uint16_t *>(x_dev);
+    a.y = static_cast<uint16_t *>(y_dev);
+    a.batch = batch;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (dense_pays(a)) { // M * K fits the array (above)
+        a.y = static_cast<uint16_t *>(work);
+        if (launch_dequantize(a, st) != hipSuccess) return AP_ERR_HIP;
+        const int row_tiles = (a.M + 15) / 16, tiles = row_tiles * ((batch + 15) / 16);
+        hipLaunchKernelGGL(dense_gemm_kernel, dim3((tiles + 3) / 4), dim3(256), 0, st, static_cast<const uint16_t *>(work), a.x,
+                           static_cast<uint16_t *>(y_dev), a.M, a.K, batch, row_tiles, tiles);
+        return hipGetLastError() == hipSuccess ? AP_OK : AP_ERR_HIP;
+    }
     a.work_bytes = AP_GEMM_STATIC_MAX_BYTES;
-    // up to 16 rows on the kernels of ap_gemv; else as many batch rows at a time as the array has room for (at least 48:
-    // those need no copy of x)
+    // up to 16 rows on the kernels of ap_gemv, unless that means two passes over a tiny matrix (64x256 b = 3 batch 16 8.9 us, fused 5.0)
+    const int gemv_rows = a.K <= 256 && a.M < 512 ? AP_MAX_BATCH / 2 : AP_MAX_BATCH;
+    // the others in as few passes as keep the copy of x within 16 MB, 8 MB with more than 32 row blocks, which all read it: passes
+    // of 512 rows / as many as that, us: 16x256 b = 3 batch 4096 62/9, 512x4096 b = 5 batch 1024 40/27, 4096x512 batch 4096 98/70; but
+    // all rows in one pass at 33 and 17 MB: 2048x8192 b = 3 batch 2048 125/165, 4096x4096 119/161
+    const int steps = (a.K / 32 + 3) / 4;
+    const int most = (int)((size_t)(a.M <= 32 * 64 ? 1 << 24 : 1 << 23) / ((size_t)steps * 256));
+    const int passes = (batch + (most > 512 ? most : 512) - 1) / (most > 512 ? most : 512);
+    const int rows = ((batch + passes - 1) / passes + 63) / 64 * 64;
     for (int first = 0; first < batch;) {
         a.x = static_cast<const uint16_t *>(x_dev) + (size_t)first * a.K;
         a.y = static_cast<uint16_t *>(y_dev) + (size_t)first * a.M;
-        a.batch = batch - first < kMaxFusedBatch ? batch - first : kMaxFusedBatch;
-        while (a.batch > 48 && !gemm_fused_ok(a)) a.batch = a.batch > 96 ? a.batch / 2 : 48;
-        a.work = a.batch > AP_MAX_BATCH ? work : nullptr;
-        if (launch_gemv(a, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
+        a.batch = batch - first < rows ? batch - first : rows;
+        while (a.batch > 48 && !gemm_fused_ok(a)) a.batch = a.batch > 96 ? a.batch / 2 : 48; // (at 48 rows no copy of x)
+        a.work = a.batch > gemv_rows ? work : nullptr;
+        if (launch_gemv(a, st) != hipSuccess) return AP_ERR_HIP;
         first += a.batch;
     }
     return AP_OK;

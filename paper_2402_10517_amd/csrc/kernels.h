@@ -28,8 +28,7 @@ struct GemvArgs {
     size_t work_bytes = 0;
 };
 
-// The fused large-batch kernel (gemm_fused.hip) takes a product of up to kMaxFusedBatch batch rows straight from the packed form.
-constexpr int kMaxFusedBatch = 512;
+// The fused large-batch kernel (gemm_fused.hip) takes a product straight from the packed form.
 // How it divides a product: `ntiles` tiles of up to 64 batch rows, evenly filled with `nj` times 16 rows; blocks of 64 rows;
 // `waves` per workgroup; with nj = 4 a copy of x in the scratch.
 struct FusedPlan {
@@ -67,12 +66,12 @@ inline int fused_parts(const FusedPlan &p, const GemvArgs &a)
     return room >= (size_t)wanted ? wanted : room > 1 ? (int)room : 1;
 }
 // Whether it takes the call with a.work_bytes of scratch (always for 48 rows of an aligned x): 16-byte loads of x, whose rows are
-// multiples of 64 bytes; room for the copy of x.
+// multiples of 64 bytes; room for the copy of x; grids within 2^32 threads and 65535 tiles of 16 batch rows.
 inline bool gemm_fused_ok(const GemvArgs &a)
 {
-    if (reinterpret_cast<uintptr_t>(a.x) % 16 || a.batch < 1 || a.batch > kMaxFusedBatch) return false;
-    const size_t copy = fused_plan(a).copy_bytes;
-    return copy <= a.work_bytes && copy < 0xffffffffu;
+    if (reinterpret_cast<uintptr_t>(a.x) % 16 || a.batch < 1 || a.batch > 1 << 19) return false;
+    const FusedPlan p = fused_plan(a);
+    return p.copy_bytes <= a.work_bytes && p.copy_bytes < 0xffffffffu && (long long)p.blocks * p.ntiles <= 1 << 22;
 }
 
 constexpr int kMaxMulti = 8;

@@ -106,6 +106,28 @@ def test_fused_gemm_tile_edges(B, M, K, batch):
     pm.close()
 
 
+# ap_gemm_static in several passes: more rows than one pass takes, and rows so long that the copy of 320 of them exceeds the
+# static array (passes of half the rows); and the sizes on either side of its dense kernel
+@pytest.mark.parametrize("M,K,batch,bits", [(2100, 2048, 2100, [5]), (20, 65536 + 96, 300, [3, 8]), (96, 256, 700, ALL_BITS),
+                                            (96, 288, 700, [4, 7]), (33, 512, 49, [6, 8]), (33, 544, 49, [6, 8])])
+def test_static_gemm_passes_and_dense_kernel(B, M, K, batch, bits):
+    import torch
+    idx, luts, x = inputs.make_case(48, M, K, batch=batch, bit_widths=bits)
+    rows = np.unique(np.random.default_rng(batch).integers(0, M, size=24))
+    pm = B.ap_pack(idx, luts)
+    xd = torch.from_numpy(x).cuda()
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    guard = 64
+    for b in bits:
+        buf = torch.full((guard + batch * M + guard,), -7.0, dtype=torch.float16, device="cuda")
+        assert B.lib.ap_gemm_static(pm.handle, b, xd.data_ptr(), buf.data_ptr() + 2 * guard, batch, sp) == 0
+        torch.cuda.synchronize()
+        out = buf.cpu().numpy()
+        assert np.all(out[:guard] == -7.0) and np.all(out[-guard:] == -7.0)
+        check_against_oracle(out[guard:-guard].reshape(batch, M), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
 def test_fused_gemm_non_finite_values_stay_where_they_are(B):
     # infinities in a table (b = 3, 8) and in one activation reach exactly the outputs that use them, also next to the ragged
     # last step; an x that is not 16-byte aligned gives the same values by the other route

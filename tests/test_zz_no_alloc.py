@@ -40,8 +40,10 @@ def test_static_gemm_matches_gemm_on_two_calls_in_a_row(B):
     import torch
     # first call: larger matrix, ragged in every dimension (rows not a multiple of 16, batch not a
     # multiple of 16, a ragged last span); second call: a smaller matrix, which leaves the first
-    # call's weights in the rest of the shared array
-    cases = [((200, 2048 + 96, 37), (3, 8)), ((52, 160, 5), (4, 7))]
+    # call's weights in the rest of the shared array; then calls that use the array themselves, each over what the one
+    # before it left there: a copy of x and partial sums, a smaller copy, dense weights, a copy again
+    cases = [((200, 2048 + 96, 37), (3, 8)), ((52, 160, 5), (4, 7)), ((200, 2048 + 96, 150), (5, 8)), ((70, 544, 49), (4, 7)),
+             ((52, 160, 49), (4, 7)), ((70, 544, 64), (3, 6))]
     for (M, K, batch), bits in cases:
         idx, luts, x = inputs.make_case(41, M, K, batch=batch)
         pm = B.ap_pack(idx, luts)
