@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2402_10517_amd import inputs
-from gpu_util import check_against_oracle
+from gpu_util import check_against_oracle, check_planted, plant_infinities
 
 pytestmark = pytest.mark.gpu
 ALL_BITS = list(range(3, 9))
@@ -106,6 +106,27 @@ def test_fused_gemm_tile_edges(B, M, K, batch):
     pm.close()
 
 
+# more row blocks times batch tiles than CUs (4 waves per workgroup), and both sides of the largest batches that run on
+# the fused kernel, in sampled rows
+@pytest.mark.parametrize("M,K,batch,bits", [(16400, 160, 17, ALL_BITS), (16400, 160, 48, ALL_BITS), (16400, 160, 64, ALL_BITS),
+                                            (700, 544, 256, [6, 8]), (700, 544, 257, [6, 8]), (700, 544, 384, [4, 5]),
+                                            (700, 544, 385, [4, 5]), (700, 544, 512, [3]), (700, 544, 513, [3])])
+def test_fused_gemm_many_workgroups_and_largest_batches(B, M, K, batch, bits):
+    import torch
+    idx, luts, x = inputs.make_case(47, M, K, batch=batch, bit_widths=bits)
+    rows = np.unique(np.concatenate([np.arange(66), np.random.default_rng(batch).integers(0, M, size=64), np.arange(M - 70, M)]))
+    pm = B.ap_pack(idx, luts)
+    xd = torch.from_numpy(x).cuda()
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for b in bits:
+        y = torch.full((batch, M), -7.0, dtype=torch.float16, device="cuda")
+        assert B.lib.ap_gemm_static(pm.handle, b, xd.data_ptr(), y.data_ptr(), batch, sp) == 0
+        for out in (B.ap_gemm(pm, b, xd), y):
+            torch.cuda.synchronize()
+            check_against_oracle(out.cpu().numpy(), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
 # ap_gemm_static in several passes: more rows than one pass takes, and rows so long that the copy of 320 of them exceeds the
 # static array (passes of half the rows); and the sizes on either side of its dense kernel
 @pytest.mark.parametrize("M,K,batch,bits", [(2100, 2048, 2100, [5]), (20, 65536 + 96, 300, [3, 8]), (96, 256, 700, ALL_BITS),
@@ -129,29 +150,30 @@ def test_static_gemm_passes_and_dense_kernel(B, M, K, batch, bits):
 
 
 def test_fused_gemm_non_finite_values_stay_where_they_are(B):
-    # infinities in a table (b = 3, 8) and in one activation reach exactly the outputs that use them, also next to the ragged
-    # last step; an x that is not 16-byte aligned gives the same values by the other route
+    # one infinite weight in some rows (b = 3, 8; also in the ragged last step) and an infinity in one activation reach exactly
+    # the outputs that use them; an x that is not 16-byte aligned gives the same values by the other route
     import torch
     M, K, batch = 70, 2048 + 160, 20
-    idx, luts, x = inputs.make_case(43, M, K, batch=batch)
-    x[3, K - 1] = np.float16(np.inf)
     for b in (3, 8):
-        lut = luts[b].copy()
-        lut[5, :] = np.abs(lut[5, :])
-        lut[5, (1 << b) - 1] = np.float16(np.inf)
-        w = lut[np.arange(M)[:, None], idx >> (8 - b)].astype(np.float64)
+        idx, luts, x = inputs.make_case(43, M, K, batch=batch, bit_widths=[b])
+        cells = [(0, K - 1, 1), (5, K - 32, -1), (18, 2048 + 3, 1), (40, 2047, 1), (63, 0, -1), (69, 2048 + 50, 1)]
+        plant_infinities(idx, luts[b], b, x, cells)
+        x[3, 100] = np.float16(np.inf)
+        w = luts[b][np.arange(M), idx[:, 100] >> (8 - b)].astype(np.float64)
+        assert np.all(w != 0)
         with np.errstate(invalid="ignore"):
-            ref = (x.astype(np.float64)[:, None, :] * w[None]).sum(axis=2)
-        pm = B.ap_pack(idx, {b: lut})
+            row3 = np.inf * w
+            for r, c, sign in cells:
+                row3[r] += sign * np.inf * x[3, c].astype(np.float64)
+        keep = np.arange(batch) != 3
+        pm = B.ap_pack(idx, luts)
         xd = torch.from_numpy(x).cuda()
         shifted = torch.empty(batch * K + 1, dtype=torch.float16, device="cuda")[1:].view(batch, K)
         shifted.copy_(xd)
         ys = [B.ap_gemm(pm, b, xd), B.ap_gemm(pm, b, shifted)]
         torch.cuda.synchronize()
         for y in ys:
-            got = y.cpu().numpy().astype(np.float64)
-            finite = np.isfinite(ref)
-            assert np.array_equal(np.isnan(got), np.isnan(ref))
-            assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
-            assert np.allclose(got[finite], ref[finite], rtol=2e-3, atol=1e-3 * np.abs(ref[finite]).max())
+            got = y.cpu().numpy()
+            check_planted(got[keep], idx, luts[b], b, x[keep], cells, rows=range(M))
+            assert np.array_equal(got[3].astype(np.float64), row3, equal_nan=True)
         pm.close()

@@ -665,6 +665,18 @@ def test_tile_kernel_on_ragged_rows_and_at_batch_nine_to_sixteen(B, batch):
     pm.close()
 
 
+# two tiles per workgroup on ragged rows: at 3 bits on tall matrices, on long rows, and at batch 9 to 16
+@pytest.mark.parametrize("M,K,batch,bits", [(24580, 416, 8, [3]), (8180, 16384 + 32, 5, [4]), (15363, 800, 16, ALL_BITS),
+                                            (8190, 288, 9, ALL_BITS)])
+def test_two_tiles_per_workgroup_on_ragged_rows(B, M, K, batch, bits):
+    rows = np.unique(np.concatenate([np.arange(34), np.random.default_rng(M).integers(0, M, size=60), np.arange(M - 34, M)]))
+    idx, luts, x = inputs.make_case(49, M, K, batch=batch, sigma=0.01, bit_widths=bits)
+    pm = B.ap_pack(idx, luts)
+    for b in bits:
+        check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
 def _octet_cells(M, K):
     """One cell per row: columns of the last octet of 256 columns (its first and last chunk, the first and the last of
     its four runs) and of the first one; rows of different tiles."""
