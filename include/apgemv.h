@@ -109,8 +109,8 @@ ap_status ap_unpack(const ap_matrix *h, uint8_t *idx_host_out, void *stream);
  *   x_dev  device, batch*K binary16 row-major, 16-byte aligned
  *   y_dev  device, batch*M binary16 row-major, 2-byte aligned; must not overlap x_dev or the blob
  *   batch  1..16 (the paper switches to a dequantise + dense GEMM path above about 16, Section 6.2).
- *          Batches 9..16 run as one launch on matrices of about 1024 rows or more, else (and with a tuning override) as
- *          two passes on the stream, the first over rows 0..7
+ *          Batches 9..16 run as one launch on matrices of about 2048 rows or more (1024 at b <= 5 and up to 12288
+ *          columns, 512 at up to 1024 columns), else (and with a tuning override) as two passes on the stream, the first over rows 0..7
  * Products are exact in binary32, accumulation is binary32, the result is rounded to binary16
  * (round to nearest even).  Asynchronous on `stream`; allocates nothing, synchronises nothing,
  * never repacks; the bit-width is chosen per call.  Results are deterministic (no atomics).
@@ -208,8 +208,8 @@ ap_status ap_gemv_list(const ap_gemv_list_item *items, int count, void *stream);
  * list launches of the kernel that single calls use at batch 1 and 2 (any shapes and bit-widths together, up
  * to 32 per launch; bit-identical to separate ap_gemv calls).  At batch >= 3 the items
  * that the matrix-core kernel on tiles of 16 rows can take (K_i % 256 == 0) are launched together per
- * bit-width and class of row length, up to 32 per launch, whenever such a group has at least 1024 row
- * groups in total (the size rule of ap_gemv applied to the launch); every other item runs as its own
+ * bit-width and class of row length, up to 32 per launch, whenever such a group has at least two
+ * items and 1024 groups of 4 rows in total; every other item runs as its own
  * ap_gemv call on the same stream.  Outputs meet the tolerance of ap_gemv; an item that runs on the tile
  * kernel is bit-identical to ap_gemv on that kernel (AP_VARIANT_TILE) when every row of its launch has
  * at least 2048 columns (shorter rows lower the number of waves per tile of the launch, which changes the

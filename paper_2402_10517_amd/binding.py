@@ -283,7 +283,7 @@ def ap_dequantize(pm, b, w=None, stream=None):
 
 
 def ap_gemm(pm, b, x, work=None, y=None, stream=None):
-    """Large-batch path: x (batch, K) float16 -> y (batch, M) float16 via dequantise + dense GEMM."""
+    """x (batch, K) float16 -> y (batch, M) float16 for any batch; work = device memory of ap_gemm_workspace_size bytes."""
     assert x.dtype == torch.float16 and x.is_cuda and x.is_contiguous() and x.dim() == 2
     batch = x.shape[0]
     size = ctypes.c_size_t(0)

@@ -367,8 +367,8 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
     }
     m.count = count;
     m.batch = batch;
-    // The matrix-core kernel on tiles of 16 rows when the launch as a whole is large enough for it (the
-    // rule of ap_gemv, applied to the sum of the row groups) or when the first handle asks for it
+    // The matrix-core kernel on tiles of 16 rows when the launch as a whole is large enough for it (1024 row
+    // groups in total at batch 5..8, 2048 at batch 3, 4) or when the first handle asks for it
     // (AP_VARIANT_TILE).  Measured on the 7B projections (q,k,v: 3 x 4096x4096; gate,up: 2 x 11008x4096)
     // against the ALU kernel of this launch: batch 5..8 9.8 / 11.5 / 16.7 us against 17.7 / 19.7 / 23.7
     // (q,k,v; b = 3, 4, 8) and 15.0 / 19.0 / 28.4 against 27.7 / 31.2 / 35.9 (gate,up); batch 3..4 level

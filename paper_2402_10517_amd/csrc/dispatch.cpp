@@ -70,14 +70,11 @@ hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
         return launch_gemv(pass, stream);
     }
     if (a.batch >= 2 && (forced || (!tuned && tile_pays(a)))) return launch_matrix_tile(a, stream);
-    // What is left for batch >= 2 (smaller matrices, batch 2..4) was settled by
-    // measurement on the 70B shapes (8192x8192, 28672x8192, 8192x28672; all b):
-    //  * batch 2: the plain kernel (one group of rows per workgroup) wins everywhere;
-    //  * batch 5..8 with >= 2048 groups of rows: the matrix-core kernel with in-wave exchange, every b
-    //    (up to 24 % faster than the ALU kernels at b <= 5, level at b = 8);
-    //  * batch 3..4: that kernel for b >= 6 and, on the tallest matrices (>= 4096 groups), for b = 4, 5,
-    //    when every span has its own wave; b = 3 and short matrices stay on the plain kernel, long
-    //    rows at b >= 6 on the first matrix-core kernel.
+    // What is left for batch >= 2: the plain ALU kernel at batch 2 (fastest everywhere), on smaller matrices, and at batch 3, 4 on ragged
+    // rows below 8192 columns (b >= 4), where the matrix-core kernel with in-wave exchange takes those of a multiple of 128 columns
+    // from 2048 row groups on at b >= 6, from 4096 on at b = 4, 5 too (up to 24 % faster than the ALU kernels).  A handle with
+    // an option stays away from the tile kernel; for it the rules of the exchange kernel reach further: batch 5..8 at every b, and
+    // one wave per span at batch 3, 4.
     // variant: 1 = never the in-wave-exchange kernel, 3 = whenever the shape allows (tuning overrides).
     if (a.batch >= 2 && a.K % 128 == 0 && a.variant != 1) {
         const int groups = padded_rows(a.M) / kRowsPerGroup;
@@ -91,8 +88,8 @@ hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
         if (a.variant == 3 || pays)
             return launch_matrix_exchange(a, stream);
     }
-    // The first matrix-core kernel (one row per lane): batch 3..8 at b >= 6 when the row length allows
-    // it; at b <= 5 the four rows' small tables of a block share LDS banks and it is slower.  Matrices
+    // The first matrix-core kernel (one row per lane) is reached by handles with options only: batch 3..8 at b >= 6 when the row
+    // length allows it; at b <= 5 the four rows' small tables of a block share LDS banks and it is slower.  Matrices
     // with fewer than 2048 groups of rows stay on the ALU kernels: measured on 4096x4096 and 4096x11008
     // at batch 3, 4, 8 the ALU kernels are level or up to 30 % faster there (the device is not full,
     // and a call is bound by latency, not by the multiply-accumulates the matrix cores take over).

@@ -10,9 +10,9 @@
 //  * The units are loaded 4 lanes to 64 contiguous bytes and change to that order through a wave-private LDS buffer (one
 //    ds_write_b128 + ds_read_b128 per slice).  Loaded directly in the instruction's order every lane is a cache access of its
 //    own, and the vector L1 then bounds the kernel: 28672 x 8192, b = 4, batch 64: 74 -> 59 us.
-//  * Activations: up to 48 batch rows take the same way through LDS.  Beyond that a small kernel first copies x to
-//    the caller's workspace in fragment order, and the waves read their fragments as whole lines (3 us for the copy; the
-//    exchange of 4 tiles would cost as much LDS time as the lookups).
+//  * Activations: up to 48 batch rows per workgroup take the same way through LDS.  With 64 (batch 49..64, 97..128, 145 and more)
+//    a small kernel first copies x to the workspace in fragment order, and the waves read their fragments as whole lines (3 us for
+//    the copy; the exchange of 4 tiles would cost as much LDS time as the lookups).
 //  * Tables: 32 lanes of an LDS clock = 16 row groups x 2 lane groups, each with a bank of its own: two copies per row, the rows
 //    2 rp and 2 rp + 1 of a group in the halves of one dword, entries 256 bytes apart, so that one v_perm_b32 of the index byte
 //    and the lane's base makes an address (64 KB at 8 bits, 8 KB at 4 and 5).  b = 3 looks up pairs.
@@ -78,8 +78,7 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     const int M = a.M, K = a.K, batch = a.batch, ntiles = a.ntiles;
     constexpr int kRows = 64, kGroups = 16, kStepChunks = 4, kNT = 16 * NJ;
     constexpr int kRedRow = 16 * 16 + 16;               // bytes of one batch row of partial sums: 16 groups x 4 rows
-    constexpr int kRedTiles = NJ <= 4 ? NJ : 4;         // tiles of 16 batch rows summed at a time
-    constexpr int kRedBytes = W * kRedTiles * 16 * kRedRow;
+    constexpr int kRedBytes = W * NJ * 16 * kRedRow;
     constexpr int kBounceSlices = B <= 4 ? B : (B + 1) / 2;
     constexpr int kBounce = (!XF && NJ > kBounceSlices ? NJ : kBounceSlices) * 1024;
     constexpr int kMain = BT::kBytes + W * kBounce;
@@ -321,43 +320,39 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
         }
     }
 
-    // ---- waves are added in fixed order, one tile of 16 batch rows at a time: element q of acc[j][r] is row group
-    // 4 kg + q (row r of it), batch row 16 j + i
+    // ---- waves are added in fixed order: element q of acc[j][r] is row group 4 kg + q (row r of it), batch row 16 j + i
     const bool wide = M % 4 == 0 && reinterpret_cast<uintptr_t>(y) % 8 == 0;
+    __syncthreads();
 #pragma unroll
-    for (int j0 = 0; j0 < NJ; j0 += kRedTiles) {
-        __syncthreads();
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int j = 0; j < kRedTiles; ++j)
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4_t *>(smem + ((wave * NJ + j) * 16 + i) * kRedRow + (4 * kg + q) * 16) =
+                float4_t{acc[j][0][q], acc[j][1][q], acc[j][2][q], acc[j][3][q]};
+    __syncthreads();
+    for (int o = tid; o < 256 * NJ; o += nth) {
+        const int n = o >> 4, g = o & 15;
+        float4_t s = *reinterpret_cast<const float4_t *>(smem + n * kRedRow + g * 16);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4_t *>(smem + ((wave * kRedTiles + j) * 16 + i) * kRedRow + (4 * kg + q) * 16) =
-                    float4_t{acc[j0 + j][0][q], acc[j0 + j][1][q], acc[j0 + j][2][q], acc[j0 + j][3][q]};
-        __syncthreads();
-        for (int o = tid; o < 256 * kRedTiles; o += nth) {
-            const int nn = o >> 4, g = o & 15, n = 16 * j0 + nn;
-            float4_t s = *reinterpret_cast<const float4_t *>(smem + nn * kRedRow + g * 16);
+        for (int w = 1; w < W; ++w) s += *reinterpret_cast<const float4_t *>(smem + (w * NJ * 16 + n) * kRedRow + g * 16);
+        const int row = row0 + 4 * g;
+        if (n < nrows && row < M && a.parts > 1) {
+            float *dst = a.partial + ((size_t)part * batch + n0 + n) * M + row;
+            if (M % 4 == 0) *reinterpret_cast<float4_t *>(dst) = s;
+            else
 #pragma unroll
-            for (int w = 1; w < W; ++w) s += *reinterpret_cast<const float4_t *>(smem + (w * kRedTiles * 16 + nn) * kRedRow + g * 16);
-            const int row = row0 + 4 * g;
-            if (n < nrows && row < M && a.parts > 1) {
-                float *dst = a.partial + ((size_t)part * batch + n0 + n) * M + row;
-                if (M % 4 == 0) *reinterpret_cast<float4_t *>(dst) = s;
-                else
+                for (int r = 0; r < 4; ++r)
+                    if (row + r < M) dst[r] = s[r];
+        } else if (n < nrows && row < M) {
+            uint16_t *dst = y + (size_t)(n0 + n) * M + row;
+            uint16_t hv[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (row + r < M) dst[r] = s[r];
-            } else if (n < nrows && row < M) {
-                uint16_t *dst = y + (size_t)(n0 + n) * M + row;
-                uint16_t hv[4];
+            for (int r = 0; r < 4; ++r) hv[r] = __builtin_bit_cast(uint16_t, __float2half_rn(s[r]));
+            if (wide) *reinterpret_cast<u32x2 *>(dst) = u32x2{hv[0] | ((uint32_t)hv[1] << 16), hv[2] | ((uint32_t)hv[3] << 16)};
+            else
 #pragma unroll
-                for (int r = 0; r < 4; ++r) hv[r] = __builtin_bit_cast(uint16_t, __float2half_rn(s[r]));
-                if (wide) *reinterpret_cast<u32x2 *>(dst) = u32x2{hv[0] | ((uint32_t)hv[1] << 16), hv[2] | ((uint32_t)hv[3] << 16)};
-                else
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (row + r < M) dst[r] = hv[r];
-            }
+                for (int r = 0; r < 4; ++r)
+                    if (row + r < M) dst[r] = hv[r];
         }
     }
 }

@@ -470,7 +470,8 @@ static hipError_t launch_one(const GemvArgs &a, hipStream_t stream)
     if (nw > nspans) nw = nspans;
     if (NB <= 2 && a.waves_per_group == 0) nw = batch1_waves(nspans); // batch 2 gains the same (5 to 14 %)
     // several row groups per workgroup at batch 5..8 when every span has its own wave and there are
-    // enough groups to keep the device full (at batch 2..4 the plain kernel measured faster)
+    // enough groups to keep the device full (at batch 2..4 the plain kernel measured faster); such calls
+    // come here only from handles with options, the others run on the tile kernel
     int rg = a.row_groups_per_wg;
     if (rg < 0) rg = (nspans <= kMaxWaves && groups >= 2048 && NB >= 8) ? kMaxRowGroups : 1;
     if (rg > kMaxRowGroups) rg = kMaxRowGroups;

@@ -1,4 +1,4 @@
-// Small-batch kernel (batch 2..8) that feeds v_mfma_f32_16x16x32_f16 from the dequantising lanes
+// Small-batch kernel (batch 2..16) that feeds v_mfma_f32_16x16x32_f16 from the dequantising lanes
 // (Section 6.2 "Matrix-Matrix Multiplication Performance": the paper's kernel runs batches on the
 // ordinary ALUs and slows down by up to 2x at batch 8).
 //
@@ -615,7 +615,7 @@ hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t st
         long_rows = a.item[i].K >= 12288;
     }
     for (int i = a.count; i < kMaxListItems; ++i) a.group_begin[i] = 0x7fffffff;
-    int nw = long_rows ? 8 : 4; // as in single calls; no more waves than the shortest row has pairs of octets
+    int nw = long_rows ? 8 : 4; // as in single calls on this kernel by option; no more waves than the shortest row has pairs of octets
     if (nw > min_pairs) nw = min_pairs;
     switch (b) {
     case 3: return launch_tile_list_b<3>(a, total, nw, batch, stream);

@@ -50,7 +50,7 @@ inline FusedPlan fused_plan(const GemvArgs &a)
 }
 // Column parts (workgroups that share a row block's columns): as many as give every CU one workgroup, a step or more per wave.
 // Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5 batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3
-// batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096 b = 4 batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups
+// batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096 b = 3 batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups
 // costs more than idle CUs.
 inline int fused_parts_wanted(const FusedPlan &p)
 {
