@@ -18,30 +18,44 @@ namespace apgemv {
 //                 6144x4096 1.07/0.94/0.94  6144x8192 1.02/0.89/0.88  6144x11008 1.50/1.52/1.16  6144x13824 1.45/1.52/1.12
 //                 8192x4096 1.18/1.16/1.28  8192x4224 1.21/1.06/1.06  8192x8192 1.21/1.09/1.20  8192x16384 1.63/1.76/1.25
 //   batch 2       4096x4096 1.01/0.95/0.92  6144x11008 0.77/0.77/0.77
-// At batch 3 and 4 below 2048 row groups the ALU kernel is close, and two things decide: the CUs that the last round of tiles leaves
-// idle (5120 rows are 320 tiles, 1.25 rounds), and the last span of the ALU kernel's rows (whole at 8192 and 16384 columns; at
-// b >= 7 rows of more than 6 spans).  b = 4 always wins there (1.0 to 2.4).
+// Where the ALU kernel is close, three things decide: the CUs that the last round of tiles leaves idle (5120 rows are 320 tiles, 1.25
+// rounds; `busy` below), the last span of the ALU kernel's rows (whole at 8192 and 16384 columns; at b >= 7 it gains again beyond 6
+// spans), and whether the row ends inside 128 columns (the last octet is then mostly padding, and the other kernel is the ALU kernel
+// at every height).  From another 11000 calls at batch 4, 6, 8 (24 heights 3072..12200, 34 row lengths), batch 4, b = 7: 5100 / 6300 /
+// 7600 x 8224 1.02/1.24/1.37  x 11808 0.90/1.04/1.17  x 15808 0.70/0.85/0.92  x 18432 0.98/1.20/1.28, 8600 / 10600 x 15808 0.76/0.90;
+// b = 8: 5700 / 6300 x 13056 1.06/1.14, 6700 / 7600 x 8192 0.89/1.01; b = 3: 5100 / 5400 x 8192 0.92/1.01, 8600 / 9800 x 7200 0.89/1.0;
+// batch 8, b = 8: 5100 / 6300 x 2208 0.93/1.08  x 7200 0.83/0.98  x 10400 0.98/1.21, 5700 x 2016 0.85.  b = 4 always wins there
+// (1.0 to 2.4).  What is left of calls slower than without this kernel: 1.3 % of them by 3 to 12 %.
 static bool tile_pays(const GemvArgs &a)
 {
-    const int groups = padded_rows(a.M) / kRowsPerGroup;
+    const int groups = padded_rows(a.M) / kRowsPerGroup, b = a.b, K = a.K;
     if (a.batch >= 9)
-        return groups >= 512 || (groups >= 256 && a.b <= 5 && a.K <= 12288 && (a.b <= 4 || a.K <= 4096 || a.batch >= 13)) ||
-               (groups >= 128 && a.K <= 1024);
-    // tiles of the last round: at least 3/4, 4/5 of the CUs busy on average over the rounds
-    const int tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
-    const bool most = tiles >= 192 * rounds, full = tiles >= 205 * rounds;
-    if (a.batch >= 5) {
-        if (a.b == 8 && a.K % 256 && a.K > 2048 && a.K < 3072 && groups < 2048 && !most) return false;
-        return groups >= 768 || (groups >= 512 && a.b == 3);
-    }
+        return groups >= 512 || (groups >= 256 && b <= 5 && K <= 12288 && (b <= 4 || K <= 4096 || a.batch >= 13)) ||
+               (groups >= 128 && K <= 1024);
     if (a.batch < 3) return false;
-    if (groups >= 2048) return a.K >= 8192 || a.K % 256 == 0 || a.b == 3;
-    if (groups < 768 || a.K < 4096 || (a.K < 8192 && (a.K % 256 || a.b > 4))) return false;
-    if (a.b == 4) return true;
-    if (a.b == 3) return a.K > 8192 || most;
-    if (a.b <= 6) return a.K > 8192 || full;
-    if (a.K <= 8192) return full;
-    return a.K <= 12288 || (rounds > 1 ? most : full);
+    const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
+    auto busy = [&](int percent) { return 100 * tiles >= percent * 256 * rounds; }; // of the CUs, over the rounds
+    const bool ragged = K % 128 != 0;
+    if (a.batch >= 5) {
+        if (groups < 512 || (groups < 768 && b > 3)) return false;
+        if (!ragged || groups >= 2048 || b < 7) return true;
+        if (K <= 2048) return K <= (b == 8 ? 1024 : 1536);
+        if (b == 7) return (K <= 2560 || (K > 4096 && K <= 5376) || (K > 8192 && K <= 12800)) || busy(65);
+        if (rounds == 1 && K > 4096 && K <= 8192) return busy(80);
+        return (K > 8192 && K <= 11264) || busy(65);
+    }
+    if (groups >= 2048) {
+        if (b >= 7 && K > 8192 && ragged) return groups >= 3072 || (K <= 12288 && (K <= 9472 || busy(75)));
+        return K >= 8192 || K % 256 == 0 || (b == 3 && busy(78));
+    }
+    if (groups < 768 || K < 4096 || (K < 8192 && (K % 256 || b > 4))) return false;
+    if (b == 4) return true;
+    if (b == 3) return K > 8192 || busy(65);
+    if (b <= 6) return K > 8192 || busy(80);
+    if (K <= 8192) return busy(85);
+    if (rounds == 1) return (K <= 12288 && !ragged) || (busy(80) && (K <= 12288 || !ragged));
+    if (ragged) return K <= 12288 && (K <= 9472 || busy(75));
+    return K <= 12288 || busy(68);
 }
 
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
