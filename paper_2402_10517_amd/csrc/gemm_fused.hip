@@ -113,7 +113,6 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     const int lastspan = (chunks - 1) / kSpanLanes;
     const int ragged = chunks - lastspan * kSpanLanes;
     const int nsteps = (chunks + kStepChunks - 1) / kStepChunks;
-    const int nfull = chunks / kStepChunks;
 
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, 0xffffffffu, kBufferRsrcWord3);
@@ -165,6 +164,14 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     int st = (int)((long long)nsteps * slot / slots);
     const int st1 = (int)((long long)nsteps * (slot + 1) / slots);
     const bool any = st < st1;
+    // Unconditional (a wave without steps loads some step and drops it): past a branch the compiler cannot tell these loads from
+    // the tables' and waits for all of them before the first table entry is written (4096 x 4096 b = 3..8 batch 17, 64: 1 to 4 %).
+    auto load_first = [&]() {
+        const int first = any ? st : 0;
+        load_q(first);
+        load_x(first, 0);
+        load_x(first, 1);
+    };
 
     // ---- tables: bank = copy * 16 + group; all loads go out before the slice loads
     if constexpr (BT::kPair) {
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
         const int bank = tid & 31, r = (tid >> 5) & 3, e0 = (tid >> 7) & 1;
         const int row = row0 + (bank & 15) * 4 + r;
         const u32x4 c = *reinterpret_cast<const u32x4 *>(lut + (size_t)(row < M ? row : M - 1) * 8);
-        if (any) { load_q(st); load_x(st, 0); load_x(st, 1); }
+        load_first();
         uint32_t ev[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) ev[k] = e0 ? c[k] >> 16 : c[k] & 0xffffu;
@@ -190,26 +197,37 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
         if (m0 == 0) fill(std::integral_constant<int, 0>{});
         else fill(std::integral_constant<int, 16>{});
     } else {
-        constexpr int kPieces = (2 << B) / 16; // 8 entries each
-        constexpr int kTasks = 64 * kPieces, kPer = (kTasks + nth - 1) / nth;
+        // Thread (row group, row pair, piece of 8 entries) loads for both copies: 4 lanes read 64 contiguous bytes of a row, and of
+        // every two neighbours one writes its entries to the first copy first, the other to the second, which spreads a store over the
+        // banks of both.  A thread per bank instead loaded every piece twice and each lane from a row of its own: 4096 x 4096
+        // batch 17 b = 8 12.2 -> 11.6 us, b = 6 10.8 -> 10.4, level at b = 4, 5.
+        constexpr int kPieces = (2 << B) / 16;
+        constexpr int kTasks = 32 * kPieces, kPer = (kTasks + nth - 1) / nth;
+        constexpr int kLanes = kPieces < 4 ? kPieces : 4; // neighbouring lanes of a row
         u32x4 lo[kPer], hi[kPer];
 #pragma unroll
         for (int m = 0; m < kPer; ++m) {
-            const int k = tid + m * nth, bank = k & 31, rp = (k >> 5) & 1, pc = k >> 6 < kPieces ? k >> 6 : kPieces - 1;
-            const int ra = row0 + (bank & 15) * 4 + rp * 2, rlo = ra < M ? ra : M - 1, rhi = ra + 1 < M ? ra + 1 : M - 1;
+            const int k = tid + m * nth < kTasks ? tid + m * nth : kTasks - 1;
+            const int g = (k / kLanes) & 15, rp = (k / (kLanes * 16)) & 1, pc = k / (kLanes * 32) * kLanes + k % kLanes;
+            const int ra = row0 + g * 4 + rp * 2, rlo = ra < M ? ra : M - 1, rhi = ra + 1 < M ? ra + 1 : M - 1;
             lo[m] = reinterpret_cast<const u32x4 *>(lut + ((size_t)rlo << B))[pc];
             hi[m] = reinterpret_cast<const u32x4 *>(lut + ((size_t)rhi << B))[pc];
         }
-        if (any) { load_q(st); load_x(st, 0); load_x(st, 1); }
+        load_first();
 #pragma unroll
         for (int m = 0; m < kPer; ++m) {
-            const int k = tid + m * nth, bank = k & 31, rp = (k >> 5) & 1, pc = k >> 6;
-            uint8_t *dst = tab + rp * 128 + bank * 4;
-            if (kTasks % nth == 0 || k < kTasks)
+            const int k = tid + m * nth;
+            const int g = (k / kLanes) & 15, rp = (k / (kLanes * 16)) & 1, pc = k / (kLanes * 32) * kLanes + k % kLanes;
+            if (kTasks % nth == 0 || k < kTasks) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    *reinterpret_cast<uint32_t *>(dst + BT::slot_of(8 * pc + e) * 256) =
-                        (e & 1) ? (lo[m][e >> 1] >> 16) | (hi[m][e >> 1] & 0xffff0000u) : (lo[m][e >> 1] & 0xffffu) | (hi[m][e >> 1] << 16);
+                for (int c = 0; c < 2; ++c) {
+                    uint8_t *dst = tab + rp * 128 + ((c ^ (k & 1)) * 16 + g) * 4;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        *reinterpret_cast<uint32_t *>(dst + BT::slot_of(8 * pc + e) * 256) =
+                            (e & 1) ? (lo[m][e >> 1] >> 16) | (hi[m][e >> 1] & 0xffff0000u) : (lo[m][e >> 1] & 0xffffu) | (hi[m][e >> 1] << 16);
+                }
+            }
         }
     }
     __syncthreads();
@@ -281,15 +299,13 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     if (any) {
         exchange_q();
         merge();
-        load_q(st + 1 < st1 ? st + 1 : st);
+        if (st + 1 < st1) load_q(st + 1);
         lookup(0);
         if constexpr (!XF) exchange(X[0], 0, NJ);
         pack();
     }
-    const int stf = st1 < nfull ? st1 : nfull;
-    for (; st < stf; ++st) {
-        const int next = st + 1 < st1 ? st + 1 : st;    // the last pass loads and looks up its own step again
-        const int next2 = st + 2 < st1 ? st + 2 : next;
+    for (; st + 1 < st1; ++st) {
+        const int next2 = st + 2 < st1 ? st + 2 : st + 1; // the pass before the last step loads that step's units again
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (t == 2) exchange_q();
@@ -299,12 +315,15 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
             }
             lookup((t + 1) & 3);
             products(t);
-            load_x(t < 2 ? st : next, (t + 2) & 3);
+            load_x(t < 2 ? st : st + 1, (t + 2) & 3);
             if constexpr (!XF) exchange(X[(t + 1) & 1], 0, NJ);
             pack();
         }
     }
-    if (st < st1) { // the ragged step: chunks past the row count for nothing
+    // The wave's last step, which prepares nothing for a next one: with up to 4096 columns it is the only one, and looking up a step that
+    // does not follow took 1.3 to 1.6 us of 11 to 13 (4096 x 4096, batch 17 and 33, b = 5).  Chunks past the row (a ragged step)
+    // count for nothing.
+    if (any) {
         const uint32_t keep = kg < chunks - st * kStepChunks ? 0xffffffffu : 0u;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -376,14 +395,23 @@ __global__ __launch_bounds__(256) void fragment_x_kernel(const uint16_t *__restr
     }
 }
 
-// y = sum of the parts, in order (n = batch * M values each)
+// y = sum of the parts, in order (n = batch * M values each).  All latency: a part's values come from beyond this XCD's L2, so the
+// loads of up to 8 parts go out together (4096 x 4096 b = 5 batch 33, 4 parts: 3.0 -> 2.5 us one after the other against together).
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restrict__ partial, uint16_t *__restrict__ y, size_t n, int parts)
 {
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= n) return;
+    constexpr int kBurst = 8;
     if (n % 4 == 0) {
-        float4_t s = *reinterpret_cast<const float4_t *>(partial + i);
-        for (int p = 1; p < parts; ++p) s += *reinterpret_cast<const float4_t *>(partial + p * n + i);
+        float4_t s = {0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < parts; p0 += kBurst) {
+            float4_t v[kBurst];
+#pragma unroll
+            for (int p = 0; p < kBurst; ++p) v[p] = *reinterpret_cast<const float4_t *>(partial + (size_t)(p0 + p < parts ? p0 + p : p0) * n + i);
+#pragma unroll
+            for (int p = 0; p < kBurst; ++p)
+                if (p0 + p < parts) s = p0 + p ? s + v[p] : v[p];
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[i + e] = __builtin_bit_cast(uint16_t, __float2half_rn(s[e]));
     } else {
