@@ -11,8 +11,8 @@
 //    ds_write_b128 + ds_read_b128 per slice).  Loaded directly in the instruction's order every lane is a cache access of its
 //    own, and the vector L1 then bounds the kernel: 28672 x 8192, b = 4, batch 64: 74 -> 59 us.
 //  * Activations: up to 48 batch rows per workgroup take the same way through LDS.  With 64 (batch 49..64, 97..128, 145 and more)
-//    a small kernel first copies x to the workspace in fragment order, and the waves read their fragments as whole lines (3 us for
-//    the copy; the exchange of 4 tiles would cost as much LDS time as the lookups).
+//    and several steps per wave a small kernel first copies x to the workspace in fragment order, and the waves read their fragments
+//    as whole lines (3 us for the copy; the exchange of 4 tiles costs as much LDS time per step as the lookups): fused_plan.
 //  * Tables: 32 lanes of an LDS clock = 16 row groups x 2 lane groups, each with a bank of its own: two copies per row, the rows
 //    2 rp and 2 rp + 1 of a group in the halves of one dword, entries 256 bytes apart, so that one v_perm_b32 of the index byte
 //    and the lane's base makes an address (64 KB at 8 bits, 8 KB at 4 and 5).  b = 3 looks up pairs.
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(256) void fragment_x_kernel(const uint16_t *__restr
 }
 
 // y = sum of the parts, in order (n = batch * M values each).  All latency: a part's values come from beyond this XCD's L2, so the
-// loads of up to 8 parts go out together (4096 x 4096 b = 5 batch 33, 4 parts: 3.0 -> 2.5 us one after the other against together).
+// loads of up to 8 parts go out together (4096 x 4096 b = 5 batch 33, 4 parts: 3.0 us one after the other, 2.65 together).
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restrict__ partial, uint16_t *__restrict__ y, size_t n, int parts)
 {
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -423,10 +423,9 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restri
     }
 }
 
-template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
+template <int B, int NJ, int W, bool XF> static hipError_t launch_fused_w(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
 {
-    constexpr bool kXF = NJ >= 4;
-    if (kXF) {
+    if (XF) {
         const int tiles = p.ntiles * NJ;
         hipLaunchKernelGGL(fragment_x_kernel, dim3((p.steps + 3) / 4, tiles), dim3(256), 0, stream, a.x, reinterpret_cast<u32x4 *>(work), a.K,
                            a.batch, tiles);
@@ -434,7 +433,7 @@ template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, c
         work += p.copy_bytes;
     }
     a.partial = reinterpret_cast<float *>(work);
-    hipLaunchKernelGGL((gemm_fused_kernel<B, NJ, W, kXF>), dim3(p.blocks * p.ntiles, a.parts), dim3(64 * W), 0, stream, a);
+    hipLaunchKernelGGL((gemm_fused_kernel<B, NJ, W, XF>), dim3(p.blocks * p.ntiles, a.parts), dim3(64 * W), 0, stream, a);
     if (a.parts > 1) {
         const size_t n = (size_t)a.M * a.batch;
         hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, a.partial, a.y, n, a.parts);
@@ -444,7 +443,10 @@ template <int B, int NJ, int W> static hipError_t launch_fused_w(FusedArgs &a, c
 
 template <int B, int NJ> static hipError_t launch_fused_nj(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)
 {
-    return p.waves == 8 ? launch_fused_w<B, NJ, 8>(a, p, work, stream) : launch_fused_w<B, NJ, 4>(a, p, work, stream);
+    if constexpr (NJ == 4) {
+        if (p.copy_bytes) return p.waves == 8 ? launch_fused_w<B, NJ, 8, true>(a, p, work, stream) : launch_fused_w<B, NJ, 4, true>(a, p, work, stream);
+    }
+    return p.waves == 8 ? launch_fused_w<B, NJ, 8, false>(a, p, work, stream) : launch_fused_w<B, NJ, 4, false>(a, p, work, stream);
 }
 
 template <int B> static hipError_t launch_fused_b(FusedArgs &a, const FusedPlan &p, uint8_t *work, hipStream_t stream)

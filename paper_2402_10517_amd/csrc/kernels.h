@@ -30,11 +30,21 @@ struct GemvArgs {
 
 // The fused large-batch kernel (gemm_fused.hip) takes a product straight from the packed form.
 // How it divides a product: `ntiles` tiles of up to 64 batch rows, evenly filled with `nj` times 16 rows; blocks of 64 rows;
-// `waves` per workgroup; with nj = 4 a copy of x in the scratch.
+// `waves` per workgroup; `copy_bytes` of the scratch hold a copy of x in fragment order (none if 0).
 struct FusedPlan {
     int ntiles, nj, blocks, waves, steps;
     size_t copy_bytes;
 };
+// Column parts (workgroups that share a row block's columns): as many as give every CU one workgroup, a step or more per wave.
+// Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5 batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3
+// batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096 b = 3 batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups
+// costs more than idle CUs.
+inline int fused_parts_wanted(const FusedPlan &p)
+{
+    const int fill = (int)(256 / ((long long)p.blocks * p.ntiles));
+    const int parts = fill < p.steps / p.waves ? fill : p.steps / p.waves;
+    return parts > 1 ? parts : 1;
+}
 inline FusedPlan fused_plan(const GemvArgs &a)
 {
     FusedPlan p;
@@ -45,18 +55,15 @@ inline FusedPlan fused_plan(const GemvArgs &a)
     // 65 -> 59 us with 4, 11008 x 4096 b = 4 batch 32 17.3 -> 20.3.
     p.waves = (long long)p.blocks * p.ntiles <= 256 ? 8 : 4;
     p.steps = (a.K / 32 + 3) / 4;
-    p.copy_bytes = p.nj < 4 ? 0 : (size_t)p.steps * 4 * p.ntiles * p.nj * 1024;
+    // With 64 batch rows per workgroup the copy of x pays from the third step of a wave on (at 8 bits, whose instance with the exchange
+    // spills in its loop, from the second): it is a launch of 2 to 3 us, the exchange 0.1 us per step.  With the copy / without,
+    // us: 1 step 4096 x 4096 batch 64 b = 3 13.9 / 12.3, b = 8 16.3 / 15.0, 1024 x 1024 b = 5 batch 300 10.1 / 7.9; 2 steps 8192 x 4096
+    // batch 64 b = 3 16.4 / 15.7, b = 5 18.7 / 18.5, b = 8 22.3 / 26.0; 4 steps 8192 x 8192 b = 5 24.8 / 24.8, 11008 x 4096 b = 8
+    // 25.6 / 29.6.
+    const int slots = p.waves * fused_parts_wanted(p);
+    const bool copy = p.nj >= 4 && p.steps > (a.b == 8 ? 1 : 2) * slots;
+    p.copy_bytes = copy ? (size_t)p.steps * 4 * p.ntiles * p.nj * 1024 : 0;
     return p;
-}
-// Column parts (workgroups that share a row block's columns): as many as give every CU one workgroup, a step or more per wave.
-// Measured, 1 / 2 / 4 / 8 parts, us: 4096 x 4096 b = 5 batch 33 (64 row blocks) 18.7 / 15.5 / 13.5 / 13.3, 8192 x 8192 b = 3
-// batch 64 (128) 27.9 / 23.5 / 29.9 / 38.5, 11008 x 4096 b = 3 batch 64 (172) 18.1 / 26.9 / 29.5: a second round of workgroups
-// costs more than idle CUs.
-inline int fused_parts_wanted(const FusedPlan &p)
-{
-    const int fill = (int)(256 / ((long long)p.blocks * p.ntiles));
-    const int parts = fill < p.steps / p.waves ? fill : p.steps / p.waves;
-    return parts > 1 ? parts : 1;
 }
 // As many of them as the scratch has room for partial sums of (besides the copy of x).
 inline int fused_parts(const FusedPlan &p, const GemvArgs &a)

@@ -106,9 +106,10 @@ def test_fused_gemm_tile_edges(B, M, K, batch):
     pm.close()
 
 
-# more row blocks times batch tiles than CUs (4 waves per workgroup), and both sides of the largest batches that run on
-# the fused kernel, in sampled rows
+# more row blocks times batch tiles than CUs (4 waves per workgroup; 64 batch rows with 2 steps per wave, the most without a copy of
+# x, and with a third, ragged one), and both sides of the largest batches that run on the fused kernel, in sampled rows
 @pytest.mark.parametrize("M,K,batch,bits", [(16400, 160, 17, ALL_BITS), (16400, 160, 48, ALL_BITS), (16400, 160, 64, ALL_BITS),
+                                            (5602, 1024, 190, ALL_BITS), (5602, 1056, 190, ALL_BITS),
                                             (700, 544, 256, [6, 8]), (700, 544, 257, [6, 8]), (700, 544, 384, [4, 5]),
                                             (700, 544, 385, [4, 5]), (700, 544, 512, [3]), (700, 544, 513, [3])])
 def test_fused_gemm_many_workgroups_and_largest_batches(B, M, K, batch, bits):
