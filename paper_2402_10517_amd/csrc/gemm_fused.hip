@@ -62,6 +62,7 @@ struct FusedArgs {
     uint16_t *y;
     float *partial; // parts > 1: [part][batch row][row]
     int M, K, batch, ntiles, parts;
+    int share, extra; // steps of a wave: share, one more for the first `extra` waves of a row block
 };
 
 // B bits, NJ tiles of 16 batch rows per workgroup, W waves (4 or 8).  blockIdx.y: part of the columns (the parts of a row
@@ -95,13 +96,16 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     const int blocks = (M + kRows - 1) / kRows;
     int rb, nt;
     const int part = blockIdx.y;
-    {
-        const int id = blockIdx.x, per = 8 * ntiles, full = blocks / 8 * per;
+    if (ntiles == 1) {
+        rb = blockIdx.x;
+        nt = 0;
+    } else {
+        const uint32_t id = blockIdx.x, per = 8 * (uint32_t)ntiles, full = (uint32_t)blocks / 8 * per;
         if (id < full) {
             rb = id / per * 8 + id % 8;
             nt = id % per / 8;
         } else {
-            const int rest = blocks % 8;
+            const uint32_t rest = (uint32_t)blocks % 8;
             rb = blocks / 8 * 8 + (id - full) % rest;
             nt = (id - full) / rest;
         }
@@ -112,7 +116,6 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
     const int chunks = K / kChunkSlots;
     const int lastspan = (chunks - 1) / kSpanLanes;
     const int ragged = chunks - lastspan * kSpanLanes;
-    const int nsteps = (chunks + kStepChunks - 1) / kStepChunks;
 
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, 0xffffffffu, kBufferRsrcWord3);
@@ -159,10 +162,12 @@ __global__ __launch_bounds__(64 * W, 2) void gemm_fused_kernel(FusedArgs a)
 #pragma unroll
         for (int r = 0; r < kRowsPerGroup; ++r) acc[j][r] = float4_t{0.f, 0.f, 0.f, 0.f};
 
-    // the waves split the row's steps evenly; a wave may get none (short rows)
-    const int slot = part * W + wave, slots = a.parts * W;
-    int st = (int)((long long)nsteps * slot / slots);
-    const int st1 = (int)((long long)nsteps * (slot + 1) / slots);
+    // the waves split the row's steps evenly (by the host's division: two 64-bit ones here were 0.3 us ahead of the first load); a
+    // wave may get none (short rows)
+    const int slot = part * W + wave;
+    int st = slot * a.share + (slot < a.extra ? slot : a.extra);
+    int st1 = st + a.share + (slot < a.extra ? 1 : 0);
+    asm("" : "+s"(st), "+s"(st1)); // opaque: as products of the arguments they cost the NJ = 4 loops up to 57 spilled registers
     const bool any = st < st1;
     // Unconditional (a wave without steps loads some step and drops it): past a branch the compiler cannot tell these loads from
     // the tables' and waits for all of them before the first table entry is written (4096 x 4096 b = 3..8 batch 17, 64: 1 to 4 %).
@@ -463,7 +468,8 @@ hipError_t launch_gemm_fused(const GemvArgs &g, hipStream_t stream)
 {
     if (!gemm_fused_ok(g)) return hipErrorInvalidValue;
     const FusedPlan p = fused_plan(g);
-    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, p.ntiles, fused_parts(p, g)};
+    const int parts = fused_parts(p, g), slots = parts * p.waves;
+    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, p.ntiles, parts, p.steps / slots, p.steps % slots};
     uint8_t *w = static_cast<uint8_t *>(g.work);
     switch (g.b) {
     case 3: return launch_fused_b<3>(a, p, w, stream);
