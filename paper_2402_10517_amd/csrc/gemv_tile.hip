@@ -80,12 +80,21 @@ template <int B> struct TileTable {
     }
 };
 
+// The waves split a row's pairs of octets evenly: wave w starts at npairs * w / nwaves.  The quotient comes from a product with
+// 2^32 / nwaves + 1 (exact: npairs < 2^23, nwaves <= 8); a 64-bit division took 300 scalar instructions, ahead of the first load.
+static inline uint32_t wave_reciprocal(int nwaves) { return nwaves > 1 ? 0xffffffffu / (uint32_t)nwaves + 1 : 0; }
+__device__ __forceinline__ int first_pair(int npairs, int w, uint32_t reciprocal)
+{
+    const uint32_t a = (uint32_t)npairs * (uint32_t)w;
+    return (int)(reciprocal ? __umulhi(a, reciprocal) : a);
+}
+
 // `wg` = index of the workgroup within its matrix (R tiles each).  RAG: K is not a multiple of 256 (the last octet holds fewer than 8
 // chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.
 template <int B, int R, int MAXT, bool RAG, bool WIDE>
 __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut,
                                                const uint16_t *__restrict__ x, uint16_t *__restrict__ y, int M, int K, int batch,
-                                               int wg)
+                                               int wg, uint32_t reciprocal)
 {
     using TT = TileTable<B>;
     constexpr int kTileRows = 16, kTileGroups = kTileRows / kRowsPerGroup;
@@ -289,10 +298,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 
     const int nocts = (chunks + 7) >> 3;
     const int npairs = (nocts + 1) >> 1;
-    const int p1 = (int)((long long)npairs * (wave + 1) / nwaves);
+    const int p1 = first_pair(npairs, wave + 1, reciprocal);
     u32x4 XA[kXSets][4], XB[kXSets][4];
     uint32_t QA[R][2][B], QB[R][2][B];
-    int p = (int)((long long)npairs * wave / nwaves); // < npairs (a wave without pairs loads one and drops it)
+    int p = first_pair(npairs, wave, reciprocal); // < npairs (a wave without pairs loads one and drops it)
     // ---- tables of the R tiles into LDS (rows past the matrix repeat the last row; never stored).
     // Thread (row = tid % 16, copy = (tid / 16) % 2, part = tid / 32) writes the entries of the pieces
     // part, part + nparts, ... of its row and copy: the 32 lanes of an LDS clock hit 32 different banks
@@ -473,35 +482,36 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 template <int B, int R, int MAXT, bool RAG, bool WIDE>
 __global__ __launch_bounds__(MAXT) void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
                                                          const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
-                                                         uint16_t *__restrict__ y, int M, int K, int batch)
+                                                         uint16_t *__restrict__ y, int M, int K, int batch, uint32_t reciprocal)
 {
-    gemv_tile_body<B, R, MAXT, RAG, WIDE>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x);
+    gemv_tile_body<B, R, MAXT, RAG, WIDE>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
 }
 
 // Several matrices of equal row length at one bit-width and batch in one launch (the projections of a
 // decoder layer that share their input): workgroup -> (matrix, tile) through the prefix sums of the
 // tile counts, which the launcher puts into group_begin.
 template <int B, int MAXT>
-__global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a)
+__global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint32_t reciprocal)
 {
     int m = 0;
 #pragma unroll
     for (int i = 1; i < kMaxMulti; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) m = i;
     gemv_tile_body<B, 1, MAXT, false, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
-                               (int)blockIdx.x - a.group_begin[m]);
+                               (int)blockIdx.x - a.group_begin[m], reciprocal);
 }
 
 // A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.
 template <int B, int MAXT>
-__global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int batch)
+__global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int batch, uint32_t reciprocal)
 {
     int it = 0;
 #pragma unroll
     for (int i = 1; i < kMaxListItems; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) it = i;
     const ListItem &I = a.item[it];
-    gemv_tile_body<B, 1, MAXT, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it]);
+    gemv_tile_body<B, 1, MAXT, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
+                                             reciprocal);
 }
 
 // Waves per workgroup of a single call that no option decides.  From 9270 calls (14 heights, 23 row lengths, every b, batch 3..8);
@@ -540,10 +550,10 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
     const dim3 grid((tiles + R - 1) / R), block(64 * nw);
     if (a.K % 256)
         hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, true, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
-                           a.y, a.M, a.K, a.batch);
+                           a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
     else
         hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, false, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
-                           a.y, a.M, a.K, a.batch);
+                           a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
     return hipGetLastError();
 }
 
@@ -573,7 +583,7 @@ template <int B> static hipError_t launch_tile_multi_b(MultiArgs &m, int total_t
     const int npairs = (m.K / (8 * kChunkSlots) + 1) / 2;
     int nw = m.K >= 12288 ? kMaxWaves : 4;
     if (nw > npairs) nw = npairs;
-    hipLaunchKernelGGL((gemv_tile_multi_kernel<B, 64 * kMaxWaves>), dim3(total_tiles), dim3(64 * nw), 0, stream, m);
+    hipLaunchKernelGGL((gemv_tile_multi_kernel<B, 64 * kMaxWaves>), dim3(total_tiles), dim3(64 * nw), 0, stream, m, wave_reciprocal(nw));
     return hipGetLastError();
 }
 
@@ -599,7 +609,7 @@ hipError_t launch_matrix_tile_multi(const MultiArgs &a, int b, hipStream_t strea
 
 template <int B> static hipError_t launch_tile_list_b(const ListArgs &a, int total_tiles, int nw, int batch, hipStream_t stream)
 {
-    hipLaunchKernelGGL((gemv_tile_list_kernel<B, 512>), dim3(total_tiles), dim3(64 * nw), 0, stream, a, batch);
+    hipLaunchKernelGGL((gemv_tile_list_kernel<B, 512>), dim3(total_tiles), dim3(64 * nw), 0, stream, a, batch, wave_reciprocal(nw));
     return hipGetLastError();
 }
 
