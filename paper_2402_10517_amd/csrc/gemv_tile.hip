@@ -390,38 +390,55 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
             }
         } else {
             constexpr int kPieces = (2 << B) / 16; // 16-byte pieces (8 entries) of a row's table
-            constexpr int kBurst = 4;              // pieces per thread in the first pass: all of them from 4 waves on
+            // b >= 7: a thread loads a piece once and writes it to both copies, two neighbours reading 32 contiguous bytes of a row and
+            // starting with different copies (32 lanes on 32 banks); the smaller tables give every copy threads of its own.
+            // 4096 x 4096 batch 8 b = 7/8 7.4/8.05 -> 7.0/7.6 us, 28672 x 8192 48.3/54.6 -> 47.3/53.5, 4096 x 1024 batch 6 4.55/5.3 ->
+            // 4.35/5.15.
+            constexpr bool kBoth = B >= 7;
+            constexpr int kBurst = kBoth ? 2 : 4; // pieces per thread in the first pass: all of them from 4 waves on
+            const int prow = kBoth ? (tid >> 1) & 15 : srow, pcopy = kBoth ? tid & 1 : scopy;
+            auto piece = [&](int j) { return kBoth ? 2 * (part + j * nparts) + (tid & 1) : part + j * nparts; };
             auto store_piece = [&](uint8_t *base, int pc, const u32x4 &v) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    *reinterpret_cast<uint16_t *>(base + (TT::byte_of(8 * pc + 2 * e) << TT::kShift)) = (uint16_t)v[e];
-                    *reinterpret_cast<uint16_t *>(base + (TT::byte_of(8 * pc + 2 * e + 1) << TT::kShift)) = (uint16_t)(v[e] >> 16);
-                }
+                for (int c = 0; c < (kBoth ? 2 : 1); ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        uint8_t *dst = base + ((pcopy ^ c) << 6);
+                        *reinterpret_cast<uint16_t *>(dst + (TT::byte_of(8 * pc + 2 * e) << TT::kShift)) = (uint16_t)v[e];
+                        *reinterpret_cast<uint16_t *>(dst + (TT::byte_of(8 * pc + 2 * e + 1) << TT::kShift)) = (uint16_t)(v[e] >> 16);
+                    }
             };
             const u32x4 *src[R];
             uint8_t *base[R];
             u32x4 v[R][kBurst];
 #pragma unroll
             for (int tile = 0; tile < R; ++tile) {
-                const int row = row0 + tile * kTileRows + srow < M ? row0 + tile * kTileRows + srow : M - 1;
+                const int row = row0 + tile * kTileRows + prow < M ? row0 + tile * kTileRows + prow : M - 1;
                 src[tile] = reinterpret_cast<const u32x4 *>(lut + ((size_t)row << B));
-                base[tile] = tab + tile * TT::kTileBytes + ((srow << 2) | (scopy << 6));
+                base[tile] = tab + tile * TT::kTileBytes + (prow << 2);
 #pragma unroll
                 for (int j = 0; j < kBurst; ++j) {
-                    const int pc = part + j * nparts;
+                    const int pc = piece(j);
                     v[tile][j] = src[tile][pc < kPieces ? pc : kPieces - 1];
                 }
             }
+            // The octet's loads wait for the tables (the statements use their registers): every CU's tables then arrive ahead of
+            // every slice instead of between them, and the stores below run while the slices are on their way.  4096 x 4096 batch 8
+            // b = 5/6/7 6.4/6.8/7.8 -> 6.2/6.6/7.35 us, 4099 x 2208 b = 7 batch 5 8.2 -> 7.7, 28672 x 8192 0.97 to 1.01.
+#pragma unroll
+            for (int tile = 0; tile < R; ++tile)
+#pragma unroll
+                for (int j = 0; j < kBurst; ++j) asm volatile("" : "+v"(v[tile][j]));
             issue(2 * p, true, XA, QA);
 #pragma unroll
             for (int tile = 0; tile < R; ++tile) {
 #pragma unroll
                 for (int j = 0; j < kBurst; ++j) {
-                    const int pc = part + j * nparts;
+                    const int pc = piece(j);
                     if (pc < kPieces) store_piece(base[tile], pc, v[tile][j]);
                 }
                 // workgroups of fewer than 4 waves (rows of less than 2048 columns) at b >= 7: the rest
-                for (int pc = part + kBurst * nparts; pc < kPieces; pc += nparts) store_piece(base[tile], pc, src[tile][pc]);
+                for (int j = kBurst; piece(j) < kPieces; ++j) store_piece(base[tile], piece(j), src[tile][piece(j)]);
             }
         }
     }

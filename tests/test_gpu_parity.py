@@ -665,6 +665,18 @@ def test_tile_kernel_on_ragged_rows_and_at_batch_nine_to_sixteen(B, batch):
     pm.close()
 
 
+# tables of 128 and 256 entries staged by workgroups of 1, 2 and 3 waves, in one tile per workgroup and in two (batch 16)
+@pytest.mark.parametrize("K", [512, 1024, 1504])
+@pytest.mark.parametrize("M,batch", [(4099, 5), (14355, 8), (14355, 16)])
+def test_tile_kernel_large_tables_from_few_waves(B, M, batch, K):
+    rows = np.unique(np.concatenate([np.arange(34), np.random.default_rng(K).integers(0, M, size=60), np.arange(M - 34, M)]))
+    idx, luts, x = inputs.make_case(50, M, K, batch=batch, sigma=0.01, bit_widths=[7, 8])
+    pm = B.ap_pack(idx, luts)
+    for b in (7, 8):
+        check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
 # two tiles per workgroup on ragged rows: at 3 bits on tall matrices, on long rows, and at batch 9 to 16
 @pytest.mark.parametrize("M,K,batch,bits", [(24580, 416, 8, [3]), (8180, 16384 + 32, 5, [4]), (15363, 800, 16, ALL_BITS),
                                             (8190, 288, 9, ALL_BITS)])
