@@ -79,6 +79,8 @@ def _load():
 
 
 lib = _load()
+if torch is not None:
+    from . import _torch_call   # ap_gemv and ap_gemm as native calls (csrc/torch_call.cpp); built with the library
 
 
 def strerror(status):
@@ -142,7 +144,7 @@ def ap_read_extent(M, K, n, mask, b):
 
 
 # The current stream's address without a Stream object around it: torch.cuda.current_stream() takes 2.7 us, a third of the host
-# time of a small call (ap_gemv on 512 x 512: 9.0 -> 6.6 us), this 0.2 us.
+# time of a small call, this 0.2 us.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if torch is not None else None
 
 
@@ -152,6 +154,11 @@ def _stream_ptr(stream):
             return _raw_stream(torch.cuda.current_device()), None
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream), stream
+
+
+def _address(pm):
+    h = pm.handle
+    return h.value if isinstance(h, ctypes.c_void_p) else h
 
 
 class PackedMatrix:
@@ -210,12 +217,9 @@ def ap_unpack(pm, stream=None):
 
 def ap_gemv(pm, b, x, y=None, stream=None):
     """x: (batch, K) float16 device tensor; returns y: (batch, M) float16 device tensor."""
-    assert x.dtype == torch.float16 and x.is_cuda and x.is_contiguous()
-    batch = 1 if x.dim() == 1 else x.shape[0]
-    if y is None:
-        y = torch.empty((batch, pm.M), dtype=torch.float16, device=x.device)
-    sp, _ = _stream_ptr(stream)
-    _check(lib.ap_gemv(pm.handle, int(b), x.data_ptr(), y.data_ptr(), batch, sp), "ap_gemv")
+    y = _torch_call.gemv(_address(pm), pm.M, int(b), x, y, None if stream is None else stream.cuda_stream)
+    if type(y) is int:
+        raise ApError(y, "ap_gemv")
     return y
 
 
@@ -284,17 +288,9 @@ def ap_dequantize(pm, b, w=None, stream=None):
 
 def ap_gemm(pm, b, x, work=None, y=None, stream=None):
     """x (batch, K) float16 -> y (batch, M) float16 for any batch; work = device memory of ap_gemm_workspace_size bytes."""
-    assert x.dtype == torch.float16 and x.is_cuda and x.is_contiguous() and x.dim() == 2
-    batch = x.shape[0]
-    size = ctypes.c_size_t(0)
-    _check(lib.ap_gemm_workspace_size(pm.handle, ctypes.byref(size)), "ap_gemm_workspace_size")
-    if work is None:
-        work = torch.empty(size.value, dtype=torch.uint8, device=x.device)
-    if y is None:
-        y = torch.empty((batch, pm.M), dtype=torch.float16, device=x.device)
-    sp, _ = _stream_ptr(stream)
-    _check(lib.ap_gemm(pm.handle, int(b), x.data_ptr(), y.data_ptr(), batch, work.data_ptr(),
-                       work.numel(), sp), "ap_gemm")
+    y = _torch_call.gemm(_address(pm), pm.M, int(b), x, work, y, None if stream is None else stream.cuda_stream)
+    if type(y) is int:
+        raise ApError(abs(y), "ap_gemm" if y > 0 else "ap_gemm_workspace_size")
     return y
 
 

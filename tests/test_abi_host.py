@@ -206,3 +206,14 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
                        capture_output=True, text=True)
     assert r.returncode != 0
     assert "ImportError" in r.stderr and "libapgemv.so is not built" in r.stderr
+
+
+def test_products_refuse_what_is_not_a_contiguous_half_tensor_on_the_gpu():
+    import torch
+    pm = B.PackedMatrix(None, None, 8, 32, 8, FULL_MASK)     # never reached: x is refused first
+    for call in (B.ap_gemv, B.ap_gemm):
+        for x in (torch.zeros(2, 32, dtype=torch.float16), torch.zeros(2, 32)):
+            with pytest.raises(AssertionError):
+                call(pm, 4, x)
+        with pytest.raises(TypeError):
+            call(pm, 4, np.zeros((2, 32), dtype=np.float16))

@@ -734,3 +734,42 @@ def test_infinite_centroid_in_the_last_octet(B, M, K, bits, batch):
             check_planted(y.cpu().numpy(), idx, luts[b], b, x, cells, rows)
         pm.close()
         pm2.close()
+
+
+def test_binding_outputs_streams_and_errors(B, tiny):
+    # a given y is filled and returned, a vector x gives one row, another stream is used when named and when current, and a
+    # refused call (missing bit-width, closed matrix, small workspace) raises the library's status
+    import torch
+    idx, luts, x = inputs.make_case(1, 512, 512, batch=3)
+    pm = B.ap_pack(idx, {4: luts[4]})
+    xd = torch.from_numpy(x).cuda()
+    expect = B.ap_gemv(pm, 4, xd)
+    assert expect.shape == (3, 512) and expect.dtype == torch.float16 and expect.device == xd.device
+    assert torch.equal(B.ap_gemv(pm, 4, xd[0]), B.ap_gemv(pm, 4, xd[:1]))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for call in (B.ap_gemv, B.ap_gemm):
+        y = torch.full((3, 512), -7.0, dtype=torch.float16, device="cuda")
+        assert call(pm, 4, xd, y=y) is y and torch.equal(y, expect)
+        y.fill_(-7.0)
+        side.wait_stream(torch.cuda.current_stream())
+        call(pm, 4, xd, y=y, stream=side)
+        side.synchronize()
+        assert torch.equal(y, expect)
+        with torch.cuda.stream(side):
+            y2 = call(pm, 4, xd)
+        side.synchronize()
+        assert torch.equal(y2, expect)
+        with pytest.raises(B.ApError) as e:
+            call(pm, 5, xd)
+        assert e.value.status == 3
+        with pytest.raises(AssertionError):
+            call(pm, 4, xd.t())
+    with pytest.raises(B.ApError) as e:
+        B.ap_gemm(pm, 4, xd, work=torch.empty(1024, dtype=torch.uint8, device="cuda"))
+    assert e.value.status == 5
+    pm.close()
+    for call in (B.ap_gemv, B.ap_gemm):
+        with pytest.raises(B.ApError) as e:
+            call(pm, 4, xd)
+        assert e.value.status == 1
