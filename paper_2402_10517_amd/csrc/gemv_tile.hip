@@ -90,8 +90,9 @@ __device__ __forceinline__ int first_pair(int npairs, int w, uint32_t reciprocal
 }
 
 // `wg` = index of the workgroup within its matrix (R tiles each).  RAG: K is not a multiple of 256 (the last octet holds fewer than 8
-// chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.
-template <int B, int R, int MAXT, bool RAG, bool WIDE>
+// chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.  SKIP: loads that are dropped ask for no
+// memory (launch_tile_r).
+template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
 __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut,
                                                const uint16_t *__restrict__ x, uint16_t *__restrict__ y, int M, int K, int batch,
                                                int wg, uint32_t reciprocal)
@@ -121,8 +122,6 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // the tile, chunk c ^ 2 p of the octet (16 lanes still read 64 contiguous bytes; the exchange of the
     // chunk pairs in the odd row groups keeps the lane exchange below free of bank conflicts)
     const int lp = lane >> 5, lc = ((lane >> 2) & 7) ^ (lp << 1), lr = lane & 3;
-    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, 0xffffffffu, kBufferRsrcWord3);
     uint32_t soff_lane[R][2];
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
@@ -182,6 +181,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 #pragma unroll
             for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl + q * 64), 0);
         }
+        // no records, no memory access (the addresses are valid all the same)
+        const uint32_t records = SKIP ? (uint32_t)__builtin_amdgcn_readfirstlane(real ? -1 : 0) : 0xffffffffu;
+        const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, records, kBufferRsrcWord3);
         const uint32_t soct = (uint32_t)o * 128u;
         const uint32_t back = RAG && lc >= left ? (uint32_t)(lc - (left - 1)) * 16u : 0u; // chunks that do not exist: the last one again
 #pragma unroll
@@ -453,7 +456,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         issue(o1, second, XB, QB);
         __builtin_amdgcn_sched_barrier(0); // keep the loads ahead of the arithmetic they overlap with
         compute(XA, QA, 2 * p);
-        issue(p + 1 < p1 ? 2 * p + 2 : 2 * p, true, XA, QA);
+        issue(p + 1 < p1 ? 2 * p + 2 : 2 * p, !SKIP || p + 1 < p1, XA, QA);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (RAG) {
             compute(XB, QB, 2 * p + 1); // the padding octet has no chunks: all centroids masked
@@ -496,12 +499,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 // workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
 // b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9, decoder layer b = 4 batch 4 33.0 / 32.6; 650 calls
 // on whole rows 1.000 to 1.010 by bit-width, 180 on ragged rows 1.000 to 1.036.
-template <int B, int R, int MAXT, bool RAG, bool WIDE>
+template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
 __global__ __launch_bounds__(MAXT) void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
                                                          const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
                                                          uint16_t *__restrict__ y, int M, int K, int batch, uint32_t reciprocal)
 {
-    gemv_tile_body<B, R, MAXT, RAG, WIDE>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
+    gemv_tile_body<B, R, MAXT, RAG, WIDE, SKIP>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
 }
 
 // Several matrices of equal row length at one bit-width and batch in one launch (the projections of a
@@ -514,7 +517,7 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint
 #pragma unroll
     for (int i = 1; i < kMaxMulti; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) m = i;
-    gemv_tile_body<B, 1, MAXT, false, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
+    gemv_tile_body<B, 1, MAXT, false, false, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
                                (int)blockIdx.x - a.group_begin[m], reciprocal);
 }
 
@@ -527,7 +530,7 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int ba
     for (int i = 1; i < kMaxListItems; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) it = i;
     const ListItem &I = a.item[it];
-    gemv_tile_body<B, 1, MAXT, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
+    gemv_tile_body<B, 1, MAXT, false, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
                                              reciprocal);
 }
 
@@ -565,12 +568,20 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
         nw = a.K >= 12288 ? kMaxWaves : 4; // (waves beyond the row's pairs add nothing to the sums)
     }
     const dim3 grid((tiles + R - 1) / R), block(64 * nw);
-    if (a.K % 256)
-        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, true, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
-                           a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
-    else
-        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, false, WIDE>), grid, block, 0, stream, a.slices, a.slice_bytes, a.lut, a.x,
-                           a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
+    auto launch = [&](auto ragged, auto skip) {
+        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, decltype(ragged)::value, WIDE, decltype(skip)::value>), grid, block, 0, stream,
+                           a.slices, a.slice_bytes, a.lut, a.x, a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
+    };
+    // The octet that the last pass of a wave requests and drops (with 4096 columns on 4 waves one of five) is left out where several
+    // workgroups share a CU, which then want the bandwidth; elsewhere the few scalar instructions ahead of the loads cost 0.05 us.
+    // With it / without, us: 11008x4096 b = 4 batch 16 15.3 / 14.8, b = 8 batch 16 22.0 / 21.1, b = 3 batch 8 9.0 / 8.8, 28672x8192 b = 5
+    // batch 16 56.9 / 55.1, b = 4 batch 8 40.6 / 40.1, 6144x4128 b = 5 batch 8 12.4 / 12.25; 4096x4096 b = 4 batch 8 5.53 / 5.63, 8192x512
+    // 4.57 / 4.63, 8192x1024 b = 3 batch 6 4.21 / 4.27.
+    const bool skip = grid.x > 256 && a.K > 2048;
+    const std::true_type yes;
+    const std::false_type no;
+    if (a.K % 256) skip ? launch(yes, yes) : launch(yes, no);
+    else skip ? launch(no, yes) : launch(no, no);
     return hipGetLastError();
 }
 

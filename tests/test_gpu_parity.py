@@ -677,6 +677,19 @@ def test_tile_kernel_large_tables_from_few_waves(B, M, batch, K):
     pm.close()
 
 
+# more workgroups than CUs on rows of more than 2048 columns, whose dropped loads are left out: an odd and an even number of octets, a
+# ragged row, and both sides of 256 workgroups, in sampled rows
+@pytest.mark.parametrize("K", [2304, 4096, 2080])
+@pytest.mark.parametrize("M,batch", [(4096, 8), (4099, 8), (4099, 16)])
+def test_tile_kernel_leaves_out_dropped_loads(B, M, batch, K):
+    rows = np.unique(np.concatenate([np.arange(18), np.random.default_rng(K).integers(0, M, size=40), np.arange(M - 18, M)]))
+    idx, luts, x = inputs.make_case(51, M, K, batch=batch, sigma=0.01)
+    pm = B.ap_pack(idx, luts)
+    for b in ALL_BITS:
+        check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
 # two tiles per workgroup on ragged rows: at 3 bits on tall matrices, on long rows, and at batch 9 to 16
 @pytest.mark.parametrize("M,K,batch,bits", [(24580, 416, 8, [3]), (8180, 16384 + 32, 5, [4]), (15363, 800, 16, ALL_BITS),
                                             (8190, 288, 9, ALL_BITS)])
