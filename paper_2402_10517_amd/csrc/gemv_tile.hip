@@ -495,8 +495,8 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     }
 }
 
-// No bound on the waves per SIMD: with at most 4 the b = 3, 4 instances of one tile take 107 registers instead of 74..80 and
-// workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
+// No bound on the waves per SIMD here and in the multi kernel: with at most 4 the b = 3, 4 instances of one tile take 107 registers
+// instead of 74..80 and workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
 // b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9, decoder layer b = 4 batch 4 33.0 / 32.6; 650 calls
 // on whole rows 1.000 to 1.010 by bit-width, 180 on ragged rows 1.000 to 1.036.
 template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
@@ -521,9 +521,12 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint
                                (int)blockIdx.x - a.group_begin[m], reciprocal);
 }
 
-// A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.
+// A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.  The bound asks for the registers
+// that the single instances take by themselves: without it these settle at 107 / 108 / 130 at b = 3 / 4 / 5 (4 / 4 / 3 waves per SIMD
+// instead of 6 / 6 / 5).  Without / with, us: b = 5 decoder layer batch 8 50.1 / 44.7, 3 of 8192 x 12288 batch 4 66.8 / 53.3, 32
+// matrices of 7B decoder layers batch 8 185.4 / 169.5; there b = 3 122.3 / 117.9, b = 4 148.9 / 144.0.
 template <int B, int MAXT>
-__global__ __launch_bounds__(MAXT) void gemv_tile_list_kernel(ListArgs a, int batch, uint32_t reciprocal)
+__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B <= 4 ? 6 : B <= 6 ? 5 : 4))) void gemv_tile_list_kernel(ListArgs a, int batch, uint32_t reciprocal)
 {
     int it = 0;
 #pragma unroll
