@@ -161,6 +161,16 @@ def _address(pm):
     return h.value if isinstance(h, ctypes.c_void_p) else h
 
 
+def _empty(shape, dtype, device, stream):
+    """Device memory that work on `stream` (None = the current one) writes; of a named stream's own order (csrc/torch_call.cpp)."""
+    device = torch.device(device)
+    if stream is None or device.type != "cuda":
+        return torch.empty(shape, dtype=dtype, device=device)
+    index = device.index
+    return _torch_call.empty(tuple(shape), int(dtype == torch.float16), torch.cuda.current_device() if index is None else index,
+                             stream.cuda_stream)
+
+
 class PackedMatrix:
     """Owns the torch device buffer and the library handle of one packed matrix."""
 
@@ -199,7 +209,7 @@ def ap_pack(idx, luts, n=8, device="cuda:0", stream=None):
     M, K = idx.shape
     mask = lut_mask(luts.keys())
     size = ap_packed_size(M, K, n, mask)
-    buf = torch.empty(size, dtype=torch.uint8, device=device)
+    buf = _empty((size,), torch.uint8, device, stream)
     arr, keep = _lut_array(luts)
     h = ctypes.c_void_p()
     sp, _ = _stream_ptr(stream)
@@ -216,7 +226,9 @@ def ap_unpack(pm, stream=None):
 
 
 def ap_gemv(pm, b, x, y=None, stream=None):
-    """x: (batch, K) float16 device tensor; returns y: (batch, M) float16 device tensor."""
+    """x: (batch, K) float16 device tensor; returns y: (batch, M) float16 device tensor.
+
+    With `stream` the product runs there: what is on the current stream (x, a given y) is the caller's to order against it."""
     y = _torch_call.gemv(_address(pm), pm.M, int(b), x, y, None if stream is None else stream.cuda_stream)
     if type(y) is int:
         raise ApError(y, "ap_gemv")
@@ -280,14 +292,16 @@ def ap_gemv_multi(triples, b, stream=None):
 def ap_dequantize(pm, b, w=None, stream=None):
     """Dense (M, K) float16 device tensor of the b-bit model's weights."""
     if w is None:
-        w = torch.empty((pm.M, pm.K), dtype=torch.float16, device=pm.buf.device)
+        w = _empty((pm.M, pm.K), torch.float16, pm.buf.device, stream)
     sp, _ = _stream_ptr(stream)
     _check(lib.ap_dequantize(pm.handle, int(b), w.data_ptr(), sp), "ap_dequantize")
     return w
 
 
 def ap_gemm(pm, b, x, work=None, y=None, stream=None):
-    """x (batch, K) float16 -> y (batch, M) float16 for any batch; work = device memory of ap_gemm_workspace_size bytes."""
+    """x (batch, K) float16 -> y (batch, M) float16 for any batch; work = device memory of ap_gemm_workspace_size bytes.
+
+    `stream` as in ap_gemv; a given work is in use until that stream is done with the call."""
     y = _torch_call.gemm(_address(pm), pm.M, int(b), x, work, y, None if stream is None else stream.cuda_stream)
     if type(y) is int:
         raise ApError(abs(y), "ap_gemm" if y > 0 else "ap_gemm_workspace_size")

@@ -5,8 +5,10 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <ATen/ops/empty.h>
-#include <c10/hip/HIPStream.h>
+
+#include <vector>
 
 #include "../../include/apgemv.h"
 
@@ -29,10 +31,17 @@ bool address_of(PyObject *o, void **out)
     return !PyErr_Occurred();
 }
 
-bool stream_of(PyObject *o, void **out)
+// The stream of a call: a named one, or (None) the current one
+struct CallStream {
+    void *address;
+    bool named;
+};
+
+bool stream_of(PyObject *o, CallStream *out)
 {
-    if (o != Py_None) return address_of(o, out);
-    *out = c10::hip::getCurrentHIPStream().stream();
+    out->named = o != Py_None;
+    if (out->named) return address_of(o, &out->address);
+    out->address = c10::hip::getCurrentHIPStream().stream();
     return true;
 }
 
@@ -43,9 +52,43 @@ bool activations_ok(const at::Tensor &x)
     return false;
 }
 
-at::Tensor output_like(const at::Tensor &x, int64_t batch, int64_t M)
+// Memory that work on the call's stream writes.  The caching allocator hands a block out in the order of the stream that is current,
+// and again as soon as it is released there.  For a named stream it is therefore asked in that stream's order: from the current
+// stream's blocks, work still queued there could use a block that the call overwrites, or be given one that the call still
+// uses.  A tensor that is returned is read by the caller on the current stream, so its release waits for that one too.
+at::Tensor allocate(at::IntArrayRef sizes, at::ScalarType type, at::Device device, const CallStream &stream, bool returned)
 {
-    return at::empty({batch, M}, at::TensorOptions().dtype(at::kHalf).device(x.device()));
+    const auto options = at::TensorOptions().dtype(type).device(device);
+    if (!stream.named) return at::empty(sizes, options);
+    const auto current = c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(device.index());
+    if (current.stream() == stream.address) return at::empty(sizes, options);
+    struct Restore {
+        decltype(current) &stream;
+        ~Restore() { c10::hip::setCurrentHIPStreamMasqueradingAsCUDA(stream); }
+    } restore{current};
+    c10::hip::setCurrentHIPStreamMasqueradingAsCUDA(
+        stream.address ? c10::hip::getStreamFromExternalMasqueradingAsCUDA(static_cast<hipStream_t>(stream.address), current.device_index())
+                       : c10::hip::getDefaultHIPStreamMasqueradingAsCUDA(current.device_index()));
+    at::Tensor t = at::empty(sizes, options);
+    if (returned) t.record_stream(current.unwrap());
+    return t;
+}
+
+// empty(sizes, half, device index, stream) -> a float16 (half != 0) or uint8 tensor that work on the named stream writes
+PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    if (n != 4 || !PyTuple_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError, "empty takes 4 arguments, a tuple first");
+        return nullptr;
+    }
+    std::vector<int64_t> sizes;
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(args[0]); ++i) sizes.push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(args[0], i)));
+    const long half = PyLong_AsLong(args[1]), device = PyLong_AsLong(args[2]);
+    CallStream stream;
+    if (PyErr_Occurred() || !stream_of(args[3], &stream)) return nullptr;
+    return THPVariable_Wrap(allocate(sizes, half ? at::kHalf : at::kByte, at::Device(at::kCUDA, (at::DeviceIndex)device), stream, true));
+    END_HANDLE_TH_ERRORS
 }
 
 // gemv(handle, M, b, x, y, stream) -> y, or the status of a failed call
@@ -56,7 +99,8 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n)
         PyErr_SetString(PyExc_TypeError, "gemv takes 6 arguments");
         return nullptr;
     }
-    void *handle, *stream;
+    void *handle;
+    CallStream stream;
     const long M = PyLong_AsLong(args[1]), b = PyLong_AsLong(args[2]);
     if (PyErr_Occurred() || !address_of(args[0], &handle)) return nullptr;
     const at::Tensor *x = tensor_of(args[3], "x");
@@ -64,13 +108,13 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n)
     const int64_t batch = x->dim() == 1 ? 1 : x->size(0);
     const at::Tensor *given = args[4] == Py_None ? nullptr : tensor_of(args[4], "y");
     if (PyErr_Occurred()) return nullptr;
-    const at::Tensor y = given ? *given : output_like(*x, batch, M);
     if (!stream_of(args[5], &stream)) return nullptr;
+    const at::Tensor y = given ? *given : allocate({batch, M}, at::kHalf, x->device(), stream, true);
     const void *xp = x->data_ptr();
     void *yp = y.data_ptr();
     ap_status status;
     Py_BEGIN_ALLOW_THREADS
-    status = ap_gemv(static_cast<const ap_matrix *>(handle), (int)b, xp, yp, (int)batch, stream);
+    status = ap_gemv(static_cast<const ap_matrix *>(handle), (int)b, xp, yp, (int)batch, stream.address);
     Py_END_ALLOW_THREADS
     if (status != AP_OK) return PyLong_FromLong(status);
     if (given) {
@@ -89,7 +133,8 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
         PyErr_SetString(PyExc_TypeError, "gemm takes 7 arguments");
         return nullptr;
     }
-    void *handle, *stream;
+    void *handle;
+    CallStream stream;
     const long M = PyLong_AsLong(args[1]), b = PyLong_AsLong(args[2]);
     if (PyErr_Occurred() || !address_of(args[0], &handle)) return nullptr;
     const at::Tensor *x = tensor_of(args[3], "x");
@@ -105,15 +150,14 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
     const at::Tensor *given = args[5] == Py_None ? nullptr : tensor_of(args[5], "y");
     if (PyErr_Occurred()) return nullptr;
     const int64_t batch = x->size(0);
-    const at::Tensor work = given_work ? *given_work
-                                       : at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(x->device()));
-    const at::Tensor y = given ? *given : output_like(*x, batch, M);
     if (!stream_of(args[6], &stream)) return nullptr;
+    const at::Tensor work = given_work ? *given_work : allocate({(int64_t)bytes}, at::kByte, x->device(), stream, false);
+    const at::Tensor y = given ? *given : allocate({batch, M}, at::kHalf, x->device(), stream, true);
     const void *xp = x->data_ptr();
     void *yp = y.data_ptr(), *wp = work.data_ptr();
     const size_t work_bytes = (size_t)work.numel();
     Py_BEGIN_ALLOW_THREADS
-    status = ap_gemm(static_cast<const ap_matrix *>(handle), (int)b, xp, yp, (int)batch, wp, work_bytes, stream);
+    status = ap_gemm(static_cast<const ap_matrix *>(handle), (int)b, xp, yp, (int)batch, wp, work_bytes, stream.address);
     Py_END_ALLOW_THREADS
     if (status != AP_OK) return PyLong_FromLong(status);
     if (given) {
@@ -126,6 +170,7 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
 
 PyMethodDef methods[] = {
     {"gemv", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(gemv)), METH_FASTCALL, nullptr},
+    {"empty", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(empty)), METH_FASTCALL, nullptr},
     {"gemm", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(gemm)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -786,3 +786,64 @@ def test_binding_outputs_streams_and_errors(B, tiny):
         with pytest.raises(B.ApError) as e:
             call(pm, 4, xd)
         assert e.value.status == 1
+
+
+def _pool_stream(address):
+    """The stream whose blocks of the caching allocator hold this address."""
+    import torch
+    for s in torch.cuda.memory_snapshot():
+        if s["address"] <= address < s["address"] + s["total_size"]:
+            return s["stream"]
+    raise AssertionError("not the allocator's memory")
+
+
+def test_memory_of_a_call_on_a_named_stream_is_that_streams(B):
+    # what the binding allocates for a call on a stream that is not current comes from that stream's blocks (so work queued on the
+    # current stream neither uses nor gets them meanwhile), and a returned tensor's block also waits for the current stream
+    import torch
+    M, K, batch = 2048 + 16, 2048, 40
+    idx, luts, x = inputs.make_case(52, M, K, batch=batch)
+    pm = B.ap_pack(idx, {4: luts[4]})
+    xd = torch.from_numpy(x).cuda()
+    x3 = xd[:3].contiguous()
+    side = torch.cuda.Stream()
+    here = torch.cuda.current_stream().cuda_stream
+    expect = [B.ap_gemm(pm, 4, xd), B.ap_gemv(pm, 4, x3), B.ap_dequantize(pm, 4)]
+    assert all(_pool_stream(t.data_ptr()) == here for t in expect)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    for call, want in zip((lambda: B.ap_gemm(pm, 4, xd, stream=side), lambda: B.ap_gemv(pm, 4, x3, stream=side),
+                           lambda: B.ap_dequantize(pm, 4, stream=side)), expect):
+        out = call()
+        assert _pool_stream(out.data_ptr()) == side.cuda_stream and torch.cuda.current_stream().cuda_stream == here
+        # blocks of the sizes of work and out, overwritten on the current stream while the call may still run
+        for n in (M * K * 2, out.numel() * 2):
+            torch.empty(n, dtype=torch.uint8, device="cuda").fill_(0xff)
+        side.synchronize()
+        assert torch.equal(out, want)
+        # the current stream still has work ahead of its use of out when out is released
+        address, shape = out.data_ptr(), out.shape
+        torch.cuda._sleep(20_000_000)
+        kept = out.clone()
+        del out
+        with torch.cuda.stream(side):
+            again = torch.empty(shape, dtype=torch.float16, device="cuda")
+            assert again.data_ptr() != address
+            again.fill_(-7.0)
+        torch.cuda.synchronize()
+        assert torch.equal(kept, want)
+    # the workspace, released when ap_gemm returned, is among the named stream's blocks
+    assert any(s["stream"] == side.cuda_stream and s["total_size"] >= M * K * 2 for s in torch.cuda.memory_snapshot())
+    pm2 = B.ap_pack(idx, {4: luts[4]}, stream=side)
+    assert _pool_stream(pm2.buf.data_ptr()) == side.cuda_stream
+    assert torch.equal(B.ap_gemv(pm2, 4, x3), expect[1])
+    # named and current the same stream, and a named default stream beside another current one
+    with torch.cuda.stream(side):
+        out = B.ap_gemv(pm, 4, x3, stream=side)
+        assert _pool_stream(out.data_ptr()) == side.cuda_stream
+        out2 = B.ap_gemv(pm, 4, x3, stream=torch.cuda.default_stream())
+        assert _pool_stream(out2.data_ptr()) == here
+    torch.cuda.synchronize()
+    assert torch.equal(out, expect[1]) and torch.equal(out2, expect[1])
+    pm.close()
+    pm2.close()
