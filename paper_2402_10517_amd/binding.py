@@ -229,7 +229,7 @@ def ap_gemv(pm, b, x, y=None, stream=None):
     """x: (batch, K) float16 device tensor; returns y: (batch, M) float16 device tensor.
 
     With `stream` the product runs there: what is on the current stream (x, a given y) is the caller's to order against it."""
-    y = _torch_call.gemv(_address(pm), pm.M, int(b), x, y, None if stream is None else stream.cuda_stream)
+    y = _torch_call.gemv(_address(pm), pm.M, pm.K, int(b), x, y, None if stream is None else stream.cuda_stream)
     if type(y) is int:
         raise ApError(y, "ap_gemv")
     return y
@@ -302,7 +302,7 @@ def ap_gemm(pm, b, x, work=None, y=None, stream=None):
     """x (batch, K) float16 -> y (batch, M) float16 for any batch; work = device memory of ap_gemm_workspace_size bytes.
 
     `stream` as in ap_gemv; a given work is in use until that stream is done with the call."""
-    y = _torch_call.gemm(_address(pm), pm.M, int(b), x, work, y, None if stream is None else stream.cuda_stream)
+    y = _torch_call.gemm(_address(pm), pm.M, pm.K, int(b), x, work, y, None if stream is None else stream.cuda_stream)
     if type(y) is int:
         raise ApError(abs(y), "ap_gemm" if y > 0 else "ap_gemm_workspace_size")
     return y

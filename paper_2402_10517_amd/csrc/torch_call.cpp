@@ -8,6 +8,7 @@
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 #include <ATen/ops/empty.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "../../include/apgemv.h"
@@ -45,10 +46,29 @@ bool stream_of(PyObject *o, CallStream *out)
     return true;
 }
 
-bool activations_ok(const at::Tensor &x)
+// x: `batch` rows of K activations or more
+bool activations_ok(const at::Tensor &x, int64_t K)
 {
-    if (x.scalar_type() == at::kHalf && x.is_cuda() && x.is_contiguous()) return true;
-    PyErr_SetString(PyExc_AssertionError, "x must be a contiguous float16 tensor on the GPU");
+    if (x.scalar_type() != at::kHalf || !x.is_cuda() || !x.is_contiguous()) {
+        PyErr_SetString(PyExc_AssertionError, "x must be a contiguous float16 tensor on the GPU");
+        return false;
+    }
+    if (x.numel() >= (x.dim() < 2 ? 1 : x.size(0)) * K) return true;
+    PyErr_SetString(PyExc_AssertionError, "x holds fewer than K values per row");
+    return false;
+}
+
+// Bytes of a given tensor's memory from its first element on; 0 for memory that the GPU cannot write
+int64_t room(const at::Tensor &t)
+{
+    if (!t.is_cuda() && !t.is_pinned()) return 0;
+    return (int64_t)t.storage().nbytes() - t.storage_offset() * (int64_t)t.element_size();
+}
+
+bool output_ok(const at::Tensor &y, int64_t batch, int64_t M)
+{
+    if (room(y) >= batch * M * 2) return true;
+    PyErr_SetString(PyExc_AssertionError, "y must hold batch x M float16 values on the GPU");
     return false;
 }
 
@@ -91,24 +111,24 @@ PyObject *empty(PyObject *, PyObject *const *args, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// gemv(handle, M, b, x, y, stream) -> y, or the status of a failed call
+// gemv(handle, M, K, b, x, y, stream) -> y, or the status of a failed call
 PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 6) {
-        PyErr_SetString(PyExc_TypeError, "gemv takes 6 arguments");
+    if (n != 7) {
+        PyErr_SetString(PyExc_TypeError, "gemv takes 7 arguments");
         return nullptr;
     }
     void *handle;
     CallStream stream;
-    const long M = PyLong_AsLong(args[1]), b = PyLong_AsLong(args[2]);
+    const long M = PyLong_AsLong(args[1]), K = PyLong_AsLong(args[2]), b = PyLong_AsLong(args[3]);
     if (PyErr_Occurred() || !address_of(args[0], &handle)) return nullptr;
-    const at::Tensor *x = tensor_of(args[3], "x");
-    if (!x || !activations_ok(*x)) return nullptr;
+    const at::Tensor *x = tensor_of(args[4], "x");
+    if (!x || !activations_ok(*x, K)) return nullptr;
     const int64_t batch = x->dim() == 1 ? 1 : x->size(0);
-    const at::Tensor *given = args[4] == Py_None ? nullptr : tensor_of(args[4], "y");
-    if (PyErr_Occurred()) return nullptr;
-    if (!stream_of(args[5], &stream)) return nullptr;
+    const at::Tensor *given = args[5] == Py_None ? nullptr : tensor_of(args[5], "y");
+    if (PyErr_Occurred() || (given && !output_ok(*given, batch, M))) return nullptr;
+    if (!stream_of(args[6], &stream)) return nullptr;
     const at::Tensor y = given ? *given : allocate({batch, M}, at::kHalf, x->device(), stream, true);
     const void *xp = x->data_ptr();
     void *yp = y.data_ptr();
@@ -118,27 +138,27 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n)
     Py_END_ALLOW_THREADS
     if (status != AP_OK) return PyLong_FromLong(status);
     if (given) {
-        Py_INCREF(args[4]);
-        return args[4];
+        Py_INCREF(args[5]);
+        return args[5];
     }
     return THPVariable_Wrap(y);
     END_HANDLE_TH_ERRORS
 }
 
-// gemm(handle, M, b, x, work, y, stream) -> y, or the status of a failed call (negative: of ap_gemm_workspace_size)
+// gemm(handle, M, K, b, x, work, y, stream) -> y, or the status of a failed call (negative: of ap_gemm_workspace_size)
 PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 7) {
-        PyErr_SetString(PyExc_TypeError, "gemm takes 7 arguments");
+    if (n != 8) {
+        PyErr_SetString(PyExc_TypeError, "gemm takes 8 arguments");
         return nullptr;
     }
     void *handle;
     CallStream stream;
-    const long M = PyLong_AsLong(args[1]), b = PyLong_AsLong(args[2]);
+    const long M = PyLong_AsLong(args[1]), K = PyLong_AsLong(args[2]), b = PyLong_AsLong(args[3]);
     if (PyErr_Occurred() || !address_of(args[0], &handle)) return nullptr;
-    const at::Tensor *x = tensor_of(args[3], "x");
-    if (!x || !activations_ok(*x)) return nullptr;
+    const at::Tensor *x = tensor_of(args[4], "x");
+    if (!x || !activations_ok(*x, K)) return nullptr;
     if (x->dim() != 2) {
         PyErr_SetString(PyExc_AssertionError, "x must have two dimensions");
         return nullptr;
@@ -146,23 +166,23 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n)
     size_t bytes = 0;
     ap_status status = ap_gemm_workspace_size(static_cast<const ap_matrix *>(handle), &bytes);
     if (status != AP_OK) return PyLong_FromLong(-(long)status);
-    const at::Tensor *given_work = args[4] == Py_None ? nullptr : tensor_of(args[4], "work");
-    const at::Tensor *given = args[5] == Py_None ? nullptr : tensor_of(args[5], "y");
-    if (PyErr_Occurred()) return nullptr;
+    const at::Tensor *given_work = args[5] == Py_None ? nullptr : tensor_of(args[5], "work");
+    const at::Tensor *given = args[6] == Py_None ? nullptr : tensor_of(args[6], "y");
     const int64_t batch = x->size(0);
-    if (!stream_of(args[6], &stream)) return nullptr;
+    if (PyErr_Occurred() || (given && !output_ok(*given, batch, M))) return nullptr;
+    if (!stream_of(args[7], &stream)) return nullptr;
     const at::Tensor work = given_work ? *given_work : allocate({(int64_t)bytes}, at::kByte, x->device(), stream, false);
     const at::Tensor y = given ? *given : allocate({batch, M}, at::kHalf, x->device(), stream, true);
     const void *xp = x->data_ptr();
     void *yp = y.data_ptr(), *wp = work.data_ptr();
-    const size_t work_bytes = (size_t)work.numel();
+    const size_t work_bytes = (size_t)(given_work ? std::min(work.numel(), room(work)) : work.numel());
     Py_BEGIN_ALLOW_THREADS
     status = ap_gemm(static_cast<const ap_matrix *>(handle), (int)b, xp, yp, (int)batch, wp, work_bytes, stream.address);
     Py_END_ALLOW_THREADS
     if (status != AP_OK) return PyLong_FromLong(status);
     if (given) {
-        Py_INCREF(args[5]);
-        return args[5];
+        Py_INCREF(args[6]);
+        return args[6];
     }
     return THPVariable_Wrap(y);
     END_HANDLE_TH_ERRORS

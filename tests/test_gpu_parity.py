@@ -847,3 +847,44 @@ def test_memory_of_a_call_on_a_named_stream_is_that_streams(B):
     assert torch.equal(out, expect[1]) and torch.equal(out2, expect[1])
     pm.close()
     pm2.close()
+
+
+def test_products_refuse_tensors_that_are_too_small(B, tiny):
+    # the binding refuses, before any launch, what a kernel would read or write past its end; what holds enough is taken as before:
+    # a longer vector x, a y of another type or shape or in pinned host memory, a y in the middle of a larger tensor
+    import torch
+    M, K, batch = 512, 512, 3
+    idx, luts, x = inputs.make_case(1, M, K, batch=batch)
+    pm = B.ap_pack(idx, {4: luts[4]})
+    xd = torch.from_numpy(x).cuda()
+    expect = B.ap_gemv(pm, 4, xd)
+    for call in (B.ap_gemv, B.ap_gemm):
+        for bad in (xd[:, :K - 32].contiguous(), torch.empty((batch, 0), dtype=torch.float16, device="cuda")):
+            with pytest.raises(AssertionError):
+                call(pm, 4, bad)
+        base = torch.zeros((batch + 1) * M, dtype=torch.float16, device="cuda")
+        for bad in (base[:batch * M - 1].clone(), base[M + 1:], torch.zeros((batch, M), dtype=torch.float16),
+                    torch.zeros(batch * M, dtype=torch.uint8, device="cuda"), torch.zeros((batch, 0), dtype=torch.float16, device="cuda")):
+            with pytest.raises(AssertionError):
+                call(pm, 4, xd, y=bad)
+        torch.cuda.synchronize()
+        assert not base.any()
+        call(pm, 4, xd, y=base[M:])
+        assert torch.equal(base[M:].view(batch, M), expect) and not base[:M].any()
+        ints = torch.zeros((M, batch), dtype=torch.int16, device="cuda")
+        call(pm, 4, xd, y=ints)
+        assert torch.equal(ints.view(torch.float16).view(batch, M), expect)
+        pinned = torch.zeros((batch, M), dtype=torch.float16, pin_memory=True)
+        call(pm, 4, xd, y=pinned)
+        torch.cuda.synchronize()
+        assert torch.equal(pinned, expect.cpu())
+    with pytest.raises(AssertionError):
+        B.ap_gemv(pm, 4, xd[0, :K - 1].clone())
+    assert torch.equal(B.ap_gemv(pm, 4, xd.view(-1)), expect[:1])
+    # a workspace that says it is larger than its memory
+    work = torch.zeros(1, dtype=torch.uint8, device="cuda").expand(M * K * 2)
+    for w in (work, torch.zeros(M * K * 2, dtype=torch.uint8)):
+        with pytest.raises(B.ApError) as e:
+            B.ap_gemm(pm, 4, xd, work=w)
+        assert e.value.status == 5
+    pm.close()
