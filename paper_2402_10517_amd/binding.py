@@ -1,7 +1,8 @@
-"""Thin ctypes binding over the C-ABI library (include/apgemv.h): argument marshalling only.
+"""Thin binding over the C-ABI library (include/apgemv.h): argument marshalling only, through ctypes, and for the calls that run
+once per product (ap_gemv, ap_gemm) through native functions (csrc/torch_call.cpp).
 
 PyTorch is used for device memory and streams; every step of the path runs in the HIP library.
-If the library has not been built the import of this module fails loudly - there is no fallback.
+If either has not been built the import of this module fails loudly - there is no fallback.
 """
 import ctypes
 import os
@@ -79,8 +80,12 @@ def _load():
 
 
 lib = _load()
-if torch is not None:
-    from . import _torch_call   # ap_gemv and ap_gemm as native calls (csrc/torch_call.cpp); built with the library
+if torch is not None:   # ap_gemv and ap_gemm as native calls (csrc/torch_call.cpp); built with the library
+    try:
+        from . import _torch_call
+    except ImportError as e:
+        raise ImportError("_torch_call.so is not built, or not for this torch: run `python -m paper_2402_10517_amd.build` "
+                          "or __graft_entry__.build()") from e
 
 
 def strerror(status):

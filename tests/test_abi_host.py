@@ -206,6 +206,12 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
                        capture_output=True, text=True)
     assert r.returncode != 0
     assert "ImportError" in r.stderr and "libapgemv.so is not built" in r.stderr
+    # nor without the native calls; the message says what to run
+    shutil.copy(B.LIB_PATH, dst / "libapgemv.so")
+    r = subprocess.run([sys.executable, "-c", "import paper_2402_10517_amd.binding"], cwd=tmp_path,
+                       capture_output=True, text=True)
+    assert r.returncode != 0
+    assert "ImportError" in r.stderr and "_torch_call.so is not built" in r.stderr and "paper_2402_10517_amd.build" in r.stderr
 
 
 def test_products_refuse_what_is_not_a_contiguous_half_tensor_on_the_gpu():
