@@ -420,7 +420,7 @@ static bool gemm_fused_pays(const GemvArgs &a)
     if (a.b == 8 && M >= 12288 && K <= 1024) most = M >= 20480 ? 128 : 192;
     if (a.b == 8 && M >= 24576 && K > 1024 && K <= 2048) most = 192;
     if (a.batch > most) return false;
-    const int wanted = fused_parts_wanted(p), parts = fused_parts(p, a);
+    const int wanted = fused_parts_wanted(p), parts = p.parts;
     if (parts < wanted && ((4 * parts <= wanted && K <= 16384) || (a.b > 3 && parts == 1))) return false;
     if (p.nj == 4 && a.b >= 7 && M <= 768 && K > 1024 && K <= (a.b == 8 ? 4096 : 1536)) return false;
     if (p.nj == 4 && K < 512 && M <= (a.b == 8 ? 2048 : 1024) && (a.b >= 7 || (a.b >= 4 && a.batch > 128)))

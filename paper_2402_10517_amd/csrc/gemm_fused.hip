@@ -468,8 +468,8 @@ hipError_t launch_gemm_fused(const GemvArgs &g, hipStream_t stream)
 {
     if (!gemm_fused_ok(g)) return hipErrorInvalidValue;
     const FusedPlan p = fused_plan(g);
-    const int parts = fused_parts(p, g), slots = parts * p.waves;
-    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, p.ntiles, parts, p.steps / slots, p.steps % slots};
+    const int slots = p.parts * p.waves;
+    FusedArgs a = {g.slices, g.slice_bytes, g.lut, g.x, g.y, nullptr, g.M, g.K, g.batch, p.ntiles, p.parts, p.steps / slots, p.steps % slots};
     uint8_t *w = static_cast<uint8_t *>(g.work);
     switch (g.b) {
     case 3: return launch_fused_b<3>(a, p, w, stream);

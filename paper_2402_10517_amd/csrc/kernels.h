@@ -30,9 +30,10 @@ struct GemvArgs {
 
 // The fused large-batch kernel (gemm_fused.hip) takes a product straight from the packed form.
 // How it divides a product: `ntiles` tiles of up to 64 batch rows, evenly filled with `nj` times 16 rows; blocks of 64 rows;
-// `waves` per workgroup; `copy_bytes` of the scratch hold a copy of x in fragment order (none if 0).
+// `waves` per workgroup; `parts` of the columns, which the scratch has room for the partial sums of; `copy_bytes` of the scratch
+// hold a copy of x in fragment order (none if 0).
 struct FusedPlan {
-    int ntiles, nj, blocks, waves, steps;
+    int ntiles, nj, blocks, waves, steps, parts;
     size_t copy_bytes;
 };
 // Column parts (workgroups that share a row block's columns): as many as give every CU one workgroup, a step or more per wave.
@@ -55,22 +56,21 @@ inline FusedPlan fused_plan(const GemvArgs &a)
     // 65 -> 59 us with 4, 11008 x 4096 b = 4 batch 32 17.3 -> 20.3.
     p.waves = (long long)p.blocks * p.ntiles <= 256 ? 8 : 4;
     p.steps = (a.K / 32 + 3) / 4;
+    const int wanted = fused_parts_wanted(p);
+    const auto parts_in = [&](size_t bytes) { // as many of them as fit
+        const size_t room = bytes / ((size_t)a.batch * a.M * 4);
+        return room >= (size_t)wanted ? wanted : room > 1 ? (int)room : 1;
+    };
+    p.parts = parts_in(a.work_bytes);
     // With 64 batch rows per workgroup the copy of x pays from the third step of a wave on (at 8 bits, whose instance with the exchange
     // spills in its loop, from the second): it is a launch of 2 to 3 us, the exchange 0.1 us per step.  With the copy / without,
     // us: 1 step 4096 x 4096 batch 64 b = 3 13.9 / 12.3, b = 8 16.3 / 15.0, 1024 x 1024 b = 5 batch 300 10.1 / 7.9; 2 steps 8192 x 4096
     // batch 64 b = 3 16.4 / 15.7, b = 5 18.7 / 18.5, b = 8 22.3 / 26.0; 4 steps 8192 x 8192 b = 5 24.8 / 24.8, 11008 x 4096 b = 8
-    // 25.6 / 29.6.
-    const int slots = p.waves * fused_parts_wanted(p);
-    const bool copy = p.nj >= 4 && p.steps > (a.b == 8 ? 1 : 2) * slots;
+    // 25.6 / 29.6.  The steps are those of the parts that fit, not of the wanted ones.
+    const bool copy = p.nj >= 4 && p.steps > (a.b == 8 ? 1 : 2) * p.waves * p.parts;
     p.copy_bytes = copy ? (size_t)p.steps * 4 * p.ntiles * p.nj * 1024 : 0;
+    if (copy) p.parts = a.work_bytes > p.copy_bytes ? parts_in(a.work_bytes - p.copy_bytes) : 1;
     return p;
-}
-// As many of them as the scratch has room for partial sums of (besides the copy of x).
-inline int fused_parts(const FusedPlan &p, const GemvArgs &a)
-{
-    const int wanted = fused_parts_wanted(p);
-    const size_t room = (a.work_bytes - p.copy_bytes) / ((size_t)a.batch * a.M * 4);
-    return room >= (size_t)wanted ? wanted : room > 1 ? (int)room : 1;
 }
 // Whether it takes the call with a.work_bytes of scratch (always for 48 rows of an aligned x): 16-byte loads of x, whose rows are
 // multiples of 64 bytes; room for the copy of x; grids within 2^32 threads and 65535 tiles of 16 batch rows.
