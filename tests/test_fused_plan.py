@@ -48,3 +48,21 @@ def test_copy_of_x_is_decided_for_the_parts_that_fit(plans):
         assert p.copy_bytes + (batch * M * 4 * p.parts if p.parts > 1 else 0) <= work, what
         if p.nj == 4 and p.copy_bytes == 0:
             assert p.steps <= (1 if b == 8 else 2) * p.waves * p.parts, what
+
+
+def test_plans_that_the_gpu_tests_name(plans):
+    # the shapes of the GPU tests reach the paths that they are there for
+    from test_gpu_large_batch import ALL_BITS, COPIED_X, PASSES_OF_HALF_THE_ROWS
+    from test_zz_no_alloc import SEQUENCE
+    for M, K, batch, parts in COPIED_X:
+        for work in (M * K * 2, STATIC_BYTES):
+            for p in plans([(M, K, b, batch, work) for b in ALL_BITS]):
+                assert p.taken and p.nj == 4 and p.waves == 8 and p.copy_bytes > 0 and p.parts == parts, (M, K, batch, work, p)
+    for M, K, batch, bits in PASSES_OF_HALF_THE_ROWS:
+        for p, half in zip(plans([(M, K, b, batch, STATIC_BYTES) for b in bits]), plans([(M, K, b, batch // 2, STATIC_BYTES) for b in bits])):
+            assert not p.taken and p.copy_bytes > STATIC_BYTES and half.taken, (M, K, batch, p, half)
+    for (M, K, batch), bits, keeps in SEQUENCE:
+        for p in plans([(M, K, b, batch, STATIC_BYTES) for b in bits]):
+            assert p.taken
+            if keeps:
+                assert (p.copy_bytes > 0, p.parts > 1) == ("copy" in keeps, "parts" in keeps), (M, K, batch, keeps, p)

@@ -128,10 +128,37 @@ def test_fused_gemm_many_workgroups_and_largest_batches(B, M, K, batch, bits):
     pm.close()
 
 
-# ap_gemm_static in several passes: more rows than one pass takes, and rows so long that the copy of 320 of them exceeds the
+# 64 batch rows per workgroup with a copy of x at every bit-width, on 8 waves: one column part, two and three (partial sums behind the
+# copy; outputs whose number is and is not a multiple of 4); a ragged last step, M not a multiple of 64.  (M, K, batch, parts);
+# test_fused_plan.py checks on the host that these are the plans
+COPIED_X = [(2101, 2208, 250, 1), (1501, 4256, 250, 2), (1300, 6240, 250, 3)]
+
+
+@pytest.mark.parametrize("M,K,batch,parts", COPIED_X)
+def test_fused_gemm_with_a_copy_of_x(B, M, K, batch, parts):
+    import torch
+    idx, luts, x = inputs.make_case(53, M, K, batch=batch)
+    rows = np.unique(np.concatenate([np.arange(66), np.random.default_rng(K).integers(0, M, size=30), np.arange(M - 70, M)]))
+    pm = B.ap_pack(idx, luts)
+    xd = torch.from_numpy(x).cuda()
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for b in ALL_BITS:
+        y = torch.full((batch, M), -7.0, dtype=torch.float16, device="cuda")
+        assert B.lib.ap_gemm_static(pm.handle, b, xd.data_ptr(), y.data_ptr(), batch, sp) == 0
+        for out in (B.ap_gemm(pm, b, xd), y):
+            torch.cuda.synchronize()
+            check_against_oracle(out.cpu().numpy(), idx, luts[b], b, x, rows=rows)
+    pm.close()
+
+
+# ap_gemm_static in several passes: more rows than one pass takes, and rows so long that the copy of all of them exceeds the
 # static array (passes of half the rows); and the sizes on either side of its dense kernel
-@pytest.mark.parametrize("M,K,batch,bits", [(2100, 2048, 2100, [5]), (20, 65536 + 96, 300, [3, 8]), (96, 256, 700, ALL_BITS),
-                                            (96, 288, 700, [4, 7]), (33, 512, 49, [6, 8]), (33, 544, 49, [6, 8])])
+PASSES_OF_HALF_THE_ROWS = [(100, 38304, 500, [3, 8]), (20, 65536 + 96, 300, [8])]
+
+
+@pytest.mark.parametrize("M,K,batch,bits", PASSES_OF_HALF_THE_ROWS +
+                         [(2100, 2048, 2100, [5]), (20, 65536 + 96, 300, [3]), (96, 256, 700, ALL_BITS),
+                          (96, 288, 700, [4, 7]), (33, 512, 49, [6, 8]), (33, 544, 49, [6, 8])])
 def test_static_gemm_passes_and_dense_kernel(B, M, K, batch, bits):
     import torch
     idx, luts, x = inputs.make_case(48, M, K, batch=batch, bit_widths=bits)

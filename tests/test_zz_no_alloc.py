@@ -36,15 +36,19 @@ def _both(B, torch, pm, b, x):
     return out[guard:-guard].reshape(batch, M), y_ref.cpu().numpy()
 
 
+# ((M, K, batch), bit-widths, what a call keeps in the array where that matters)
+# first call: larger matrix, ragged in every dimension (rows not a multiple of 16, batch not a
+# multiple of 16, a ragged last span); second call: a smaller matrix; then calls that use the array themselves, each over
+# what the one before it left there: partial sums, a copy of x and partial sums, a smaller copy, dense weights, a copy again, and
+# neither (test_fused_plan.py checks on the host that these are the plans)
+SEQUENCE = [((200, 2048 + 96, 37), (3, 8), "parts"), ((52, 160, 5), (4, 7), None), ((200, 2048 + 96, 150), (5,), "parts"),
+            ((200, 2048 + 96, 150), (8,), "copy and parts"), ((70, 1088, 49), (8,), "copy"), ((70, 544, 49), (4, 7), "neither"),
+            ((52, 160, 49), (4, 7), None), ((70, 1088, 64), (8,), "copy"), ((70, 544, 64), (3, 6), "neither")]
+
+
 def test_static_gemm_matches_gemm_on_two_calls_in_a_row(B):
     import torch
-    # first call: larger matrix, ragged in every dimension (rows not a multiple of 16, batch not a
-    # multiple of 16, a ragged last span); second call: a smaller matrix, which leaves the first
-    # call's weights in the rest of the shared array; then calls that use the array themselves, each over what the one
-    # before it left there: a copy of x and partial sums, a smaller copy, dense weights, a copy again
-    cases = [((200, 2048 + 96, 37), (3, 8)), ((52, 160, 5), (4, 7)), ((200, 2048 + 96, 150), (5, 8)), ((70, 544, 49), (4, 7)),
-             ((52, 160, 49), (4, 7)), ((70, 544, 64), (3, 6))]
-    for (M, K, batch), bits in cases:
+    for (M, K, batch), bits, _ in SEQUENCE:
         idx, luts, x = inputs.make_case(41, M, K, batch=batch)
         pm = B.ap_pack(idx, luts)
         for b in bits:
