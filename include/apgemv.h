@@ -231,7 +231,8 @@ ap_status ap_dequantize(const ap_matrix *h, int b, void *w_dev, void *stream);
  * y = x * W_b^T for any batch >= 1 (the paper's route for batch above ~16).  With a 16-byte aligned x, batches of up to 16 run
  * as ap_gemv does (on a handle without options) and larger ones, up to 256 (384 at b = 4 and 5, 512 at b = 3; fewer on tall
  * matrices with short rows), on a kernel that dequantises into the matrix instructions, except where that measured slower:
- * small matrices at b >= 7, and sizes at which work_dev has no room for its partial sums.  Everything else is
+ * matrices of up to 768 rows and 2080 to 4096 columns at b = 8, and sizes at which work_dev has no room for its partial sums.
+ * Everything else is
  * ap_dequantize into work_dev, then one FP16 GEMM with binary32 accumulation from rocBLAS, which is loaded on first use
  * (AP_ERR_HIP if it cannot be loaded or fails).
  *   x_dev     device, batch*K binary16 row-major;  y_dev  device, batch*M binary16 row-major

@@ -399,35 +399,6 @@ extern "C" ap_status ap_gemm_workspace_size(const ap_matrix *h, size_t *bytes)
     return AP_OK;
 }
 
-// Whether a product of ap_gemm runs on the fused kernel rather than as ap_dequantize and one rocBLAS product.  The fused kernel
-// dequantises once per 64 batch rows, at b = 3 for half the cost.  The lines come from 14 000 calls (18 heights 64..28672, 12 row
-// lengths 256..28672, 15 batches 17..512, every b); on the calls given to it it is 1.0 to 4.6 times as fast, on 0.7 % of them 3 to 17 %
-// slower (worst 300 x 8192 at batch 160..192).  Dequantise + rocBLAS / fused, us:
-//   batch, by b   8192x8192 batch 256 / 384 / 512  b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111, b = 8 115/68 108/97 118/126
-//   tall, short   the dense weights stay in the last-level cache: 28672x1024 b = 8 batch 128 / 256 38/37 43/58, b = 5 batch 320 41/49,
-//                 b = 3 batch 512 47/61; 28672x8192 b = 8 batch 256 255/215
-//   column parts  a workspace without room for the partial sums leaves few workgroups with all columns: 64x8192 b = 8 batch 64 (no part
-//                 of 8) 16/32, batch 65 16/14 (no copy of x); 512x4096 b = 5 batch 384 (1 of 4) 18/23, batch 320 (2 of 4) 18/19
-//   small         the tables of 64 rows weigh as much as their columns: 512x256 b = 8 batch 256 9.4/11.7, 512x1056 b = 8 batch 128 13/15
-static bool gemm_fused_pays(const GemvArgs &a)
-{
-    const FusedPlan p = fused_plan(a);
-    const int M = a.M, K = a.K;
-    int most = a.b == 3 ? 512 : a.b <= 5 ? 384 : 256;
-    if (a.b == 3 && M >= 24576 && K <= 2048) most = 384;
-    if ((a.b == 4 || a.b == 5) && M >= 12288 && K < 8192) most = M >= 24576 && K <= 2048 ? 256 : 320;
-    if (a.b == 7 && M >= 24576 && K <= 1024) most = 128;
-    if (a.b == 8 && M >= 12288 && K <= 1024) most = M >= 20480 ? 128 : 192;
-    if (a.b == 8 && M >= 24576 && K > 1024 && K <= 2048) most = 192;
-    if (a.batch > most) return false;
-    const int wanted = fused_parts_wanted(p), parts = p.parts;
-    if (parts < wanted && ((4 * parts <= wanted && K <= 16384) || (a.b > 3 && parts == 1))) return false;
-    if (p.nj == 4 && a.b >= 7 && M <= 768 && K > 1024 && K <= (a.b == 8 ? 4096 : 1536)) return false;
-    if (p.nj == 4 && K < 512 && M <= (a.b == 8 ? 2048 : 1024) && (a.b >= 7 || (a.b >= 4 && a.batch > 128)))
-        return M > 128 && M < 256; // rocBLAS is slow between its tiles: 200 x 256 b = 8 batch 192 25/12
-    return true;
-}
-
 extern "C" ap_status ap_gemm(const ap_matrix *h, int b, const void *x_dev, void *y_dev, int batch,
                              void *work_dev, size_t work_bytes, void *stream)
 {

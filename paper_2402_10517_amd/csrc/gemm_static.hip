@@ -4,8 +4,8 @@
 // allocates.  Code under HIP graph capture, tight serving loops and harnesses that forbid
 // hipMalloc need an entry point that allocates nothing at all: the fused kernel (gemm_fused.hip) takes batches above 16
 // here, with its copy of the activations and its partial sums in `scratch` below (one copy per GPU, held until the process
-// ends).  Against dequantising into the array and the dense kernel below, 4096 x 4096 b = 5 batch 33: 61 -> 13 us.  The
-// dense kernel keeps products of few columns.
+// ends).  Against dequantising into the array and the dense kernel below, 4096 x 4096 b = 5 batch 33: 61 -> 11 us.  The
+// dense kernel keeps products of very few columns (static_dense_pays).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -81,18 +81,6 @@ __global__ __launch_bounds__(256) void dense_gemm_kernel(const uint16_t *__restr
     }
 }
 
-// Dequantise + this kernel over the fused kernel, us, b = 3 / 5 / 8: 64x32 batch 256 5.5/8.2 5.9/8.1 6.1/9.7, 300x256 batch 128
-// 7.4/8.7 8.1/10.0 8.2/11.8, batch 1024 9.1/9.0 9.8/10.3 9.9/12.1, 1024x256 batch 512 10.1/8.9 10.5/10.2 10.9/11.9, 300x512 batch 512
-// 10.1/9.5 10.5/10.8 10.8/13.6; up to 48 batch rows, which need no copy of x, the fused kernel is level or ahead (64x256 batch 33 1.30
-// to 0.95).  Every wave of this one reads its 16 rows and 16 batch rows for itself, so its time grows with their product (28672x32
-// b = 5 batch 64 20/9).
-bool dense_pays(const GemvArgs &a)
-{
-    const long long waves = (long long)((a.M + 15) / 16) * ((a.batch + 15) / 16);
-    if (a.b >= 7) return a.batch > 48 && a.K <= 512 && a.M <= 4096 && waves * a.K <= 1 << 19;
-    return a.batch > 48 && a.K <= 256 && a.M <= 2048 && waves * a.K <= 1 << 18;
-}
-
 } // namespace
 
 bool static_scratch_setup() { return scratch_on_current_device() != nullptr; }
@@ -129,7 +117,7 @@ extern "C" ap_status ap_gemm_static(const ap_matrix *h, int b, const void *x_dev
     a.y = static_cast<uint16_t *>(y_dev);
     a.batch = batch;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dense_pays(a)) { // M * K fits the array (above)
+    if (static_dense_pays(a)) { // M * K fits the array (above)
         a.y = static_cast<uint16_t *>(work);
         if (launch_dequantize(a, st) != hipSuccess) return AP_ERR_HIP;
         const int row_tiles = (a.M + 15) / 16, tiles = row_tiles * ((batch + 15) / 16);

@@ -80,6 +80,48 @@ inline bool gemm_fused_ok(const GemvArgs &a)
     const FusedPlan p = fused_plan(a);
     return p.copy_bytes <= a.work_bytes && p.copy_bytes < 0xffffffffu && (long long)p.blocks * p.ntiles <= 1 << 22;
 }
+// Whether a product of ap_gemm runs on the fused kernel rather than as ap_dequantize and one rocBLAS product.  The fused kernel
+// dequantises once per 64 batch rows, at b = 3 for half the cost.  The batch lines come from 14 000 calls (18 heights 64..28672, 12 row
+// lengths 256..28672, 15 batches 17..512, every b), the others from 9700 more on the kernel that copies x only where that pays (32
+// heights 1..2560, 31 row lengths 32..6656, 9 batches 49..384).  Dequantise + rocBLAS / fused, us:
+//   batch, by b   8192x8192 batch 256 / 384 / 512  b = 3 106/46 98/65 112/86, b = 5 110/59 101/84 113/111, b = 8 115/68 108/97 118/126
+//   tall, short   the dense weights stay in the last-level cache: 28672x1024 b = 8 batch 128 / 256 38/37 43/58, b = 5 batch 320 41/49,
+//                 b = 3 batch 512 47/61; 28672x8192 b = 8 batch 256 255/215
+//   column parts  a workspace without room for the partial sums leaves few workgroups with all columns: 64x5632 b = 8 batch 64 (1 of 5)
+//                 13/22, 256x13824 b = 8 batch 256 (1 of 13) 25/46, 400x16384 b = 5 batch 384 (1 of 6) 39/50, batch 320 (5 of 7) 32/30
+//   small, b = 8  a copy of x and steps that do not divide evenly among two or three parts: 300x2304 batch 64 / 192 11.8/13.1 11.7/13.9,
+//                 300x2816 12.9/14.8 12.8/16.0, 256x3584 batch 192 14.0/15.6; without the copy 300x3072 batch 64 / 192 13.3/10.8 13.5/12.3,
+//                 512x256 batch 256 9.0/7.0, 256x416 batch 64 15.8/7.1; one part 512x1056 batch 128 12.4/11.1; b = 7 512x1056 12.6/9.0
+inline bool gemm_fused_pays(const GemvArgs &a)
+{
+    const FusedPlan p = fused_plan(a);
+    const int M = a.M, K = a.K;
+    int most = a.b == 3 ? 512 : a.b <= 5 ? 384 : 256;
+    if (a.b == 3 && M >= 24576 && K <= 2048) most = 384;
+    if ((a.b == 4 || a.b == 5) && M >= 12288 && K < 8192) most = M >= 24576 && K <= 2048 ? 256 : 320;
+    if (a.b == 7 && M >= 24576 && K <= 1024) most = 128;
+    if (a.b == 8 && M >= 12288 && K <= 1024) most = M >= 20480 ? 128 : 192;
+    if (a.b == 8 && M >= 24576 && K > 1024 && K <= 2048) most = 192;
+    if (a.batch > most) return false;
+    const int wanted = fused_parts_wanted(p), parts = p.parts;
+    if (parts < wanted && ((4 * parts <= wanted && K <= 16384) || (a.b > 3 && parts == 1))) return false;
+    return !(a.b == 8 && p.copy_bytes && M <= 768 && K > 2048 && K <= (a.batch > 128 && M <= 512 ? 4096 : 3072));
+}
+// Whether ap_gemm_static dequantises and runs its dense kernel (gemm_static.hip) rather than the fused kernel, whose workgroups each
+// build the tables of 64 rows: where these outweigh few columns, most at 8 bits.  The dense kernel's waves read 16 rows and 16 batch rows
+// each for themselves, so its time grows with their product.  From 7900 calls (heights 1..4096, row lengths 32..768, batches
+// 49..5000, every b); 0.5 % of them are 3 to 17 % slower than on the other kernel where that was taken before.  Dequantise + dense
+// kernel / fused, us: 64 x 32 / 64 / 96 batch 200 b = 8 5.8/6.5 6.0/6.5 6.3/6.5, b = 3 5.1/5.4 5.3/5.4 5.6/5.4, b = 5 5.6/5.8 5.8/5.8
+// 6.2/5.8; 1024 x 32 b = 8 batch 200 / 500 / 1500 6.4/6.8 6.9/7.0 9.5/8.2, b = 5 batch 200 1.02 to 1; 8 x 128 batch 200 b = 8 6.0/6.5,
+// b = 5 5.8/5.8; 300 x 256 batch 128 b = 8 7.9/6.9.
+inline bool static_dense_pays(const GemvArgs &a)
+{
+    const long long waves = (long long)((a.M + 15) / 16) * ((a.batch + 15) / 16);
+    if (a.batch <= 48) return false;
+    if (a.M <= 8) return a.K <= 256 && waves * a.K <= 1 << 16;
+    if (a.b == 8) return a.K <= (a.M <= 200 ? 128 : 96) && a.M <= 1024 && waves * a.K <= 1 << 17;
+    return a.K <= (a.M <= 200 ? 64 : 32) && a.M <= 768 && waves * a.K <= 1 << 16;
+}
 
 constexpr int kMaxMulti = 8;
 struct MultiArgs { // passed by value as the kernel argument of a fused launch

@@ -152,11 +152,14 @@ def test_fused_gemm_with_a_copy_of_x(B, M, K, batch, parts):
 
 
 # ap_gemm_static in several passes: more rows than one pass takes, and rows so long that the copy of all of them exceeds the
-# static array (passes of half the rows); and the sizes on either side of its dense kernel
+# static array (passes of half the rows); and the sizes on either side of its dense kernel (DENSE_EDGES: the longest rows that it takes)
 PASSES_OF_HALF_THE_ROWS = [(100, 38304, 500, [3, 8]), (20, 65536 + 96, 300, [8])]
 
+DENSE_EDGES = [(96, 128, 700, [8]), (33, 128, 49, [8]), (209, 96, 300, [8]), (96, 64, 700, [3, 4, 5, 6, 7]), (209, 32, 300, [3, 4, 5, 6, 7]),
+               (7, 256, 700, ALL_BITS)]
 
-@pytest.mark.parametrize("M,K,batch,bits", PASSES_OF_HALF_THE_ROWS +
+
+@pytest.mark.parametrize("M,K,batch,bits", PASSES_OF_HALF_THE_ROWS + DENSE_EDGES + [(M, K + 32, batch, bits) for M, K, batch, bits in DENSE_EDGES] +
                          [(2100, 2048, 2100, [5]), (20, 65536 + 96, 300, [3]), (96, 256, 700, ALL_BITS),
                           (96, 288, 700, [4, 7]), (33, 512, 49, [6, 8]), (33, 544, 49, [6, 8])])
 def test_static_gemm_passes_and_dense_kernel(B, M, K, batch, bits):

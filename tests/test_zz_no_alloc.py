@@ -43,7 +43,7 @@ def _both(B, torch, pm, b, x):
 # neither (test_fused_plan.py checks on the host that these are the plans)
 SEQUENCE = [((200, 2048 + 96, 37), (3, 8), "parts"), ((52, 160, 5), (4, 7), None), ((200, 2048 + 96, 150), (5,), "parts"),
             ((200, 2048 + 96, 150), (8,), "copy and parts"), ((70, 1088, 49), (8,), "copy"), ((70, 544, 49), (4, 7), "neither"),
-            ((52, 160, 49), (4, 7), None), ((70, 1088, 64), (8,), "copy"), ((70, 544, 64), (3, 6), "neither")]
+            ((52, 96, 49), (8,), "dense"), ((70, 1088, 64), (8,), "copy"), ((70, 544, 64), (3, 6), "neither")]
 
 
 def test_static_gemm_matches_gemm_on_two_calls_in_a_row(B):
