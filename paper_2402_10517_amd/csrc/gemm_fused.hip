@@ -401,7 +401,8 @@ __global__ __launch_bounds__(256) void fragment_x_kernel(const uint16_t *__restr
 }
 
 // y = sum of the parts, in order (n = batch * M values each).  All latency: a part's values come from beyond this XCD's L2, so the
-// loads of up to 8 parts go out together (4096 x 4096 b = 5 batch 33, 4 parts: 3.0 us one after the other, 2.65 together).
+// loads of up to 8 parts go out together.  One after the other / together, us (batch 32, b = 4): 2 parts 8192 x 4096 3.84 / 3.84, 3 parts
+// 5440 x 4096 3.80 / 3.80, 4 parts 4096 x 4096 3.76 / 2.28, 8 parts 2048 x 8192 3.56 / 2.46.
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float *__restrict__ partial, uint16_t *__restrict__ y, size_t n, int parts)
 {
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
