@@ -14,20 +14,16 @@
 //     4 row groups each), and one ds_bpermute per word moves a word to the lane that dequantises it
 //     (lane 16 kg + 4 g + r: group g, row r).  Loaded directly in that order, every 4 lanes would touch
 //     another cache line and a line would be requested again while it is still in flight.
-//   * The activations of a run of an octet are 128 contiguous bytes per batch row: lane 8 n + p loads
-//     16 bytes of batch row n (chunk p ^ 2 (n / 4)), so one instruction covers 8 batch rows line by line
-//     (a lane-per-row order costs one cache access per lane).  Four ds_bpermute per run move them to the
-//     lanes of the matrix instruction: lane (i, kg) takes batch row i % 8, chunk 4 (i / 8) + kg.  The
-//     chunk exchanges (^ 2 p, ^ 2 (n / 4)) make the 32 source lanes of each half of a ds_bpermute
-//     different mod 32, which is what that instruction needs to run without bank conflicts.  Both
-//     quads of the octet use that register as B: output columns 0..7 of the first quad's instruction
-//     and columns 8..15 of the second's are the products wanted (batch rows 0..7 each), the other
-//     halves multiply one quad's weights with the other quad's activations and are dropped, so each
-//     quad has its own accumulator and the final sum takes column n of one and n + 8 of the other.
-//     Batch rows that do not exist read zeros (their buffer offset is out of range: no memory traffic).
-//   * Batch 9..16 (WIDE): every quad of chunks has activations of its own (two loads per run, 16 batch rows x 64 contiguous bytes
-//     each), and all 16 columns of both products count.  Against two passes of 8 rows, batch 16, b = 4: 4096 x 4096 11.8 -> 7.0 us,
-//     11008 x 4096 20.3 -> 15.4, 28672 x 8192 68 -> 43.
+//   * The activations of a run go into the matrix instruction as they are loaded: lane 16 kg + 2 n + h loads the 16 bytes of batch
+//     row n, chunk 4 h + kg, so column 2 n + h of operand B belongs to batch row n and quad h.  Both quads of an octet multiply with
+//     that one register: of either product the columns of its own quad count, the others are dropped, and a final sum adds the two
+//     columns of a batch row.  A load in this order costs the vector L1 33 clocks instead of 17 (16 bytes of four neighbouring lanes are
+//     64 contiguous ones there, here 32), but it replaces 4 ds_bpermute per run, and the LDS was the busiest unit: it alone took 29 of
+//     37 us that 28672 x 8192, b = 5, batch 8 needs without its loads.  With the exchange / without, us: 8192 x 28672 b = 3 batch 8
+//     26.0 / 23.2, 28672 x 8192 b = 4 batch 4 32.9 / 26.5, b = 5 batch 8 42.7 / 41.0, b = 8 53.2 / 51.3, 4096 x 4096 b = 4 batch 4
+//     5.4 / 4.95.  Batch rows that do not exist read zeros (their buffer offset is out of range: no memory traffic).
+//   * Batch 9..16 (WIDE): two such registers, rows 0..7 and 8..15, and twice the matrix instructions (11008 x 4096 b = 4 batch 16
+//     14.7 / 13.05, 28672 x 8192 b = 3 38.8 / 33.8).
 //   * One instruction takes one run of 8 consecutive columns: their indices are the bytes of the
 //     merged words of the run's even and odd slots, the activations the lane's 16 bytes of that run.
 //   * The LDS serves 32 lanes per clock, here 16 rows x 2 lane groups, so every (row, lane group
@@ -100,17 +96,17 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     using TT = TileTable<B>;
     constexpr int kTileRows = 16, kTileGroups = kTileRows / kRowsPerGroup;
     // the tables during the main loop, then the waves' partial sums [wave][tile][row][batch row]
-    constexpr int kTabBytes = R * TT::kTileBytes, kRedBytes = (MAXT / 64) * R * kTileRows * 16 * 4;
+    constexpr int kTabBytes = R * TT::kTileBytes, kCols = WIDE ? 16 : 8, kRedBytes = (MAXT / 64) * R * kTileRows * kCols * 4;
     __shared__ __attribute__((aligned(16))) uint8_t smem[kTabBytes > kRedBytes ? kTabBytes : kRedBytes];
     uint8_t *tab = smem;
     __shared__ __attribute__((aligned(16))) uint16_t nat[TT::kPair ? R * kTileRows * 10 : TT::kPair4 ? R * kTileRows * 18 : 8]; // the rows as stored (pair paths)
-    float(*red)[R][kTileRows][16] = reinterpret_cast<float(*)[R][kTileRows][16]>(smem);
+    float(*red)[R][kTileRows][kCols] = reinterpret_cast<float(*)[R][kTileRows][kCols]>(smem);
 
     const int tid = threadIdx.x, nth = blockDim.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nwaves = nth >> 6;
-    const int i = lane & 15;  // row of a tile this lane dequantises; output column (batch row) it receives
+    const int i = lane & 15;  // row of a tile this lane dequantises; output column (batch row, quad) it receives
     const int kg = lane >> 4; // its 8 columns of every instruction; its chunk of every quad of chunks
     const int groups = (M + kRowsPerGroup - 1) / kRowsPerGroup;
     const int g0 = wg * (R * kTileGroups);
@@ -138,26 +134,26 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // sources of either half of the wave are all different (without it every exchange took two clocks
     // more).
     const int bperm_src = (((((i >> 2) & 1) << 1 | (i >> 3)) << 4) | ((kg ^ (((i >> 2) & 1) << 1)) << 2) | (i & 3)) << 2; // byte address of the source lane
-    // activations: lane 8 n + p loads batch row n, chunk p ^ 2 (n / 4) of the octet (8 lanes = one 128-byte
-    // line; the exchange for the same reason as above); the descriptor ends with the last batch row, and
-    // lanes of rows past the batch carry an offset beyond it (batch * K * 2 < 2^31; valid lanes stay below
-    // the end with any scalar offset).  This lane then takes batch row i & 7, chunk 4 (i >> 3) + kg.
+    // activations: lane 16 kg + 2 n + h loads batch row n (WIDE: and n + 8), chunk 4 h + kg of the octet; the descriptor ends with the last
+    // batch row, and lanes of rows past the batch carry an offset beyond it (batch * K * 2 < 2^31; valid lanes stay below the end
+    // with any scalar offset).
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(x), 0, (uint32_t)batch * (uint32_t)K * 2u, kBufferRsrcWord3);
-    // WIDE: one load per quad of chunks instead, lane 4 n + p with batch row n, chunk p ^ 2 (n / 8) of the quad (4 lanes = 64
-    // contiguous bytes); this lane takes batch row i, chunk kg of either quad, and column i of both products counts.
     constexpr int kXSets = WIDE ? 2 : 1;
-    const int xn = WIDE ? lane >> 2 : lane >> 3, xc = WIDE ? (lane & 3) ^ ((lane >> 5) << 1) : (lane & 7) ^ ((lane >> 5) << 1);
-    const uint32_t xoff_lane = xn < batch ? (uint32_t)xn * (uint32_t)K * 2u + (uint32_t)xc * 16u : 0x80000000u;
-    const int xperm_src = (WIDE ? (i << 2) | (kg ^ ((i >> 3) << 1))
-                                : ((i & 7) << 3) | ((i >> 3) << 2) | (kg ^ (((i >> 2) & 1) << 1))) << 2; // byte address of the source lane
+    const int xn = i >> 1, xc = 4 * (i & 1) + kg;
+    uint32_t xoff_lane[kXSets];
+#pragma unroll
+    for (int q = 0; q < kXSets; ++q)
+        xoff_lane[q] = xn + 8 * q < batch ? (uint32_t)(xn + 8 * q) * (uint32_t)K * 2u + (uint32_t)xc * 16u : 0x80000000u;
     const uint32_t rowbase = ((uint32_t)i << 2) | ((uint32_t)(kg & 1) << 6);
     uint32_t seven = 7; // shift amount of the 4-bit pair path's addresses, kept in a register (SDWA operand)
     asm("" : "+v"(seven));
 
-    float4_t acc[R][2]; // one accumulator per quad of an octet: independent chains of matrix instructions
+    float4_t acc[R][kXSets][2]; // one accumulator per quad of an octet (and 8 batch rows): independent chains of matrix instructions
 #pragma unroll
-    for (int tile = 0; tile < R; ++tile) acc[tile][0] = acc[tile][1] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int tile = 0; tile < R; ++tile)
+#pragma unroll
+        for (int q = 0; q < kXSets; ++q) acc[tile][q][0] = acc[tile][q][1] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     // Octet o of a row = chunks 8 o .. 8 o + 7 (span o / 8); the waves split the row's pairs of octets
     // evenly.  The loads of an octet are issued before the arithmetic of the octet before it (two
@@ -177,9 +173,9 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         const int left = chunks - o * 8; // chunks of this octet and beyond
 #pragma unroll
         for (int q = 0; q < kXSets; ++q) {
-            const uint32_t xoff = real && (!RAG || xc + 4 * q < left) ? xoff_lane : 0x80000000u;
+            const uint32_t xoff = real && (!RAG || xc < left) ? xoff_lane[q] : 0x80000000u;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl + q * 64), 0);
+            for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl), 0);
         }
         // no records, no memory access (the addresses are valid all the same)
         const uint32_t records = SKIP ? (uint32_t)__builtin_amdgcn_readfirstlane(real ? -1 : 0) : 0xffffffffu;
@@ -196,14 +192,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                     Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane[tile][half] - back,
                                                                             soct + (uint32_t)s * (uint32_t)slice_bytes, kBufferNonTemporal);
     };
-    auto compute = [&](const u32x4 (&Xl)[kXSets][4], const uint32_t (&Q)[R][2][B], int o) {
-        u32x4 X[kXSets][4];
-#pragma unroll
-        for (int q = 0; q < kXSets; ++q)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) X[q][t][d] = (uint32_t)__builtin_amdgcn_ds_bpermute(xperm_src, (int)Xl[q][t][d]);
+    auto compute = [&](const u32x4 (&X)[kXSets][4], const uint32_t (&Q)[R][2][B], int o) {
         const uint32_t keep[2] = {kg < chunks - o * 8 ? 0xffffffffu : 0u, kg + 4 < chunks - o * 8 ? 0xffffffffu : 0u}; // RAG
 #pragma unroll
         for (int tile = 0; tile < R; ++tile) {
@@ -288,13 +277,15 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 #pragma unroll
                         for (int j = 0; j < 4; ++j) P[h][j] &= keep[h];
                 }
-                // both quads against the same B: columns 0..7 of the first product and 8..15 of the second count (WIDE: each quad
-                // against its own, all columns count)
+                // both quads against the same B: the even columns of the first product and the odd ones of the second count
                 const u32x4 a0 = {P[0][0], P[0][1], P[0][2], P[0][3]}, a1 = {P[1][0], P[1][1], P[1][2], P[1][3]};
-                acc[tile][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, X[0][t]),
-                                                                      acc[tile][0], 0, 0, 0);
-                acc[tile][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, X[kXSets - 1][t]),
-                                                                      acc[tile][1], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < kXSets; ++q) {
+                    acc[tile][q][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, X[q][t]),
+                                                                             acc[tile][q][0], 0, 0, 0);
+                    acc[tile][q][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, X[q][t]),
+                                                                             acc[tile][q][1], 0, 0, 0);
+                }
             }
         }
     };
@@ -447,9 +438,11 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     }
     __syncthreads();
 
-    float4_t before[R][2]; // the sums ahead of the wave's last octet
+    float4_t before[R][kXSets][2]; // the sums ahead of the wave's last octet
 #pragma unroll
-    for (int tile = 0; tile < R; ++tile) before[tile][0] = before[tile][1] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int tile = 0; tile < R; ++tile)
+#pragma unroll
+        for (int q = 0; q < kXSets; ++q) before[tile][q][0] = before[tile][q][1] = float4_t{0.f, 0.f, 0.f, 0.f};
     for (; p < p1; ++p) {
         const bool second = 2 * p + 1 < nocts;
         const int o1 = second ? 2 * p + 1 : 2 * p;
@@ -462,31 +455,37 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
             compute(XB, QB, 2 * p + 1); // the padding octet has no chunks: all centroids masked
         } else {
 #pragma unroll
-            for (int tile = 0; tile < R; ++tile) { before[tile][0] = acc[tile][0]; before[tile][1] = acc[tile][1]; }
+            for (int tile = 0; tile < R; ++tile)
+#pragma unroll
+                for (int q = 0; q < kXSets; ++q) { before[tile][q][0] = acc[tile][q][0]; before[tile][q][1] = acc[tile][q][1]; }
             compute(XB, QB, o1);
         }
     }
     if (!RAG && (nocts & 1) && p1 == npairs) { // the padding octet does not count
 #pragma unroll
-        for (int tile = 0; tile < R; ++tile) { acc[tile][0] = before[tile][0]; acc[tile][1] = before[tile][1]; }
+        for (int tile = 0; tile < R; ++tile)
+#pragma unroll
+            for (int q = 0; q < kXSets; ++q) { acc[tile][q][0] = before[tile][q][0]; acc[tile][q][1] = before[tile][q][1]; }
     }
 
-    // ---- acc[tile][h][r] of lane (i, kg): output row 4 kg + r of the tile over the wave's columns of quad
-    //      h; column i of the h = 0 accumulator is batch row i for i < 8, column i of the h = 1 accumulator
-    //      is batch row i - 8 for i >= 8.  Waves are added in fixed order
+    // ---- acc[tile][q][h][r] of lane (i, kg): output row 4 kg + r of the tile over the wave's columns of quad h; column i is batch row
+    //      i / 2 (+ 8 q) where i % 2 == h.  The two halves of a batch row are neighbouring lanes; waves are added in fixed order
     __syncthreads(); // every wave is done with the tables, whose memory now takes the partial sums
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            red[wave][tile][4 * kg + r][i] = WIDE ? acc[tile][0][r] + acc[tile][1][r] : i < 8 ? acc[tile][0][r] : acc[tile][1][r];
+        for (int q = 0; q < kXSets; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float half = (i & 1) ? acc[tile][q][1][r] : acc[tile][q][0][r];
+                const float sum = half + dpp_get<0xB1>(half); // quad_perm [1,0,3,2]
+                if (!(i & 1)) red[wave][tile][4 * kg + r][(i >> 1) + 8 * q] = sum;
+            }
     __syncthreads();
-    constexpr int kCols = WIDE ? 16 : 8;
     for (int o = tid; o < R * kTileRows * kCols; o += nth) {
         const int n = o % kCols, r = o / kCols; // r = row inside the workgroup's R tiles
         float s = 0.f;
-        for (int w = 0; w < nwaves; ++w)
-            s += WIDE ? red[w][r >> 4][r & 15][n] : red[w][r >> 4][r & 15][n] + red[w][r >> 4][r & 15][(n + 8) & 15];
+        for (int w = 0; w < nwaves; ++w) s += red[w][r >> 4][r & 15][n];
         const int row = row0 + r;
         if (row < M && n < batch) {
             const __half hv = __float2half_rn(s);
