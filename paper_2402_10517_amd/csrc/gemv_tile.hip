@@ -32,13 +32,14 @@
 //     of a clock share a bank.  For b <= 7, s = 8 and v = the index byte shifted down to its lowest
 //     used bit (the index words are rotated that much further and masked, once per 4 lookups), so
 //     that one v_perm_b32 per lookup builds the address from the word's byte and the lane's base; for
-//     b = 8 that would need 64 KB per tile, so s = 7 and the address takes two operations (a byte
-//     select and a shift-or).  The 3-bit path keeps its 64-entry table of centroid pairs, one pair
+//     b = 8 that would need 64 KB per tile, so s = 7 and v_dot4_u32_u8 multiplies the wanted byte by 128, the
+//     others by 0 and adds the lane's base (a byte select and a shift-or before: 28672 x 8192 batch 8 54.2 -> 51.1 us,
+//     decoder layer batch 4 54.3 -> 51.6).  The 3-bit path keeps its 64-entry table of centroid pairs, one pair
 //     per dword.  The 4-bit path looks pairs up as well: slice 3 is rotated to rotation 0 so that a
 //     merged byte is the 8-bit index of a column pair (8 selects and 4 rotates per 32 weights instead
 //     of 14 and 7, no clean-up), a row's 256 pair entries are built in LDS from its 16 stored
-//     centroids, two copies, entry p of row i at (p << 7) | (c << 6) | (i << 2) (two operations per
-//     address, but per pair, and no pack before the matrix instruction).  Here that pays (same box,
+//     centroids, two copies, entry p of row i at (p << 7) | (c << 6) | (i << 2) (v_dot4_u32_u8 here too; no pack before the
+//     matrix instruction).  Here that pays (same box,
 //     alternating runs at batch 8: 28672 x 8192 46 -> 39 us, 8192 x 8192 16 -> 13.5, 8192 x 28672
 //     46 -> 36), once the table build is cheap (below); in the batch-1 kernel, where all 64 lanes gather
 //     from one row's 256 dwords, the bank conflicts eat the gain.
@@ -58,10 +59,10 @@ template <int B> struct TileTable {
     static constexpr bool kPair4 = (B == 4);
     static constexpr uint32_t kMask = kPair ? 0xFCu : Table<B>::addr_mask(); // index bits inside a merged byte
     static constexpr int kLow = (kMask & 1) ? 0 : (kMask & 2) ? 1 : 2;       // lowest of them
-    static constexpr bool kPerm = (B <= 7);                                  // address by one v_perm_b32
+    static constexpr bool kPerm = (B <= 7 && B != 4);                        // address by v_perm_b32, else by v_dot4_u32_u8
     static constexpr int kExtra = kPerm ? kLow : 0;                          // extra rotation of the index words
     static constexpr uint32_t kClean = (kMask >> kExtra) * 0x01010101u;      // index bits of the rotated words
-    static constexpr int kShift = kPerm ? 8 : 7 - kLow;                      // entry value -> address
+    static constexpr int kShift = kPerm ? 8 : 7;                             // entry value -> address
     static constexpr int kTileBytes = kPair4 ? 256 * 128 : (int)((kMask >> kLow) + 1) << (kPerm ? 8 : 7); // 16 rows x 2 copies x 4 bytes per entry (x 2 unused)
     // value in a (rotated) index byte of the entry stored at position p of a row (lut_stored_pos order; pair index for B = 3)
     __device__ static constexpr uint32_t byte_of(uint32_t p)
@@ -72,7 +73,7 @@ template <int B> struct TileTable {
     template <int J> __device__ static __forceinline__ uint32_t addr(uint32_t w, uint32_t rowbase)
     {
         if constexpr (kPerm) return __builtin_amdgcn_perm(rowbase, w, 0x0c0c0004u | ((uint32_t)J << 8));
-        else return (byte_and<J>(w, kMask) << kShift) | rowbase;
+        else return __builtin_amdgcn_udot4(w, 128u << (8 * J), rowbase, false);
     }
 };
 
@@ -146,8 +147,6 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     for (int q = 0; q < kXSets; ++q)
         xoff_lane[q] = xn + 8 * q < batch ? (uint32_t)(xn + 8 * q) * (uint32_t)K * 2u + (uint32_t)xc * 16u : 0x80000000u;
     const uint32_t rowbase = ((uint32_t)i << 2) | ((uint32_t)(kg & 1) << 6);
-    uint32_t seven = 7; // shift amount of the 4-bit pair path's addresses, kept in a register (SDWA operand)
-    asm("" : "+v"(seven));
 
     float4_t acc[R][kXSets][2]; // one accumulator per quad of an octet (and 8 batch rows): independent chains of matrix instructions
 #pragma unroll
@@ -213,7 +212,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                     merge_words<B, TT::kExtra>(q[0], W[0]);
                     merge_words<B, TT::kExtra>(q[1], W[1]);
                 }
-                if constexpr (TT::kPerm && !TT::kPair4) {
+                if constexpr (TT::kPerm) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -228,17 +227,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const uint32_t v = W[h][2 * t];
-                        if constexpr (TT::kPair4) {
-                            ad[h][0] = byte_shl1<0>(v, seven) | rowbase;
-                            ad[h][1] = byte_shl1<1>(v, seven) | rowbase;
-                            ad[h][2] = byte_shl1<2>(v, seven) | rowbase;
-                            ad[h][3] = byte_shl1<3>(v, seven) | rowbase;
-                        } else {
-                            ad[h][0] = TT::template addr<0>(v, rowbase);
-                            ad[h][1] = TT::template addr<1>(v, rowbase);
-                            ad[h][2] = TT::template addr<2>(v, rowbase);
-                            ad[h][3] = TT::template addr<3>(v, rowbase);
-                        }
+                        ad[h][0] = TT::template addr<0>(v, rowbase);
+                        ad[h][1] = TT::template addr<1>(v, rowbase);
+                        ad[h][2] = TT::template addr<2>(v, rowbase);
+                        ad[h][3] = TT::template addr<3>(v, rowbase);
                     }
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
