@@ -103,6 +103,14 @@ __device__ __forceinline__ uint32_t pair_entry(const uint16_t *nat_row, int i6)
     return (uint32_t)nat_row[pair3_even(i6)] | ((uint32_t)nat_row[pair3_odd(i6)] << 16);
 }
 
+// LDS operations of a wave execute in order; this keeps the compiler from moving them across
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int ctrl> __device__ __forceinline__ float dpp_get(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xf, 0xf, true));

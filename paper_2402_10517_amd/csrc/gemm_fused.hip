@@ -47,14 +47,6 @@ template <int B> struct BlockTable {
     }
 };
 
-// LDS operations of a wave execute in order; this keeps the compiler from moving them across
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct FusedArgs {
     const uint8_t *slices;
     size_t slice_bytes;

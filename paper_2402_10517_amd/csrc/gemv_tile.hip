@@ -8,12 +8,13 @@
 // instruction; the multiply-accumulate cost does not depend on the batch.
 //   * A wave works on octets of chunks (8 chunks = 256 columns of the tile's 16 rows): two quads of
 //     chunks, lane group kg taking chunk kg of the first and chunk 4 + kg of the second.
-//   * Every load instruction reads whole 128-byte lines in lane order.  A slice load covers 2 row groups
-//     x 8 chunks x 4 rows (lane 32 p + 4 c + r: group p, chunk c ^ 2 p, row r), two loads per slice and
-//     tile; one v_permlane16_swap turns the pair into the words of the first and of the second quad (all
-//     4 row groups each), and one ds_bpermute per word moves a word to the lane that dequantises it
-//     (lane 16 kg + 4 g + r: group g, row r).  Loaded directly in that order, every 4 lanes would touch
-//     another cache line and a line would be requested again while it is still in flight.
+//   * Every load of slices reads whole 128-byte lines in lane order: 2 row groups x 8 chunks x 4 rows (lane 32 p + 4 c + r: group p,
+//     chunk c, row r), two loads per slice and tile.  The words go to the lanes that dequantise them (lane 16 kg + 4 g + r: group g, row
+//     r; chunk 4 h + kg of quad h) through 1 KB of LDS per wave, two slices at a time: two ds_write2st64_b32 and two ds_read2st64_b32.
+//     A permlane16_swap (12 clocks of its SIMD) and two ds_bpermute (6 of the LDS each) per slice before that, us: 28672 x 8192 batch 8
+//     b = 4/5/7 31.8/39.9/46.8 -> 31.1/38.4/45.4, 4099 x 2208 b = 7 batch 5 7.24 -> 6.92, 4096 x 4096 b = 8 batch 8 7.36 -> 7.12.
+//     Loaded directly in the order of use, every 4 lanes touch another cache line and a line is requested again while it is still in
+//     flight; 64-byte pieces of all 4 row groups, which need no swap, are 10 to 15 % slower for that reason too.
 //   * The activations of a run go into the matrix instruction as they are loaded: lane 16 kg + 2 n + h loads the 16 bytes of batch
 //     row n, chunk 4 h + kg, so column 2 n + h of operand B belongs to batch row n and quad h.  Both quads of an octet multiply with
 //     that one register: of either product the columns of its own quad count, the others are dropped, and a final sum adds the two
@@ -86,6 +87,8 @@ __device__ __forceinline__ int first_pair(int npairs, int w, uint32_t reciprocal
     return (int)(reciprocal ? __umulhi(a, reciprocal) : a);
 }
 
+constexpr int kExchangeBytes = 1024; // LDS per wave, given at the launch
+
 // `wg` = index of the workgroup within its matrix (R tiles each).  RAG: K is not a multiple of 256 (the last octet holds fewer than 8
 // chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.  SKIP: loads that are dropped ask for no
 // memory (launch_tile_r).
@@ -101,6 +104,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     __shared__ __attribute__((aligned(16))) uint8_t smem[kTabBytes > kRedBytes ? kTabBytes : kRedBytes];
     uint8_t *tab = smem;
     __shared__ __attribute__((aligned(16))) uint16_t nat[TT::kPair ? R * kTileRows * 10 : TT::kPair4 ? R * kTileRows * 18 : 8]; // the rows as stored (pair paths)
+    extern __shared__ __attribute__((aligned(16))) uint32_t bounce_all[]; // kExchangeBytes per wave
     float(*red)[R][kTileRows][kCols] = reinterpret_cast<float(*)[R][kTileRows][kCols]>(smem);
 
     const int tid = threadIdx.x, nth = blockDim.x;
@@ -116,25 +120,21 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     const int nspans = (chunks + kSpanLanes - 1) / kSpanLanes;
 
     // ---- per-lane offsets of the slice loads: lane 32 p + 4 c + r loads row r of row group 2 half + p of
-    // the tile, chunk c ^ 2 p of the octet (16 lanes still read 64 contiguous bytes; the exchange of the
-    // chunk pairs in the odd row groups keeps the lane exchange below free of bank conflicts)
-    const int lp = lane >> 5, lc = ((lane >> 2) & 7) ^ (lp << 1), lr = lane & 3;
-    uint32_t soff_lane[R][2];
-#pragma unroll
-    for (int tile = 0; tile < R; ++tile)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            int rg = tile * kTileGroups + 2 * half + lp;
-            if (g0 + rg >= groups) rg = groups - 1 - g0; // past the matrix: the last group again (never stored)
-            soff_lane[tile][half] = (uint32_t)(rg * chunks + lc) * 16u + (uint32_t)lr * 4u;
-        }
-    // After the swap of 16-lane rows, lane 16 p + 4 c + r of the first (second) word holds row r, chunk
-    // c ^ 2 (g & 1) (plus 4) of the row group g at position p of the order 0, 2, 1, 3; this lane
-    // dequantises row i & 3 of row group i >> 2, chunk kg (4 + kg).  ds_bpermute serves 32 lanes a clock
-    // and two of them conflict when their source lanes are equal mod 32: with the chunk exchange the 32
-    // sources of either half of the wave are all different (without it every exchange took two clocks
-    // more).
-    const int bperm_src = (((((i >> 2) & 1) << 1 | (i >> 3)) << 4) | ((kg ^ (((i >> 2) & 1) << 1)) << 2) | (i & 3)) << 2; // byte address of the source lane
+    // the tile, chunk c of the octet
+    const int lp = lane >> 5, lc = (lane >> 2) & 7, lr = lane & 3;
+    const uint32_t group_bytes = (uint32_t)chunks * 16u, lane_part = (uint32_t)lc * 16u + (uint32_t)lr * 4u;
+    const uint32_t soff_first = (uint32_t)lp * group_bytes + lane_part, soff_last = (uint32_t)(groups - 1 - g0) * group_bytes + lane_part;
+    auto soff_lane = [&](int tile, int half) { // groups past the matrix: the last one again (never stored)
+        const uint32_t off = soff_first + (uint32_t)(tile * kTileGroups + 2 * half) * group_bytes;
+        return off < soff_last ? off : soff_last;
+    };
+    // Dword in the wave's exchange memory of the word of row r, row group g, quad h, lane group k: 32 lanes a clock are on 32 banks both
+    // when a load is written (one g; all h, k, r) and when a quad is read (one h, two k; all g, r).
+    auto place = [](int h, int k, int g, int r) {
+        return r | (k & 1) << 2 | ((k >> 1) ^ (g & 1)) << 3 | (h ^ (g >> 1)) << 4 | (k >> 1) << 5 | h << 6;
+    };
+    uint32_t *bounce = bounce_all + wave * 256;
+    int put0 = place(lc >> 2, lc & 3, lp, lr), get0 = place(0, kg, i >> 2, i & 3);
     // activations: lane 16 kg + 2 n + h loads batch row n (WIDE: and n + 8), chunk 4 h + kg of the octet; the descriptor ends with the last
     // batch row, and lanes of rows past the batch carry an offset beyond it (batch * K * 2 < 2^31; valid lanes stay below the end
     // with any scalar offset).
@@ -148,6 +148,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         xoff_lane[q] = xn + 8 * q < batch ? (uint32_t)(xn + 8 * q) * (uint32_t)K * 2u + (uint32_t)xc * 16u : 0x80000000u;
     const uint32_t rowbase = ((uint32_t)i << 2) | ((uint32_t)(kg & 1) << 6);
 
+    int lanes = xc | lc << 8; // the chunks that this lane loads, for ragged octets
+    // Two ragged tiles at 3 bits keep within 128 registers (4 waves per SIMD) only if what is cheap to compute again is not kept, and if the
+    // second tile's exchange does not move up: with 129 registers 25000 x 288 batch 3 takes 8.5 us instead of 6.2, x 12320 52 instead of 42.
+    constexpr bool kTight = B == 3 && R == 2 && RAG;
     float4_t acc[R][kXSets][2]; // one accumulator per quad of an octet (and 8 batch rows): independent chains of matrix instructions
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
@@ -170,9 +174,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         const int nl = rem < kSpanLanes ? rem : kSpanLanes;
         const uint32_t xs = (uint32_t)span * (kSpanCols * 2u) + (uint32_t)oi * 128u;
         const int left = chunks - o * 8; // chunks of this octet and beyond
+        if constexpr (kTight) asm volatile("" : "+v"(lanes));
 #pragma unroll
         for (int q = 0; q < kXSets; ++q) {
-            const uint32_t xoff = real && (!RAG || xc < left) ? xoff_lane[q] : 0x80000000u;
+            const uint32_t xoff = real && (!RAG || (lanes & 7) < left) ? xoff_lane[q] : 0x80000000u;
 #pragma unroll
             for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl), 0);
         }
@@ -181,29 +186,40 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t *>(slices + (size_t)g0 * chunks * 16), 0, records, kBufferRsrcWord3);
         const uint32_t soct = (uint32_t)o * 128u;
-        const uint32_t back = RAG && lc >= left ? (uint32_t)(lc - (left - 1)) * 16u : 0u; // chunks that do not exist: the last one again
+        const int clane = RAG ? lanes >> 8 : 0;
+        const uint32_t back = RAG && clane >= left ? (uint32_t)(clane - (left - 1)) * 16u : 0u; // chunks that do not exist: the last one again
 #pragma unroll
         for (int tile = 0; tile < R; ++tile)
 #pragma unroll
             for (int s = 0; s < B; ++s)
 #pragma unroll
                 for (int half = 0; half < 2; ++half)
-                    Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane[tile][half] - back,
+                    Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane(tile, half) - back,
                                                                             soct + (uint32_t)s * (uint32_t)slice_bytes, kBufferNonTemporal);
     };
     auto compute = [&](const u32x4 (&X)[kXSets][4], const uint32_t (&Q)[R][2][B], int o) {
+        if constexpr (kTight) asm volatile("" : "+v"(put0), "+v"(get0));
+        const int put[2] = {put0, put0 ^ 16}, get[2] = {get0, (get0 ^ 16) + 64}; // [half of the row groups], [quad]
         const uint32_t keep[2] = {kg < chunks - o * 8 ? 0xffffffffu : 0u, kg + 4 < chunks - o * 8 ? 0xffffffffu : 0u}; // RAG
 #pragma unroll
         for (int tile = 0; tile < R; ++tile) {
             const uint8_t *tt = tab + tile * TT::kTileBytes;
+            if constexpr (kTight) __builtin_amdgcn_sched_barrier(0);
             uint32_t W[2][8]; // [quad of the octet]
             {
                 uint32_t q[2][B];
 #pragma unroll
-                for (int s = 0; s < B; ++s) {
-                    const auto sw = __builtin_amdgcn_permlane16_swap(Q[tile][0][s], Q[tile][1][s], false, false);
-                    q[0][s] = (uint32_t)__builtin_amdgcn_ds_bpermute(bperm_src, (int)sw[0]);
-                    q[1][s] = (uint32_t)__builtin_amdgcn_ds_bpermute(bperm_src, (int)sw[1]);
+                for (int s0 = 0; s0 < B; s0 += 2) {
+#pragma unroll
+                    for (int s = s0; s < B && s < s0 + 2; ++s)
+#pragma unroll
+                        for (int half = 0; half < 2; ++half) bounce[(s - s0) * 128 + put[half]] = Q[tile][half][s];
+                    wave_lds_fence();
+#pragma unroll
+                    for (int s = s0; s < B && s < s0 + 2; ++s)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) q[h][s] = bounce[(s - s0) * 128 + get[h]];
+                    wave_lds_fence();
                 }
                 if constexpr (TT::kPair4) {
                     merge_words_pair4(q[0], W[0]);
@@ -462,6 +478,8 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 
     // ---- acc[tile][q][h][r] of lane (i, kg): output row 4 kg + r of the tile over the wave's columns of quad h; column i is batch row
     //      i / 2 (+ 8 q) where i % 2 == h.  The two halves of a batch row are neighbouring lanes; waves are added in fixed order
+    //      (lane and thread number again from the hardware: kept through the loop they cost registers)
+    const int olane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), oi = olane & 15, okg = olane >> 4;
     __syncthreads(); // every wave is done with the tables, whose memory now takes the partial sums
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
@@ -469,12 +487,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         for (int q = 0; q < kXSets; ++q)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float half = (i & 1) ? acc[tile][q][1][r] : acc[tile][q][0][r];
+                const float half = (oi & 1) ? acc[tile][q][1][r] : acc[tile][q][0][r];
                 const float sum = half + dpp_get<0xB1>(half); // quad_perm [1,0,3,2]
-                if (!(i & 1)) red[wave][tile][4 * kg + r][(i >> 1) + 8 * q] = sum;
+                if (!(oi & 1)) red[wave][tile][4 * okg + r][(oi >> 1) + 8 * q] = sum;
             }
     __syncthreads();
-    for (int o = tid; o < R * kTileRows * kCols; o += nth) {
+    for (int o = wave * 64 + olane; o < R * kTileRows * kCols; o += nth) {
         const int n = o % kCols, r = o / kCols; // r = row inside the workgroup's R tiles
         float s = 0.f;
         for (int w = 0; w < nwaves; ++w) s += red[w][r >> 4][r & 15][n];
@@ -488,12 +506,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 
 // No bound on the waves per SIMD here and in the multi kernel: with at most 4 the b = 3, 4 instances of one tile take 107 registers
 // instead of 74..80 and workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
-// b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9, decoder layer b = 4 batch 4 33.0 / 32.6; 650 calls
-// on whole rows 1.000 to 1.010 by bit-width, 180 on ragged rows 1.000 to 1.036.
+// b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9.  Asked for the waves that they have anyway (as the list kernel is), they
+// schedule worse: 4099 x 2208 b = 7 batch 5 7.0 -> 7.2, 9000 x 3104 b = 5 batch 6 11.5 -> 12.1.
 template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
-__global__ __launch_bounds__(MAXT) void gemv_tile_kernel(const uint8_t *__restrict__ slices, size_t slice_bytes,
-                                                         const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
-                                                         uint16_t *__restrict__ y, int M, int K, int batch, uint32_t reciprocal)
+__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B == 3 && R == 2 && RAG && !WIDE ? 4 : 1))) void gemv_tile_kernel(
+    const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
+    uint16_t *__restrict__ y, int M, int K, int batch, uint32_t reciprocal)
 {
     gemv_tile_body<B, R, MAXT, RAG, WIDE, SKIP>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
 }
@@ -514,8 +532,7 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint
 
 // A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.  The bound asks for the registers
 // that the single instances take by themselves: without it these settle at 107 / 108 / 130 at b = 3 / 4 / 5 (4 / 4 / 3 waves per SIMD
-// instead of 6 / 6 / 5).  Without / with, us: b = 5 decoder layer batch 8 50.1 / 44.7, 3 of 8192 x 12288 batch 4 66.8 / 53.3, 32
-// matrices of 7B decoder layers batch 8 185.4 / 169.5; there b = 3 122.3 / 117.9, b = 4 148.9 / 144.0.
+// instead of 6 / 6 / 5).  Without / with, us: b = 5 decoder layer batch 8 50.1 / 44.7, 3 of 8192 x 12288 batch 4 66.8 / 53.3.
 template <int B, int MAXT>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B <= 4 ? 6 : B <= 6 ? 5 : 4))) void gemv_tile_list_kernel(ListArgs a, int batch, uint32_t reciprocal)
 {
@@ -563,7 +580,7 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
     }
     const dim3 grid((tiles + R - 1) / R), block(64 * nw);
     auto launch = [&](auto ragged, auto skip) {
-        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, decltype(ragged)::value, WIDE, decltype(skip)::value>), grid, block, 0, stream,
+        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, decltype(ragged)::value, WIDE, decltype(skip)::value>), grid, block, nw * kExchangeBytes, stream,
                            a.slices, a.slice_bytes, a.lut, a.x, a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
     };
     // The octet that the last pass of a wave requests and drops (with 4096 columns on 4 waves one of five) is left out where several
@@ -605,7 +622,7 @@ template <int B> static hipError_t launch_tile_multi_b(MultiArgs &m, int total_t
     const int npairs = (m.K / (8 * kChunkSlots) + 1) / 2;
     int nw = m.K >= 12288 ? kMaxWaves : 4;
     if (nw > npairs) nw = npairs;
-    hipLaunchKernelGGL((gemv_tile_multi_kernel<B, 64 * kMaxWaves>), dim3(total_tiles), dim3(64 * nw), 0, stream, m, wave_reciprocal(nw));
+    hipLaunchKernelGGL((gemv_tile_multi_kernel<B, 64 * kMaxWaves>), dim3(total_tiles), dim3(64 * nw), nw * kExchangeBytes, stream, m, wave_reciprocal(nw));
     return hipGetLastError();
 }
 
@@ -631,7 +648,7 @@ hipError_t launch_matrix_tile_multi(const MultiArgs &a, int b, hipStream_t strea
 
 template <int B> static hipError_t launch_tile_list_b(const ListArgs &a, int total_tiles, int nw, int batch, hipStream_t stream)
 {
-    hipLaunchKernelGGL((gemv_tile_list_kernel<B, 512>), dim3(total_tiles), dim3(64 * nw), 0, stream, a, batch, wave_reciprocal(nw));
+    hipLaunchKernelGGL((gemv_tile_list_kernel<B, 512>), dim3(total_tiles), dim3(64 * nw), nw * kExchangeBytes, stream, a, batch, wave_reciprocal(nw));
     return hipGetLastError();
 }
 
