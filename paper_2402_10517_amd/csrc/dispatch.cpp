@@ -6,56 +6,54 @@
 namespace apgemv {
 
 // Whether the matrix-core kernel on tiles of 16 rows is the fastest for a call without tuning overrides.  Time of the kernels below
-// (batch 9 and more: in two passes) over its time, at M x K and b = 3 / 5 / 8, from 9270 calls at batch 3..8 (14 heights, 23 row
-// lengths) and 5500 at 9..16:
-//   batch 9       1024x4096 1.30/1.23/1.09  1024x8192 1.04/0.95/-  1024x20480 0.97/0.91/0.85  512x1024 1.80/1.26/1.47  2048x20480 1.32/1.23/1.15
-//   batch 16      1024x11008 1.37/1.25/1.08  1024x4192 1.27/1.02/0.93  4096x4096 1.58/1.62/1.68  28000x4192 3.59/3.16/2.36
-//   batch 5       1024x4096 1.08/0.92/0.77  2048x1024 1.25/0.92/0.94  2048x4192 1.13/0.95/0.78  2048x8224 1.16/0.95/0.79
-//                 3072x1024 1.32/0.96/1.01  3072x4096 1.60/1.38/1.18  5120x2208 1.38/1.22/0.95  28000x2208 2.52/2.02/1.50
-//   batch 3, 4    3072x4096 1.14/1.01/0.95  3072x8192 1.06/0.92/0.88  3072x11008 1.31/1.36/1.04  3072x16384 1.15/1.27/0.95
-//                 4096x4096 1.24/1.08/1.04  4096x8192 1.19/1.06/1.02  4096x11008 1.88/1.69/1.47  4096x12416 1.32/1.48/0.98
-//                 5120x4096 0.96/0.86/0.83  5120x8192 0.94/0.80/0.78  5120x11008 1.33/1.32/1.05  5120x13824 1.10/1.30/0.86
-//                 6144x4096 1.07/0.94/0.94  6144x8192 1.02/0.89/0.88  6144x11008 1.50/1.52/1.16  6144x13824 1.45/1.52/1.12
-//                 8192x4096 1.18/1.16/1.28  8192x4224 1.21/1.06/1.06  8192x8192 1.21/1.09/1.20  8192x16384 1.63/1.76/1.25
-//   batch 2       4096x4096 1.01/0.95/0.92  6144x11008 0.77/0.77/0.77
-// Where the ALU kernel is close, three things decide: the CUs that the last round of tiles leaves idle (5120 rows are 320 tiles, 1.25
-// rounds; `busy` below), the last span of the ALU kernel's rows (whole at 8192 and 16384 columns; at b >= 7 it gains again beyond 6
-// spans), and whether the row ends inside 128 columns (the last octet is then mostly padding, and the other kernel is the ALU kernel
-// at every height).  From another 11000 calls at batch 4, 6, 8 (24 heights 3072..12200, 34 row lengths), batch 4, b = 7: 5100 / 6300 /
-// 7600 x 8224 1.02/1.24/1.37  x 11808 0.90/1.04/1.17  x 15808 0.70/0.85/0.92  x 18432 0.98/1.20/1.28, 8600 / 10600 x 15808 0.76/0.90;
-// b = 8: 5700 / 6300 x 13056 1.06/1.14, 6700 / 7600 x 8192 0.89/1.01; b = 3: 5100 / 5400 x 8192 0.92/1.01, 8600 / 9800 x 7200 0.89/1.0;
-// batch 8, b = 8: 5100 / 6300 x 2208 0.93/1.08  x 7200 0.83/0.98  x 10400 0.98/1.21, 5700 x 2016 0.85.  b = 4 always wins there
-// (1.0 to 2.4).  What is left of calls slower than without this kernel: 1.3 % of them by 3 to 12 %.
+// over its time, at M x K, from 21 000 calls (37 heights 256..28672, 55 row lengths 256..28672, every b, batch 3, 4, 5, 8) and 5200 at batch 9, 16:
+//   batch 16      b = 3/5/8   512x1120 1.71/1.90/1.75  512x7200 1.28/1.22/1.00  2048x9312 1.53/1.63/1.41
+//   batch 9       512x1120 1.57/1.66/1.57  512x7200 1.08/1.02/0.87  2048x4640 1.40/1.40/1.32
+//   batch 5       512x2048 1.20/1.08/1.03  512x4096 1.10/0.98/0.91  1536x4096 1.43/1.30/1.22  1536x8192 1.31/1.08/1.00
+//                 1536x8224 1.24/0.99/0.98  1536x11008 1.53/1.21/1.15  3072x1024 1.35/1.10/1.17  3072x8192 1.75/1.51/1.36
+//   batch 3, 4    2048x4096 1.08/1.00/0.97  3072x4096 1.16/1.09/1.11  3072x5120 1.13/0.89/0.95  3072x11008 1.50/1.55/1.24
+//                 4096x4096 1.27/1.19/1.23  4096x8192 1.29/1.17/1.08  4096x8224 1.94/1.59/1.51  4352x4096 1.08/0.96/0.96
+//                 5120x8192 1.11/0.94/0.94  6144x4096 1.24/1.06/1.09  7168x8192 1.39/1.19/1.15  8192x3744 1.24/1.13/0.99
+//                 b = 4 2048x4096 1.18  1536x8224 1.15  3072x1024 0.94  3072x4096 1.27  4352x512 1.05
+// What decides where the other kernel is close: the CUs that the last round of tiles leaves idle (5120 rows are 320 tiles, 1.25 rounds;
+// `busy` below), whether the last octet of a row is partly padding (`whole`, `half`), how much of the call is building the tables (short
+// rows; by b), and the ALU kernel's second round of spans from 8193 columns on.  Over the 21 000 calls this rule loses 0.1 to 0.8 % (by b
+// and batch) against the better kernel of each, the rule of the tile kernel's earlier forms 2 to 10 %; 14 of them are 3 to 8 % slower than
+// by that rule.  512 rows stand for fewer: up to 1024 every tile has a CU to itself.
 static bool tile_pays(const GemvArgs &a)
 {
     const int groups = padded_rows(a.M) / kRowsPerGroup, b = a.b, K = a.K;
-    if (a.batch >= 9)
-        return groups >= 512 || (groups >= 256 && b <= 5 && K <= 12288 && (b <= 4 || K <= 4096 || a.batch >= 13)) ||
-               (groups >= 128 && K <= 1024);
-    if (a.batch < 3) return false;
+    if (a.batch >= 9) {
+        if (groups >= 320) return true;
+        return groups >= 64 && (a.batch >= 13 ? K <= 12288 || b <= 6 : K <= 5632 || (b <= 5 && K <= 12288));
+    }
     const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
     auto busy = [&](int percent) { return 100 * tiles >= percent * 256 * rounds; }; // of the CUs, over the rounds
-    const bool ragged = K % 128 != 0;
+    const bool whole = K % 256 == 0, half = K % 128 == 0;
+    if (a.batch < 3) return false;
     if (a.batch >= 5) {
-        if (groups < 512 || (groups < 768 && b > 3)) return false;
-        if (!ragged || groups >= 2048 || b < 7) return true;
-        if (K <= 2048) return K <= (b == 8 ? 1024 : 1536);
-        if (b == 7) return (K <= 2560 || (K > 4096 && K <= 5376) || (K > 8192 && K <= 12800)) || busy(65);
-        if (rounds == 1 && K > 4096 && K <= 8192) return busy(80);
-        return (K > 8192 && K <= 11264) || busy(65);
+        if (groups >= 640) return half || b < 7 || K <= 5632 || K > 8192 || rounds != 2 || busy(58);
+        if (groups >= 320) return K <= 4096 || b <= 4 || (K > 8192 && whole && (b <= 6 || K <= 12288));
+        if (!whole) return groups >= 64 && K <= (b == 3 ? 1536 : 512);
+        return groups >= 64 && K <= (b <= 4 ? 4096 : b == 6 ? 512 : 2048);
     }
-    if (groups >= 2048) {
-        if (b >= 7 && K > 8192 && ragged) return groups >= 3072 || (K <= 12288 && (K <= 9472 || busy(75)));
-        return K >= 8192 || K % 256 == 0 || (b == 3 && busy(78));
+    if (b == 3) {
+        if (groups >= 640) return whole || K <= 5632 || K > 8192 || rounds != 2 || busy(60);
+        if (groups >= 64 && K <= 512) return true;
+        return whole && groups >= 64 && (K <= 2048 || (groups >= 320 && (K <= 4096 || (K > 8192 && K <= 13824))));
     }
-    if (groups < 768 || K < 4096 || (K < 8192 && (K % 256 || b > 4))) return false;
-    if (b == 4) return true;
-    if (b == 3) return K > 8192 || busy(65);
-    if (b <= 6) return K > 8192 || busy(80);
-    if (K <= 8192) return busy(85);
-    if (rounds == 1) return (K <= 12288 && !ragged) || (busy(80) && (K <= 12288 || !ragged));
-    if (ragged) return K <= 12288 && (K <= 9472 || busy(75));
-    return K <= 12288 || busy(68);
+    if (b == 4) return groups >= 1088 || (groups >= 640 && K > 2048) || (groups >= 320 && (whole ? K > 2560 : K > 9216));
+    if (half && groups >= 2048) return true; // the kernel with in-wave exchange is the other one: 14336x640 b = 8 2.7, 8192x8320 b = 5 1.95
+    if (K <= 512) return groups >= (b >= 7 ? 320 : 1088);
+    if (K <= 2048) return whole ? groups >= (b <= 6 ? 1792 : 1088) : b == 5 && groups >= 2048 && K <= 1536;
+    if (groups < 640) return false;
+    if (rounds == 1) {
+        if (K <= 4096) return b != 6 || groups >= 896 || whole;
+        if (K <= 8192) return groups >= 896 && (whole || (b <= 6 && K > 5632));
+        return b <= 6 || K <= (groups > 768 ? 12288 : 11264) || half;
+    }
+    if (K <= 8192) return whole ? busy(69) : b <= 6 && busy(b == 5 ? 85 : 95);
+    return b <= 6 || K <= (whole || busy(68) ? 12288 : 11264) || busy(whole ? 60 : 85);
 }
 
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
@@ -84,11 +82,9 @@ hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
         return launch_gemv(pass, stream);
     }
     if (a.batch >= 2 && (forced || (!tuned && tile_pays(a)))) return launch_matrix_tile(a, stream);
-    // What is left for batch >= 2: the plain ALU kernel at batch 2 (fastest everywhere), on smaller matrices, and at batch 3, 4 on ragged
-    // rows below 8192 columns (b >= 4), where the matrix-core kernel with in-wave exchange takes those of a multiple of 128 columns
-    // from 2048 row groups on at b >= 6, from 4096 on at b = 4, 5 too (up to 24 % faster than the ALU kernels).  A handle with
-    // an option stays away from the tile kernel; for it the rules of the exchange kernel reach further: batch 5..8 at every b, and
-    // one wave per span at batch 3, 4.
+    // What is left for batch >= 2: the plain ALU kernel at batch 2 and on what tile_pays refuses.  The matrix-core kernel with in-wave
+    // exchange takes calls of handles with an option only: batch 5..8 at every b and, where every span has a wave, batch 3, 4 at b >= 6
+    // (b = 4, 5 from 4096 row groups on), from 2048 row groups on at K % 128 == 0.
     // variant: 1 = never the in-wave-exchange kernel, 3 = whenever the shape allows (tuning overrides).
     if (a.batch >= 2 && a.K % 128 == 0 && a.variant != 1) {
         const int groups = padded_rows(a.M) / kRowsPerGroup;

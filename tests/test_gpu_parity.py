@@ -888,3 +888,18 @@ def test_products_refuse_tensors_that_are_too_small(B, tiny):
             B.ap_gemm(pm, 4, xd, work=w)
         assert e.value.status == 5
     pm.close()
+
+
+@pytest.mark.parametrize("batch", [3, 5, 8, 9, 13, 16])
+def test_small_and_ragged_matrices_at_batches(B, batch):
+    # calls that go to the tile kernel by size alone (few tiles, short rows, rows that end inside 128 or 256 columns) and their
+    # neighbours that do not: both sides of the lines that the choice draws at 256, 1280, 2560 rows and 512, 2048, 4096 columns
+    shapes = [(256, 32), (253, 512), (257, 2048), (260, 2080), (1277, 512), (1280, 1632), (1281, 4096), (1285, 4128), (2557, 2592),
+              (2561, 2176)]
+    for k, (M, K) in enumerate(shapes):
+        idx, luts, x = inputs.make_case(41, M, K, batch=batch, salt=k)
+        pm = B.ap_pack(idx, luts)
+        rows = np.unique(np.r_[0:17, M // 2:M // 2 + 16, M - 17:M])
+        for b in ALL_BITS:
+            check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
+        pm.close()
