@@ -250,6 +250,40 @@ extern "C" ap_status ap_gemv_list(const ap_gemv_list_item *items, int count, voi
     return AP_OK;
 }
 
+// Items of a work list at batch 2 (checked), on the kernels of single calls and with their number of waves, so that the bits are the same:
+// list launches of the batch-1/2 kernel and, per number of waves, of the tile kernel.  A launch goes out when its list is full.
+class Batch2List {
+public:
+    explicit Batch2List(hipStream_t stream) : stream_(stream)
+    {
+        for (ListArgs &la : lists_) la.count = 0;
+    }
+    bool add(const ap_matrix *h, int b, const void *x_dev, void *y_dev)
+    {
+        GemvArgs a;
+        fill_args(h, b, &a);
+        const int waves = batch2_tile_waves(a), k = waves == 0 ? 0 : waves == 4 ? 1 : 2;
+        fill_list_item(h, b, x_dev, y_dev, &lists_[k].item[lists_[k].count++]);
+        return lists_[k].count < kMaxListItems || launch(k);
+    }
+    bool finish()
+    {
+        for (int k = 0; k < 3; ++k)
+            if (lists_[k].count > 0 && !launch(k)) return false;
+        return true;
+    }
+
+private:
+    bool launch(int k)
+    {
+        const hipError_t e = k == 0 ? launch_gemv_list(lists_[0], 2, stream_) : launch_matrix_tile_list(lists_[k], lists_[k].item[0].b, 2, stream_, 4 * k);
+        lists_[k].count = 0;
+        return e == hipSuccess;
+    }
+    hipStream_t stream_;
+    ListArgs lists_[3]; // batch-1/2 kernel, tile kernel with 4 and with 8 waves (b = 4)
+};
+
 extern "C" ap_status ap_gemv_list_batch(const ap_gemv_list_item *items, int count, int batch, void *stream)
 {
     if (batch == 1) return ap_gemv_list(items, count, stream);
@@ -261,22 +295,15 @@ extern "C" ap_status ap_gemv_list_batch(const ap_gemv_list_item *items, int coun
         if (s != AP_OK) return s;
     }
     if (batch == 2) {
-        // single calls at batch 2 run the batch-1/2 kernel: the items without a tuning override go into list
-        // launches of that kernel (any shapes and bit-widths together), the others run on their own
+        // the items without a tuning override go into list launches of the kernels that single calls run on: the batch-1/2
+        // kernel (any shapes and bit-widths together) or the tile kernel; the others run on their own
         auto plain = [](const ap_matrix *h) {
             return h->variant == AP_VARIANT_AUTO && h->waves_per_group == 0 && h->row_groups_per_wg < 0 && h->mfma_min_batch == 0;
         };
-        ListArgs la;
-        std::memset(&la, 0, sizeof(la));
-        for (int i = 0; i < count; ++i) {
-            if (!plain(items[i].h)) continue;
-            fill_list_item(items[i].h, items[i].b, items[i].x_dev, items[i].y_dev, &la.item[la.count++]);
-            if (la.count == kMaxListItems) {
-                if (launch_gemv_list(la, 2, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
-                la.count = 0;
-            }
-        }
-        if (la.count > 0 && launch_gemv_list(la, 2, static_cast<hipStream_t>(stream)) != hipSuccess) return AP_ERR_HIP;
+        Batch2List list(static_cast<hipStream_t>(stream));
+        for (int i = 0; i < count; ++i)
+            if (plain(items[i].h) && !list.add(items[i].h, items[i].b, items[i].x_dev, items[i].y_dev)) return AP_ERR_HIP;
+        if (!list.finish()) return AP_ERR_HIP;
         for (int i = 0; i < count; ++i) {
             if (plain(items[i].h)) continue;
             ap_status s = ap_gemv(items[i].h, items[i].b, items[i].x_dev, items[i].y_dev, batch, stream);
@@ -347,6 +374,7 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
     MultiArgs m;
     std::memset(&m, 0, sizeof(m));
     int total = 0;
+    bool any_tile = false; // at batch 2: a single call on that matrix runs on the tile kernel
     for (int i = 0; i < count; ++i) {
         GemvArgs a;
         ap_status s = fill_args(items[i].h, b, &a);
@@ -355,6 +383,7 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
         if (reinterpret_cast<uintptr_t>(items[i].x_dev) % 16 || reinterpret_cast<uintptr_t>(items[i].y_dev) % 2)
             return AP_ERR_INVALID_ARG;
         if (i > 0 && a.K != m.K) return AP_ERR_SHAPE;
+        any_tile = any_tile || (batch == 2 && batch2_tile_waves(a));
         m.K = a.K;
         m.slices[i] = a.slices;
         m.slice_bytes[i] = a.slice_bytes;
@@ -377,6 +406,12 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
     const bool tile = m.K % 256 == 0 &&
                       (first_variant == AP_VARIANT_TILE ||
                        (first_variant == AP_VARIANT_AUTO && ((batch >= 5 && total >= 1024) || (batch >= 3 && total >= 2048))));
+    if (batch == 2 && first_variant == AP_VARIANT_AUTO && any_tile) {
+        Batch2List list(static_cast<hipStream_t>(stream));
+        for (int i = 0; i < count; ++i)
+            if (!list.add(items[i].h, b, items[i].x_dev, items[i].y_dev)) return AP_ERR_HIP;
+        return list.finish() ? AP_OK : AP_ERR_HIP;
+    }
     const hipError_t e = tile ? launch_matrix_tile_multi(m, b, static_cast<hipStream_t>(stream))
                               : launch_gemv_multi(m, b, total, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? AP_OK : AP_ERR_HIP;

@@ -15,6 +15,8 @@ namespace apgemv {
 //                 4096x4096 1.27/1.19/1.23  4096x8192 1.29/1.17/1.08  4096x8224 1.94/1.59/1.51  4352x4096 1.08/0.96/0.96
 //                 5120x8192 1.11/0.94/0.94  6144x4096 1.24/1.06/1.09  7168x8192 1.39/1.19/1.15  8192x3744 1.24/1.13/0.99
 //                 b = 4 2048x4096 1.18  1536x8224 1.15  3072x1024 0.94  3072x4096 1.27  4352x512 1.05
+//   in us: 4096x4096 b = 8 batch 4 7.66 / 6.16, 2048x4096 b = 5 batch 8 7.14 / 5.52, 1536x11008 b = 4 batch 8 11.54 / 8.02, 14336x640 b = 7
+//   batch 4 17.7 / 6.1, 4096x8224 b = 5 batch 3 16.3 / 10.3, 512x1120 b = 5 batch 16 9.4 / 5.2
 // What decides where the other kernel is close: the CUs that the last round of tiles leaves idle (5120 rows are 320 tiles, 1.25 rounds;
 // `busy` below), whether the last octet of a row is partly padding (`whole`, `half`), how much of the call is building the tables (short
 // rows; by b), and the ALU kernel's second round of spans from 8193 columns on.  Over the 21 000 calls this rule loses 0.1 to 0.8 % (by b
@@ -30,7 +32,13 @@ static bool tile_pays(const GemvArgs &a)
     const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
     auto busy = [&](int percent) { return 100 * tiles >= percent * 256 * rounds; }; // of the CUs, over the rounds
     const bool whole = K % 256 == 0, half = K % 128 == 0;
-    if (a.batch < 3) return false;
+    // Batch 2: large products in pairs of centroids (b = 4, where the lookups of the ALU kernel cost most): 8192x8192 12.2 -> 9.4 us, 28672x8192
+    // 36.7 -> 28.9, ALU kernel over tile kernel 13824x5120 1.16, 14336x12288 1.28, 4096x16384 1.35, 8192x28672 1.61, but 5120x13824 1.01
+    // (62 % busy).  Smaller single calls would gain as well (11008x4096 9.3 -> 7.9, 4096x11008 9.9 -> 7.7), but mixed work lists of them
+    // pay for the further launches: the 18 products of three 7B shapes at every b 103 -> 109.  b = 3 is level up to 8192 columns, b = 5
+    // to 8 within 5 % or behind.
+    if (a.batch == 2) return b == 4 && whole && (long long)a.M * K >= 1 << 26 && busy(69);
+    if (a.batch < 2) return false;
     if (a.batch >= 5) {
         if (groups >= 640) return half || b < 7 || K <= 5632 || K > 8192 || rounds != 2 || busy(58);
         if (groups >= 320) return K <= 4096 || b <= 4 || (K > 8192 && whole && (b <= 6 || K <= 12288));
@@ -54,6 +62,14 @@ static bool tile_pays(const GemvArgs &a)
     }
     if (K <= 8192) return whole ? busy(69) : b <= 6 && busy(b == 5 ? 85 : 95);
     return b <= 6 || K <= (whole || busy(68) ? 12288 : 11264) || busy(whole ? 60 : 85);
+}
+
+int batch2_tile_waves(const GemvArgs &a)
+{
+    GemvArgs two = a;
+    two.batch = 2;
+    two.variant = two.waves_per_group = 0;
+    return tile_pays(two) ? tile_call_waves(two) : 0;
 }
 
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
@@ -82,7 +98,7 @@ hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)
         return launch_gemv(pass, stream);
     }
     if (a.batch >= 2 && (forced || (!tuned && tile_pays(a)))) return launch_matrix_tile(a, stream);
-    // What is left for batch >= 2: the plain ALU kernel at batch 2 and on what tile_pays refuses.  The matrix-core kernel with in-wave
+    // What is left for batch >= 2: the plain ALU kernel on what tile_pays refuses.  The matrix-core kernel with in-wave
     // exchange takes calls of handles with an option only: batch 5..8 at every b and, where every span has a wave, batch 3, 4 at b >= 6
     // (b = 4, 5 from 4096 row groups on), from 2048 row groups on at K % 128 == 0.
     // variant: 1 = never the in-wave-exchange kernel, 3 = whenever the shape allows (tuning overrides).

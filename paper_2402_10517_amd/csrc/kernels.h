@@ -160,7 +160,11 @@ hipError_t launch_gemv_multi(const MultiArgs &a, int b, int total_groups, hipStr
 hipError_t launch_matrix_tile_multi(const MultiArgs &a, int b, hipStream_t stream);
 // a work list on that kernel: every item at bit-width b, K % 256 == 0, all rows in the same class of length
 // (below / from 12288 columns); group_begin is filled in here
-hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream);
+// nw: waves per workgroup, 0 = those of the class
+hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream, int nw = 0);
+// Waves per tile of a single call at batch 2 without options that goes to that kernel (K % 256 == 0 then, b = 4, 4 or 8 waves), 0 if it
+// goes to the batch-1/2 kernel: work lists give the same bits only on the same kernel with as many waves
+int batch2_tile_waves(const GemvArgs &a);
 hipError_t launch_dequantize(const GemvArgs &a, hipStream_t stream);
 hipError_t launch_probe_read(const void *dev_buf, size_t bytes, hipStream_t stream);
 hipError_t launch_probe_issue(int kind, int passes, hipStream_t stream);

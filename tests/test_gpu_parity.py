@@ -903,3 +903,33 @@ def test_small_and_ragged_matrices_at_batches(B, batch):
         for b in ALL_BITS:
             check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
         pm.close()
+
+
+def test_batch_2_on_the_tile_kernel_same_bits_in_lists_and_fused_launches(B):
+    # b = 4 at batch 2 goes to the tile kernel from 2^26 weights on (4 and 8 waves, one and two tiles per workgroup); list and fused
+    # launches of such matrices, among others that stay on the batch-1/2 kernel, give the bits of single calls
+    import torch
+    shapes = [(8192, 8192), (8192, 7936), (4096, 16384), (6150, 11008), (16384, 4096), (8205, 16640), (2050, 4096), (70, 2048 + 96)]
+    mats = []
+    for k, (M, K) in enumerate(shapes):
+        idx, luts, x = inputs.make_case(42, M, K, batch=2, salt=k, bit_widths=[4, 5], sigma=0.01)
+        mats.append((idx, luts, x, B.ap_pack(idx, luts), torch.from_numpy(x).cuda()))
+    single = {}
+    for k, (idx, luts, x, pm, xd) in enumerate(mats):
+        rows = np.unique(np.r_[0:20, pm.M // 2:pm.M // 2 + 16, pm.M - 20:pm.M])
+        for b in (4, 5):
+            single[k, b] = y = B.ap_gemv(pm, b, xd)
+            check_against_oracle(y.cpu().numpy(), idx, luts[b], b, x, rows=rows)
+    picks = [(k, b) for b in (4, 5, 4) for k in range(len(mats))] + [(0, 4)] * 34   # more than one launch's worth
+    out = [torch.full((2, mats[k][3].M), -5.0, dtype=torch.float16, device="cuda") for k, b in picks]
+    B.ap_gemv_list_batch([(mats[k][3], b, mats[k][4], y) for (k, b), y in zip(picks, out)], 2)
+    for (k, b), y in zip(picks, out):
+        assert torch.equal(y.view(torch.int16), single[k, b].view(torch.int16)), (shapes[k], b)
+    out = [torch.full((2, shapes[k][0]), -5.0, dtype=torch.float16, device="cuda") for k in range(len(mats))]
+    for b in (4, 5):
+        for group in ([4, 6], [0], [6]):                             # equal row length
+            B.ap_gemv_multi([(mats[k][3], mats[k][4], out[k]) for k in group], b)
+            for k in group:
+                assert torch.equal(out[k].view(torch.int16), single[k, b].view(torch.int16)), (shapes[k], b)
+    for m in mats:
+        m[3].close()
