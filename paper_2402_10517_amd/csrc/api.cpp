@@ -251,7 +251,7 @@ extern "C" ap_status ap_gemv_list(const ap_gemv_list_item *items, int count, voi
 }
 
 // Items of a work list at batch 2 (checked), on the kernels of single calls and with their number of waves, so that the bits are the same:
-// list launches of the batch-1/2 kernel and, per number of waves, of the tile kernel.  A launch goes out when its list is full.
+// list launches of the batch-1/2 kernel and, per class of row length, of the tile kernel.  A launch goes out when its list is full.
 class Batch2List {
 public:
     explicit Batch2List(hipStream_t stream) : stream_(stream)
@@ -262,7 +262,7 @@ public:
     {
         GemvArgs a;
         fill_args(h, b, &a);
-        const int waves = batch2_tile_waves(a), k = waves == 0 ? 0 : waves == 4 ? 1 : 2;
+        const int k = !batch2_tile_pays(a) ? 0 : a.K < 12288 ? 1 : 2;
         fill_list_item(h, b, x_dev, y_dev, &lists_[k].item[lists_[k].count++]);
         return lists_[k].count < kMaxListItems || launch(k);
     }
@@ -276,12 +276,12 @@ public:
 private:
     bool launch(int k)
     {
-        const hipError_t e = k == 0 ? launch_gemv_list(lists_[0], 2, stream_) : launch_matrix_tile_list(lists_[k], lists_[k].item[0].b, 2, stream_, 4 * k);
+        const hipError_t e = k == 0 ? launch_gemv_list(lists_[0], 2, stream_) : launch_matrix_tile_list(lists_[k], 4, 2, stream_);
         lists_[k].count = 0;
         return e == hipSuccess;
     }
     hipStream_t stream_;
-    ListArgs lists_[3]; // batch-1/2 kernel, tile kernel with 4 and with 8 waves (b = 4)
+    ListArgs lists_[3]; // batch-1/2 kernel; tile kernel (b = 4), rows below and from 12288 columns
 };
 
 extern "C" ap_status ap_gemv_list_batch(const ap_gemv_list_item *items, int count, int batch, void *stream)
@@ -383,7 +383,7 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
         if (reinterpret_cast<uintptr_t>(items[i].x_dev) % 16 || reinterpret_cast<uintptr_t>(items[i].y_dev) % 2)
             return AP_ERR_INVALID_ARG;
         if (i > 0 && a.K != m.K) return AP_ERR_SHAPE;
-        any_tile = any_tile || (batch == 2 && batch2_tile_waves(a));
+        any_tile = any_tile || (batch == 2 && batch2_tile_pays(a));
         m.K = a.K;
         m.slices[i] = a.slices;
         m.slice_bytes[i] = a.slice_bytes;

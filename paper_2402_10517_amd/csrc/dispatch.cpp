@@ -32,12 +32,7 @@ static bool tile_pays(const GemvArgs &a)
     const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
     auto busy = [&](int percent) { return 100 * tiles >= percent * 256 * rounds; }; // of the CUs, over the rounds
     const bool whole = K % 256 == 0, half = K % 128 == 0;
-    // Batch 2: large products in pairs of centroids (b = 4, where the lookups of the ALU kernel cost most): 8192x8192 12.2 -> 9.4 us, 28672x8192
-    // 36.7 -> 28.9, ALU kernel over tile kernel 13824x5120 1.16, 14336x12288 1.28, 4096x16384 1.35, 8192x28672 1.61, but 5120x13824 1.01
-    // (62 % busy).  Smaller single calls would gain as well (11008x4096 9.3 -> 7.9, 4096x11008 9.9 -> 7.7), but mixed work lists of them
-    // pay for the further launches: the 18 products of three 7B shapes at every b 103 -> 109.  b = 3 is level up to 8192 columns, b = 5
-    // to 8 within 5 % or behind.
-    if (a.batch == 2) return b == 4 && whole && (long long)a.M * K >= 1 << 26 && busy(69);
+    if (a.batch == 2) return batch2_tile_pays(a);
     if (a.batch < 2) return false;
     if (a.batch >= 5) {
         if (groups >= 640) return half || b < 7 || K <= 5632 || K > 8192 || rounds != 2 || busy(58);
@@ -62,14 +57,6 @@ static bool tile_pays(const GemvArgs &a)
     }
     if (K <= 8192) return whole ? busy(69) : b <= 6 && busy(b == 5 ? 85 : 95);
     return b <= 6 || K <= (whole || busy(68) ? 12288 : 11264) || busy(whole ? 60 : 85);
-}
-
-int batch2_tile_waves(const GemvArgs &a)
-{
-    GemvArgs two = a;
-    two.batch = 2;
-    two.variant = two.waves_per_group = 0;
-    return tile_pays(two) ? tile_call_waves(two) : 0;
 }
 
 hipError_t launch_gemv(const GemvArgs &a, hipStream_t stream)

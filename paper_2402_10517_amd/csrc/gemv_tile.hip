@@ -567,8 +567,6 @@ static int tile_waves(const GemvArgs &a, int tiles, int npairs, bool wide)
     return nw < 4 && helpers ? 4 : nw;
 }
 
-int tile_call_waves(const GemvArgs &a) { return tile_waves(a, (a.M + 15) / 16, ((a.K + 255) / 256 + 1) / 2, false); }
-
 template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArgs &a, hipStream_t stream)
 {
     constexpr int kMaxWaves = 8;
@@ -654,7 +652,7 @@ template <int B> static hipError_t launch_tile_list_b(const ListArgs &a, int tot
     return hipGetLastError();
 }
 
-hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream, int waves)
+hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream)
 {
     int total = 0, min_pairs = 1 << 30;
     bool long_rows = false;
@@ -668,7 +666,6 @@ hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t st
     for (int i = a.count; i < kMaxListItems; ++i) a.group_begin[i] = 0x7fffffff;
     int nw = long_rows ? 8 : 4; // as in single calls on this kernel by option; no more waves than the shortest row has pairs of octets
     if (nw > min_pairs) nw = min_pairs;
-    if (waves) nw = waves;
     switch (b) {
     case 3: return launch_tile_list_b<3>(a, total, nw, batch, stream);
     case 4: return launch_tile_list_b<4>(a, total, nw, batch, stream);

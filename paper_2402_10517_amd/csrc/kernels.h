@@ -123,6 +123,19 @@ inline bool static_dense_pays(const GemvArgs &a)
     return a.K <= (a.M <= 200 ? 64 : 32) && a.M <= 768 && waves * a.K <= 1 << 16;
 }
 
+// Whether a product at batch 2 without options runs on the kernel on tiles of 16 rows rather than on the batch-1/2 kernel, in a single call as in
+// a list or fused launch (which give its bits: rows of 3072 columns and more have 4 waves, from 12288 on 8, in both).  Large
+// products in pairs of centroids (b = 4, where the lookups of the ALU kernel cost most): 8192x8192 12.2 -> 9.4 us, 13824x5120 14.0 -> 11.4,
+// 28672x8192 37.9 -> 28.8, ALU kernel over tile kernel 14336x12288 1.28, 4096x16384 1.35, 8192x28672 1.61, but 5120x13824 1.01 (320 tiles,
+// 62 % of two rounds) and 28672x2048 0.94.  Smaller single calls would gain as well (11008x4096 9.3 -> 7.9, 4096x11008 9.9 -> 7.7), but mixed
+// work lists of them pay for the further launches: the 18 products of three 7B shapes at every b 103 -> 109.  b = 3 is level
+// up to 8192 columns, b = 5 to 8 within 5 % or behind.
+inline bool batch2_tile_pays(const GemvArgs &a)
+{
+    const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
+    return a.b == 4 && a.K % 256 == 0 && a.K >= 3072 && (long long)a.M * a.K >= 1 << 26 && 100 * tiles >= 69 * 256 * rounds;
+}
+
 constexpr int kMaxMulti = 8;
 struct MultiArgs { // passed by value as the kernel argument of a fused launch
     const uint8_t *slices[kMaxMulti];
@@ -160,11 +173,7 @@ hipError_t launch_gemv_multi(const MultiArgs &a, int b, int total_groups, hipStr
 hipError_t launch_matrix_tile_multi(const MultiArgs &a, int b, hipStream_t stream);
 // a work list on that kernel: every item at bit-width b, K % 256 == 0, all rows in the same class of length
 // (below / from 12288 columns); group_begin is filled in here
-// nw: waves per workgroup, 0 = those of the class
-hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream, int nw = 0);
-// Waves per tile of a single call at batch 2 without options that goes to that kernel (K % 256 == 0 then, b = 4, 4 or 8 waves), 0 if it
-// goes to the batch-1/2 kernel: work lists give the same bits only on the same kernel with as many waves
-int batch2_tile_waves(const GemvArgs &a);
+hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t stream);
 hipError_t launch_dequantize(const GemvArgs &a, hipStream_t stream);
 hipError_t launch_probe_read(const void *dev_buf, size_t bytes, hipStream_t stream);
 hipError_t launch_probe_issue(int kind, int passes, hipStream_t stream);

@@ -11,7 +11,6 @@ hipError_t launch_quad(const GemvArgs &a, hipStream_t stream);                //
 hipError_t launch_matrix_row_per_lane(const GemvArgs &a, hipStream_t stream); // gemv_mfma_kernel (batch >= 3, K % 128 == 0; by option)
 hipError_t launch_matrix_exchange(const GemvArgs &a, hipStream_t stream);     // gemv_xmfma_kernel (batch >= 2, K % 128 == 0)
 hipError_t launch_matrix_tile(const GemvArgs &a, hipStream_t stream);         // gemv_tile_kernel (batch 2..16)
-int tile_call_waves(const GemvArgs &a);                                       // waves per workgroup of launch_matrix_tile, batch 2..8, no option set
 hipError_t launch_gemm_fused(const GemvArgs &a, hipStream_t stream);          // gemm_fused_kernel (gemm_fused_ok)
 
 } // namespace apgemv
