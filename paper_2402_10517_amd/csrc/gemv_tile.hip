@@ -526,9 +526,14 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint
 #pragma unroll
     for (int i = 1; i < kMaxMulti; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) m = i;
-    gemv_tile_body<B, 1, MAXT, false, false, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
+    gemv_tile_body<B, 1, MAXT, false, false, true>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
                                (int)blockIdx.x - a.group_begin[m], reciprocal);
 }
+
+// List and fused launches leave the octet that a wave's last pass drops unrequested (SKIP; single calls: launch_tile_r), us with it / without:
+// 7B decoder layer b = 3/5/8 batch 4 25.9/39.3/53.1 -> 24.9/38.2/49.0, batch 8 31.6/43.7/58.3 -> 29.3/41.0/53.6, 6 of 8192 x 2816 b = 8 batch 8
+// 43.5 -> 37.4, 2 of 11008 x 4096 b = 4 batch 8 15.6 -> 14.9, 8 of 2048 x 2048 b = 3 batch 4 7.4 -> 7.5 (a few scalar instructions ahead of
+// the loads).
 
 // A work list of matrices of any shapes (rows of one class of length) at one bit-width and batch.  The bound asks for the registers
 // that the single instances take by themselves: without it these settle at 107 / 108 / 130 at b = 3 / 4 / 5 (4 / 4 / 3 waves per SIMD
@@ -541,7 +546,7 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B <= 4 ? 6
     for (int i = 1; i < kMaxListItems; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) it = i;
     const ListItem &I = a.item[it];
-    gemv_tile_body<B, 1, MAXT, false, false, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
+    gemv_tile_body<B, 1, MAXT, false, false, true>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
                                              reciprocal);
 }
 
