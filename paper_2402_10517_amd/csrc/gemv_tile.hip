@@ -621,12 +621,23 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
     return wide_two ? launch_tile_r<B, 2, true>(a, stream) : launch_tile_r<B, 1, true>(a, stream);
 }
 
+// Waves per workgroup of a list or fused launch whose shortest row has min_pairs pairs of octets: as single calls on this kernel by option, but
+// with the smaller tables (b = 5, 6, 7) no more than that row has pairs.  At b = 3, 4, 8 waves without columns help to build the tables
+// (a sum of zero waves more: the bits are the same).  One wave per pair / with helpers, us: 8 of
+// 8192 x 512 batch 4 b = 3 14.7 / 12.1, b = 4 56.3 / 16.7, b = 8 28.4 / 22.4, 8 of 8192 x 1024 b = 4 41.6 / 18.4, 6 of 4096 x 1536 16.8 / 10.3, 4 of
+// 2048 x 512 15.0 / 6.2; b = 8 with four tiles per CU, 8 of 2048 x 1024 7.4 / 8.2: not there, as in single calls (tile_waves).
+static int launch_waves(int b, bool long_rows, int min_pairs, int tiles)
+{
+    const int nw = long_rows ? 8 : 4;
+    const bool helpers = b <= 4 || (b == 8 && (tiles < 768 || tiles > 1024));
+    return nw > min_pairs && !helpers ? min_pairs : nw;
+}
+
 template <int B> static hipError_t launch_tile_multi_b(MultiArgs &m, int total_tiles, hipStream_t stream)
 {
     constexpr int kMaxWaves = 8;
     const int npairs = (m.K / (8 * kChunkSlots) + 1) / 2;
-    int nw = m.K >= 12288 ? kMaxWaves : 4;
-    if (nw > npairs) nw = npairs;
+    const int nw = launch_waves(B, m.K >= 12288, npairs, total_tiles);
     hipLaunchKernelGGL((gemv_tile_multi_kernel<B, 64 * kMaxWaves>), dim3(total_tiles), dim3(64 * nw), nw * kExchangeBytes, stream, m, wave_reciprocal(nw));
     return hipGetLastError();
 }
@@ -669,8 +680,7 @@ hipError_t launch_matrix_tile_list(ListArgs &a, int b, int batch, hipStream_t st
         long_rows = a.item[i].K >= 12288;
     }
     for (int i = a.count; i < kMaxListItems; ++i) a.group_begin[i] = 0x7fffffff;
-    int nw = long_rows ? 8 : 4; // as in single calls on this kernel by option; no more waves than the shortest row has pairs of octets
-    if (nw > min_pairs) nw = min_pairs;
+    const int nw = launch_waves(b, long_rows, min_pairs, total);
     switch (b) {
     case 3: return launch_tile_list_b<3>(a, total, nw, batch, stream);
     case 4: return launch_tile_list_b<4>(a, total, nw, batch, stream);

@@ -933,3 +933,21 @@ def test_batch_2_on_the_tile_kernel_same_bits_in_lists_and_fused_launches(B):
                 assert torch.equal(out[k].view(torch.int16), single[k, b].view(torch.int16)), (shapes[k], b)
     for m in mats:
         m[3].close()
+
+
+@pytest.mark.parametrize("b", ALL_BITS)
+def test_short_rows_in_list_and_fused_launches(B, b):
+    # rows of 1, 2 and 3 pairs of octets, where a launch has waves without columns at b = 3, 4, 8; total rows on both sides of what a list
+    # launch takes (1024 groups) and of the 768..1024 tiles at b = 8
+    import torch
+    for K, counts in ((256, (4, 7)), (768, (4,)), (1280, (4,))):
+        idx, luts, x = inputs.make_case(43, 2050, K, batch=5, bit_widths=[b], sigma=0.01)
+        pm, xd = B.ap_pack(idx, luts), torch.from_numpy(x).cuda()
+        for count in counts:
+            out = [torch.full((5, pm.M), -5.0, dtype=torch.float16, device="cuda") for _ in range(2 * count)]
+            B.ap_gemv_list_batch([(pm, b, xd, y) for y in out[:count]], 5)
+            B.ap_gemv_multi([(pm, xd, y) for y in out[count:]], b)
+            check_against_oracle(out[0].cpu().numpy(), idx, luts[b], b, x)
+            for y in out[1:]:
+                assert torch.equal(y.view(torch.int16), out[0].view(torch.int16))
+        pm.close()
