@@ -141,6 +141,13 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(x), 0, (uint32_t)batch * (uint32_t)K * 2u, kBufferRsrcWord3);
     constexpr int kXSets = WIDE ? 2 : 1;
+    // WIDE: one set of activation registers; a run's are loaded again, for the octet after, once its last tile has used them.  With two
+    // sets as at batch 3 to 8 the registers of one tile cost a wave per SIMD at b = 5 to 8 (134 to 170 instead of 103 to 122), of two tiles
+    // at b = 4 to 7 (172 to 255 instead of 130 to 166).  Two sets / one, us: 22589 x 2560 b = 5 batch 10 19.9 / 15.6, 24352 x 1920 b = 6
+    // batch 9 19.3 / 16.9, 10816 x 2240 b = 5 batch 13 12.8 / 10.0, 11008 x 4096 b = 4 batch 16 10.6 / 10.1, 28672 x 8192 b = 5 47.8 /
+    // 44.6, but b = 4 37.1 / 37.9 and 8192 x 8192 b = 5 batch 9 16.8 / 17.3.
+    constexpr bool kRefill = WIDE;
+    constexpr int kNoMemory = 0x38f; // of sched_barrier: what may move across, all but loads and stores of memory
     const int xn = i >> 1, xc = 4 * (i & 1) + kg;
     uint32_t xoff_lane[kXSets];
 #pragma unroll
@@ -151,7 +158,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     int lanes = xc | lc << 8; // the chunks that this lane loads, for ragged octets
     // Two ragged tiles at 3 bits keep within 128 registers (4 waves per SIMD) only if what is cheap to compute again is not kept, and if the
     // second tile's exchange does not move up: with 129 registers 25000 x 288 batch 3 takes 8.5 us instead of 6.2, x 12320 52 instead of 42.
-    constexpr bool kTight = B == 3 && R == 2 && RAG;
+    constexpr bool kTight = B == 3 && R == 2 && RAG && !WIDE;
     float4_t acc[R][kXSets][2]; // one accumulator per quad of an octet (and 8 batch rows): independent chains of matrix instructions
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
@@ -168,18 +175,27 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     // RAG instances, the sums of before it in the others (0 to 1 % of the call; a branch around its
     // arithmetic cost 7 % on rows without such an octet: b = 3, 4 then schedule with 78 registers
     // instead of 107).
-    auto issue = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B]) {
+    struct XLoads { // the activations of an octet; run t at base + t * step
+        uint32_t lane[kXSets], base, step;
+    };
+    auto load_run = [&](const XLoads &l, int t, u32x4 (&X)[kXSets][4]) {
+#pragma unroll
+        for (int q = 0; q < kXSets; ++q) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, l.lane[q], l.base + (uint32_t)t * l.step, 0);
+    };
+    auto issue = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B], auto with_x) {
         const int span = o >> 3, oi = o & 7;
         const int rem = chunks - span * kSpanLanes;
         const int nl = rem < kSpanLanes ? rem : kSpanLanes;
-        const uint32_t xs = (uint32_t)span * (kSpanCols * 2u) + (uint32_t)oi * 128u;
         const int left = chunks - o * 8; // chunks of this octet and beyond
         if constexpr (kTight) asm volatile("" : "+v"(lanes));
+        XLoads l;
 #pragma unroll
-        for (int q = 0; q < kXSets; ++q) {
-            const uint32_t xoff = real && (!RAG || (lanes & 7) < left) ? xoff_lane[q] : 0x80000000u;
+        for (int q = 0; q < kXSets; ++q) l.lane[q] = real && (!RAG || (lanes & 7) < left) ? xoff_lane[q] : 0x80000000u;
+        l.base = (uint32_t)span * (kSpanCols * 2u) + (uint32_t)oi * 128u;
+        l.step = (uint32_t)(16 * nl);
+        if constexpr (decltype(with_x)::value) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) X[q][t] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff, xs + (uint32_t)(t * 16 * nl), 0);
+            for (int t = 0; t < 4; ++t) load_run(l, t, X);
         }
         // no records, no memory access (the addresses are valid all the same)
         const uint32_t records = SKIP ? (uint32_t)__builtin_amdgcn_readfirstlane(real ? -1 : 0) : 0xffffffffu;
@@ -196,8 +212,10 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                 for (int half = 0; half < 2; ++half)
                     Q[tile][half][s] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, soff_lane(tile, half) - back,
                                                                             soct + (uint32_t)s * (uint32_t)slice_bytes, kBufferNonTemporal);
+        return l;
     };
-    auto compute = [&](const u32x4 (&X)[kXSets][4], const uint32_t (&Q)[R][2][B], int o) {
+    // `used(t)`: after the last tile has used the activations of run t
+    auto compute = [&](const u32x4 (&X)[kXSets][4], const uint32_t (&Q)[R][2][B], int o, auto &&used) {
         if constexpr (kTight) asm volatile("" : "+v"(put0), "+v"(get0));
         const int put[2] = {put0, put0 ^ 16}, get[2] = {get0, (get0 ^ 16) + 64}; // [half of the row groups], [quad]
         const uint32_t keep[2] = {kg < chunks - o * 8 ? 0xffffffffu : 0u, kg + 4 < chunks - o * 8 ? 0xffffffffu : 0u}; // RAG
@@ -294,6 +312,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                     acc[tile][q][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, X[q][t]),
                                                                              acc[tile][q][1], 0, 0, 0);
                 }
+                if (tile == R - 1) used(t);
             }
         }
     };
@@ -328,7 +347,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                 const int row = row0 + r < M ? row0 + r : M - 1;
                 reinterpret_cast<uint32_t *>(nat)[r * kNatDwords + (e & 7)] = reinterpret_cast<const uint32_t *>(lut + (size_t)row * 16)[e & 7];
             }
-            issue(2 * p, true, XA, QA);
+            issue(2 * p, true, XA, QA, std::true_type());
             __syncthreads();
             auto build = [&](auto log2_parts) {
                 constexpr int L = decltype(log2_parts)::value;
@@ -364,7 +383,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                 const int row = row0 + r < M ? row0 + r : M - 1;
                 reinterpret_cast<uint32_t *>(nat)[r * kNatDwords + (e & 3)] = reinterpret_cast<const uint32_t *>(lut + (size_t)row * 8)[e & 3];
             }
-            issue(2 * p, true, XA, QA);
+            issue(2 * p, true, XA, QA, std::true_type());
             __syncthreads();
             auto build = [&](auto log2_parts) {
                 constexpr int L = decltype(log2_parts)::value;
@@ -431,7 +450,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
             for (int tile = 0; tile < R; ++tile)
 #pragma unroll
                 for (int j = 0; j < kBurst; ++j) asm volatile("" : "+v"(v[tile][j]));
-            issue(2 * p, true, XA, QA);
+            issue(2 * p, true, XA, QA, std::true_type());
 #pragma unroll
             for (int tile = 0; tile < R; ++tile) {
 #pragma unroll
@@ -454,19 +473,29 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     for (; p < p1; ++p) {
         const bool second = 2 * p + 1 < nocts;
         const int o1 = second ? 2 * p + 1 : 2 * p;
-        issue(o1, second, XB, QB);
-        __builtin_amdgcn_sched_barrier(0); // keep the loads ahead of the arithmetic they overlap with
-        compute(XA, QA, 2 * p);
-        issue(p + 1 < p1 ? 2 * p + 2 : 2 * p, !SKIP || p + 1 < p1, XA, QA);
-        __builtin_amdgcn_sched_barrier(0);
+        // the loads of octet o: its activations into the other set ahead of the arithmetic, or (WIDE) run by run into the one that is in use
+        auto ahead = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B]) {
+            const XLoads l = issue(o, real, X, Q, std::bool_constant<!kRefill>());
+            __builtin_amdgcn_sched_barrier(0); // keep the loads ahead of the arithmetic they overlap with
+            return [&XA, &load_run, l](int t) {
+                if constexpr (kRefill) {
+                    __builtin_amdgcn_sched_barrier(kNoMemory);
+                    load_run(l, t, XA);
+                    __builtin_amdgcn_sched_barrier(kNoMemory);
+                }
+            };
+        };
+        u32x4 (&X1)[kXSets][4] = kRefill ? XA : XB;
+        compute(XA, QA, 2 * p, ahead(o1, second, XB, QB));
+        auto next = ahead(p + 1 < p1 ? 2 * p + 2 : 2 * p, !SKIP || p + 1 < p1, XA, QA);
         if constexpr (RAG) {
-            compute(XB, QB, 2 * p + 1); // the padding octet has no chunks: all centroids masked
+            compute(X1, QB, 2 * p + 1, next); // the padding octet has no chunks: all centroids masked
         } else {
 #pragma unroll
             for (int tile = 0; tile < R; ++tile)
 #pragma unroll
                 for (int q = 0; q < kXSets; ++q) { before[tile][q][0] = acc[tile][q][0]; before[tile][q][1] = acc[tile][q][1]; }
-            compute(XB, QB, o1);
+            compute(X1, QB, o1, next);
         }
     }
     if (!RAG && (nocts & 1) && p1 == npairs) { // the padding octet does not count

@@ -951,3 +951,16 @@ def test_short_rows_in_list_and_fused_launches(B, b):
             for y in out[1:]:
                 assert torch.equal(y.view(torch.int16), out[0].view(torch.int16))
         pm.close()
+
+
+@pytest.mark.parametrize("batch", [9, 16])
+@pytest.mark.parametrize("M,K", [(250, 12288 + 256), (1029, 8192 + 64), (7190, 4352), (12305, 6144 + 96), (20481, 1792)])
+def test_nine_to_sixteen_batch_rows_over_several_passes(B, M, K, batch):
+    # waves that load activations again for a second, third and later octet: even and odd numbers of octets, ragged last ones, one tile per
+    # workgroup and (from 449 tiles on) two
+    idx, luts, x = inputs.make_case(46, M, K, batch=batch, sigma=0.01)
+    pm = B.ap_pack(idx, luts)
+    rows = np.unique(np.r_[0:20, M // 2:M // 2 + 16, M - 20:M])
+    for b in ALL_BITS:
+        check_against_oracle(run_gemv(pm, b, x), idx, luts[b], b, x, rows=rows)
+    pm.close()
