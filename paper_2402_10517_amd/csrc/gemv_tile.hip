@@ -322,7 +322,15 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     const int p1 = first_pair(npairs, wave + 1, reciprocal);
     u32x4 XA[kXSets][4], XB[kXSets][4];
     uint32_t QA[R][2][B], QB[R][2][B];
-    int p = first_pair(npairs, wave, reciprocal); // < npairs (a wave without pairs loads one and drops it)
+    int p = first_pair(npairs, wave, reciprocal); // < npairs, also for a wave without pairs
+    // The wave's first octet.  Waves without pairs (short rows at b = 3, 4, 8: they help to build the tables) would load and drop one, in the way
+    // of the others at the vector L1: at b = 3, 4 they leave it out, at b = 8, where a branch costs the longer rows 1 %, their activations
+    // ask for no memory.  Loaded / left out, us: 18532 x 512 batch 14 b = 3 7.15 / 6.8, 8592 x 480 batch 16 b = 4 6.15 / 5.5.  Not where
+    // several workgroups share a CU and rows are long (SKIP): no such waves in single calls.
+    auto load_first = [&]() {
+        constexpr bool kBranch = !SKIP && (B == 3 || B == 4);
+        if (!kBranch || p < p1) issue(2 * p, SKIP || B != 8 || p < p1, XA, QA, std::true_type());
+    };
     // ---- tables of the R tiles into LDS (rows past the matrix repeat the last row; never stored).
     // Thread (row = tid % 16, copy = (tid / 16) % 2, part = tid / 32) writes the entries of the pieces
     // part, part + nparts, ... of its row and copy: the 32 lanes of an LDS clock hit 32 different banks
@@ -347,7 +355,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                 const int row = row0 + r < M ? row0 + r : M - 1;
                 reinterpret_cast<uint32_t *>(nat)[r * kNatDwords + (e & 7)] = reinterpret_cast<const uint32_t *>(lut + (size_t)row * 16)[e & 7];
             }
-            issue(2 * p, true, XA, QA, std::true_type());
+            load_first();
             __syncthreads();
             auto build = [&](auto log2_parts) {
                 constexpr int L = decltype(log2_parts)::value;
@@ -383,7 +391,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
                 const int row = row0 + r < M ? row0 + r : M - 1;
                 reinterpret_cast<uint32_t *>(nat)[r * kNatDwords + (e & 3)] = reinterpret_cast<const uint32_t *>(lut + (size_t)row * 8)[e & 3];
             }
-            issue(2 * p, true, XA, QA, std::true_type());
+            load_first();
             __syncthreads();
             auto build = [&](auto log2_parts) {
                 constexpr int L = decltype(log2_parts)::value;
@@ -450,7 +458,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
             for (int tile = 0; tile < R; ++tile)
 #pragma unroll
                 for (int j = 0; j < kBurst; ++j) asm volatile("" : "+v"(v[tile][j]));
-            issue(2 * p, true, XA, QA, std::true_type());
+            load_first();
 #pragma unroll
             for (int tile = 0; tile < R; ++tile) {
 #pragma unroll
