@@ -91,8 +91,8 @@ constexpr int kExchangeBytes = 1024; // LDS per wave, given at the launch
 
 // `wg` = index of the workgroup within its matrix (R tiles each).  RAG: K is not a multiple of 256 (the last octet holds fewer than 8
 // chunks; lanes of chunks that do not exist multiply zeros by zeros).  WIDE: batch 9..16.  SKIP: loads that are dropped ask for no
-// memory (launch_tile_r).
-template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
+// memory, REFILL: one set of activation registers (both: launch_tile_r).
+template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP, bool REFILL>
 __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut,
                                                const uint16_t *__restrict__ x, uint16_t *__restrict__ y, int M, int K, int batch,
                                                int wg, uint32_t reciprocal)
@@ -141,12 +141,6 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(x), 0, (uint32_t)batch * (uint32_t)K * 2u, kBufferRsrcWord3);
     constexpr int kXSets = WIDE ? 2 : 1;
-    // WIDE: one set of activation registers; a run's are loaded again, for the octet after, once its last tile has used them.  With two
-    // sets as at batch 3 to 8 the registers of one tile cost a wave per SIMD at b = 5 to 8 (134 to 170 instead of 103 to 122), of two tiles
-    // at b = 4 to 7 (172 to 255 instead of 130 to 166).  Two sets / one, us: 22589 x 2560 b = 5 batch 10 19.9 / 15.6, 24352 x 1920 b = 6
-    // batch 9 19.3 / 16.9, 10816 x 2240 b = 5 batch 13 12.8 / 10.0, 11008 x 4096 b = 4 batch 16 10.6 / 10.1, 28672 x 8192 b = 5 47.8 /
-    // 44.6, but b = 4 37.1 / 37.9 and 8192 x 8192 b = 5 batch 9 16.8 / 17.3.
-    constexpr bool kRefill = WIDE;
     constexpr int kNoMemory = 0x38f; // of sched_barrier: what may move across, all but loads and stores of memory
     const int xn = i >> 1, xc = 4 * (i & 1) + kg;
     uint32_t xoff_lane[kXSets];
@@ -158,7 +152,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     int lanes = xc | lc << 8; // the chunks that this lane loads, for ragged octets
     // Two ragged tiles at 3 bits keep within 128 registers (4 waves per SIMD) only if what is cheap to compute again is not kept, and if the
     // second tile's exchange does not move up: with 129 registers 25000 x 288 batch 3 takes 8.5 us instead of 6.2, x 12320 52 instead of 42.
-    constexpr bool kTight = B == 3 && R == 2 && RAG && !WIDE;
+    constexpr bool kTight = B == 3 && R == 2 && RAG && !(WIDE && REFILL);
     float4_t acc[R][kXSets][2]; // one accumulator per quad of an octet (and 8 batch rows): independent chains of matrix instructions
 #pragma unroll
     for (int tile = 0; tile < R; ++tile)
@@ -483,17 +477,17 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
         const int o1 = second ? 2 * p + 1 : 2 * p;
         // the loads of octet o: its activations into the other set ahead of the arithmetic, or (WIDE) run by run into the one that is in use
         auto ahead = [&](int o, bool real, u32x4 (&X)[kXSets][4], uint32_t (&Q)[R][2][B]) {
-            const XLoads l = issue(o, real, X, Q, std::bool_constant<!kRefill>());
+            const XLoads l = issue(o, real, X, Q, std::bool_constant<!REFILL>());
             __builtin_amdgcn_sched_barrier(0); // keep the loads ahead of the arithmetic they overlap with
             return [&XA, &load_run, l](int t) {
-                if constexpr (kRefill) {
+                if constexpr (REFILL) {
                     __builtin_amdgcn_sched_barrier(kNoMemory);
                     load_run(l, t, XA);
                     __builtin_amdgcn_sched_barrier(kNoMemory);
                 }
             };
         };
-        u32x4 (&X1)[kXSets][4] = kRefill ? XA : XB;
+        u32x4 (&X1)[kXSets][4] = REFILL ? XA : XB;
         compute(XA, QA, 2 * p, ahead(o1, second, XB, QB));
         auto next = ahead(p + 1 < p1 ? 2 * p + 2 : 2 * p, !SKIP || p + 1 < p1, XA, QA);
         if constexpr (RAG) {
@@ -545,12 +539,12 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 // instead of 74..80 and workgroups of 8 waves then lose residency, b = 5, 6 go from 5 waves to 4 for nothing.  Bounded / unbounded, us: 16384 x 12288
 // b = 4 batch 3 28.4 / 25.9, 5120 x 2208 b = 4 batch 5 11.6 / 8.9.  Asked for the waves that they have anyway (as the list kernel is), they
 // schedule worse: 4099 x 2208 b = 7 batch 5 7.0 -> 7.2, 9000 x 3104 b = 5 batch 6 11.5 -> 12.1.
-template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP>
+template <int B, int R, int MAXT, bool RAG, bool WIDE, bool SKIP, bool REFILL>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B == 3 && R == 2 && RAG && !WIDE ? 4 : 1))) void gemv_tile_kernel(
     const uint8_t *__restrict__ slices, size_t slice_bytes, const uint16_t *__restrict__ lut, const uint16_t *__restrict__ x,
     uint16_t *__restrict__ y, int M, int K, int batch, uint32_t reciprocal)
 {
-    gemv_tile_body<B, R, MAXT, RAG, WIDE, SKIP>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
+    gemv_tile_body<B, R, MAXT, RAG, WIDE, SKIP, REFILL>(slices, slice_bytes, lut, x, y, M, K, batch, (int)blockIdx.x, reciprocal);
 }
 
 // Several matrices of equal row length at one bit-width and batch in one launch (the projections of a
@@ -563,7 +557,7 @@ __global__ __launch_bounds__(MAXT) void gemv_tile_multi_kernel(MultiArgs a, uint
 #pragma unroll
     for (int i = 1; i < kMaxMulti; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) m = i;
-    gemv_tile_body<B, 1, MAXT, false, false, true>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
+    gemv_tile_body<B, 1, MAXT, false, false, true, false>(a.slices[m], a.slice_bytes[m], a.lut[m], a.x[m], a.y[m], a.M[m], a.K, a.batch,
                                (int)blockIdx.x - a.group_begin[m], reciprocal);
 }
 
@@ -583,7 +577,7 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(B <= 4 ? 6
     for (int i = 1; i < kMaxListItems; ++i)
         if (i < a.count && (int)blockIdx.x >= a.group_begin[i]) it = i;
     const ListItem &I = a.item[it];
-    gemv_tile_body<B, 1, MAXT, false, false, true>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
+    gemv_tile_body<B, 1, MAXT, false, false, true, false>(I.slices, I.slice_bytes, I.lut, I.x, I.y, I.M, I.K, batch, (int)blockIdx.x - a.group_begin[it],
                                              reciprocal);
 }
 
@@ -621,9 +615,9 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
         nw = a.K >= 12288 ? kMaxWaves : 4; // (waves beyond the row's pairs add nothing to the sums)
     }
     const dim3 grid((tiles + R - 1) / R), block(64 * nw);
-    auto launch = [&](auto ragged, auto skip) {
-        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, decltype(ragged)::value, WIDE, decltype(skip)::value>), grid, block, nw * kExchangeBytes, stream,
-                           a.slices, a.slice_bytes, a.lut, a.x, a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
+    auto launch = [&](auto ragged, auto skip, auto refill) {
+        hipLaunchKernelGGL((gemv_tile_kernel<B, R, 64 * kMaxWaves, decltype(ragged)::value, WIDE, decltype(skip)::value, decltype(refill)::value>), grid, block,
+                           nw * kExchangeBytes, stream, a.slices, a.slice_bytes, a.lut, a.x, a.y, a.M, a.K, a.batch, wave_reciprocal(nw));
     };
     // The octet that the last pass of a wave requests and drops (with 4096 columns on 4 waves one of five) is left out where several
     // workgroups share a CU, which then want the bandwidth; elsewhere the few scalar instructions ahead of the loads cost 0.05 us.
@@ -633,8 +627,22 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
     const bool skip = grid.x > 256 && a.K > 2048;
     const std::true_type yes;
     const std::false_type no;
-    if (a.K % 256) skip ? launch(yes, yes) : launch(yes, no);
-    else skip ? launch(no, yes) : launch(no, no);
+    if constexpr (!WIDE) {
+        if (a.K % 256) skip ? launch(yes, yes, no) : launch(yes, no, no);
+        else skip ? launch(no, yes, no) : launch(no, no, no);
+    } else {
+        // Batch 9 to 16: one set of activation registers, a run's loaded again, for the octet after, once its last tile has used them.  With
+        // two sets as at batch 3 to 8 the registers of one tile cost a wave per SIMD at b = 5 to 8 (134 to 170 instead of 103 to 122),
+        // of two tiles at b = 4 to 7 (172 to 255 instead of 130 to 166).  Two sets / one, us: 22589 x 2560 b = 5 batch 10 19.9 / 15.6,
+        // 24352 x 1920 b = 6 batch 9 19.3 / 16.9, 10816 x 2240 b = 5 batch 13 12.8 / 10.0, 11008 x 4096 b = 4 batch 16 10.6 / 10.1, 28672 x
+        // 8192 b = 5 47.8 / 44.6.  Where every workgroup has a CU to itself or rows are short, b = 3, 4 have as many waves as they need
+        // either way and the loads of two sets are further ahead (two sets over one: up to 4096 rows 0.98, 2101 x 26624 0.83); on long
+        // whole rows that outweighs the wave at b = 5 to 8 as well (2870 x 27648 b = 5 30.4 / 33, 16k columns and more 0.96 to 0.99).
+        const std::bool_constant<(B >= 5)> many;
+        if (skip) a.K % 256 ? launch(yes, yes, yes) : launch(no, yes, yes);
+        else if (a.K % 256) launch(yes, no, many);
+        else a.K < 12288 ? launch(no, no, many) : launch(no, no, no);
+    }
     return hipGetLastError();
 }
 

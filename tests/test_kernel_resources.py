@@ -47,7 +47,7 @@ def test_one_tile_kernels_keep_their_waves_per_simd(kernel):
     assert seen == set(WAVES)
 
 
-# the same kernel at batch 9 to 16, with one and with two tiles per workgroup
+# the same kernel at batch 9 to 16 with one set of activation registers, with one and with two tiles per workgroup
 WIDE_WAVES = {1: {3: 5, 4: 5, 5: 4, 6: 4, 7: 4, 8: 4}, 2: {3: 3, 4: 3, 5: 3, 6: 3, 7: 3, 8: 2}}
 
 
@@ -55,7 +55,7 @@ WIDE_WAVES = {1: {3: 5, 4: 5, 5: 4, 6: 4, 7: 4, 8: 4}, 2: {3: 3, 4: 3, 5: 3, 6: 
 def test_kernels_for_nine_to_sixteen_batch_rows_keep_their_waves_per_simd(tiles):
     seen = set()
     for name, k in _kernels().items():
-        m = re.search(r"gemv_tile_kernelILi(\d)ELi%dELi512ELb[01]ELb1E" % tiles, name)
+        m = re.search(r"gemv_tile_kernelILi(\d)ELi%dELi512ELb[01]ELb1ELb[01]ELb1E" % tiles, name)
         if m:
             b = int(m.group(1))
             seen.add(b)
