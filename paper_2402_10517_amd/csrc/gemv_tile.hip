@@ -660,9 +660,31 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
     const bool long_rows = a.K >= 16384 && (a.K % 256 == 0 ? tiles >= 512 || (tiles > 256 && (B <= 4 || a.batch >= 7)) : tiles >= 512 && B <= 4);
     const bool two = a.variant == 10 || (a.variant != 9 && (long_rows || (B == 3 && tiles >= 1536)));
     if (a.batch <= 8) return two ? launch_tile_r<B, 2, false>(a, stream) : launch_tile_r<B, 1, false>(a, stream);
-    // with twice the activations two tiles take about 0.8 of the time per tile, unless that leaves the CUs more unevenly
-    // loaded: 28672 x 8192 b = 4 batch 16 57.1 -> 43.2 us, 8192 x 8192 18.0 -> 15.2, 11008 x 4096 b = 8 22.2 -> 24.0
-    const bool wide_two = tiles >= 448 && 1.6 * ((tiles + 511) / 512) < (tiles + 255) / 256;
+    // Batch 9 to 16.  Two tiles load the activations half as often, which pays where these weigh most (long rows, many batch rows, few bits;
+    // by half more where rows begin inside a 128-byte line) and where as many tiles fall to the busiest CU either way (769 to 1024 and
+    // 1281 to 1536 tiles); on short rows the CU wants more workgroups.  From 27 000 calls on either form (4112 to 28672 rows, all b, batch
+    // 9, 12, 14, 16); time with two tiles over time with one at batch 9 / 16, whole rows:
+    //                       b = 3                   b = 4                   b = 5, 6                b = 7, 8
+    //   columns             2-4k 4-6k      8-12k    2-4k 4-6k      8-12k    2-4k 4-6k      8-12k    2-4k 4-6k      8-12k
+    //   448..512 tiles      1.18 1.18/1.06 /0.94    1.21 1.22/1.09 /0.95    1.23 1.22/1.15 /1.05    1.24 1.21/1.12 /1.03
+    //   769..1024           0.97 0.90/0.79 /0.73    1.02 0.93/0.84 /0.77    1.08 1.04/0.93 /0.84    1.07 1.01/0.91 /0.85
+    //   1025..1280          1.01 0.94/0.85 /0.82    1.22 1.16/1.04 /0.92    1.12 1.09/1.00 /0.94    1.31 1.23/1.10 /1.01
+    //   1281..1536          0.86 0.82/0.75 /0.71    1.14 1.05/0.92 /0.82    1.00 0.98/0.89 /0.82    1.20 1.09/0.96 /0.88
+    //   1537..1792          1.04 0.99/0.85 /0.80    1.11 1.03/0.92 /0.86    1.12 1.09/0.97 /0.93    1.19 1.14/1.00 /0.94
+    // (rows of 1537 to 2048 columns, one pair of octets for every wave, 0.80 to 1.01 at batch 16 and 1281 to 1536 tiles.)  Over another 3780
+    // calls the rule is 0.3 to 1.0 % behind the better form of each, by b, at worst 1.28 where it keeps one tile on fewer than 448 (5261 x
+    // 24576 b = 3 batch 15).
+    const bool many = a.batch >= 11;
+    const int k = a.K % 64 ? a.K + a.K / 2 : a.K, never = 1 << 30;
+    int from; // columns from which two tiles are ahead
+    if (tiles < 448) from = never;
+    else if (tiles <= 768) from = many ? (B <= 4 || (tiles <= 512 && a.K % 256) ? 8192 : never) : tiles <= 512 && a.K % 64 ? 24576 : never;
+    else if (tiles <= 1024) from = many || B <= 4 ? 1537 : 6144;
+    else if (tiles <= 1280) from = B == 3 ? (many ? 1537 : 4096) : many && B <= 6 ? (B == 4 ? 6144 : 8192) : never;
+    else if (tiles <= 1536) from = B == 3 ? 0 : B == 5 || B == 6 || (many && a.K <= 2048) ? 1537 : many ? 4096 : 8192;
+    else if (B == 3) from = a.K % 256 ? 0 : 1537;
+    else from = many ? (B <= 6 ? 4096 : 6144) : B == 4 ? 8192 : never;
+    const bool wide_two = k >= from;
     return wide_two ? launch_tile_r<B, 2, true>(a, stream) : launch_tile_r<B, 1, true>(a, stream);
 }
 
