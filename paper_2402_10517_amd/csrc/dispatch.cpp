@@ -19,9 +19,15 @@ namespace apgemv {
 //   batch 4 17.7 / 6.1, 4096x8224 b = 5 batch 3 16.3 / 10.3, 512x1120 b = 5 batch 16 9.4 / 5.2
 // What decides where the other kernel is close: the CUs that the last round of tiles leaves idle (5120 rows are 320 tiles, 1.25 rounds;
 // `busy` below), whether the last octet of a row is partly padding (`whole`, `half`), how much of the call is building the tables (short
-// rows; by b), and the ALU kernel's second round of spans from 8193 columns on.  Over the 21 000 calls this rule loses 0.1 to 0.8 % (by b
-// and batch) against the better kernel of each, the rule of the tile kernel's earlier forms 2 to 10 %; 14 of them are 3 to 8 % slower than
-// by that rule.  512 rows stand for fewer: up to 1024 every tile has a CU to itself.
+// rows; by b), the ALU kernel's second round of spans from 8193 columns on, and its batch: it takes the same time at 5 to 8 rows, the tile
+// kernel grows with them.  On ragged rows at b = 7, 8 up to 1280 row groups are one round of the ALU kernel's workgroups (5 per CU) and more
+// than one of tiles (`one_alu_round`); it is then ahead the more of its last span is filled and the higher b and batch are, ALU / tile kernel:
+// 4384x24288 b = 8 batch 5..8 0.92 0.88 0.87 0.83, b = 7 0.97 0.93 0.92 0.88, but 4798x26592 b = 7 batch 5 1.1; 4978x7648 b = 3 batch 4 0.88.
+// At batch 9 and more the other kernel takes two passes, of which the second costs as much as the first from 13 on (two passes / tile, below
+// 320 row groups at 6 to 8k columns b = 7, 8 0.92 at batch 9, 0.99 at 12, 1.09 at 13 and 16).
+// Over the 21 000 calls this rule loses 0.1 to 0.8 % (by b and batch) against the better kernel of each; where it keeps to the ALU kernel for
+// simplicity the tile kernel is ahead by up to 1.3 (b = 4, batch 5 to 8, 512x28672 15.6 / 12.0) and, at batch 9 and more below 64 row
+// groups, 1.9 to 2.3 (182x256 b = 3).  512 rows stand for fewer: up to 1024 every tile has a CU to itself.
 static bool tile_pays(const GemvArgs &a)
 {
     const int groups = padded_rows(a.M) / kRowsPerGroup, b = a.b, K = a.K;
@@ -31,17 +37,22 @@ static bool tile_pays(const GemvArgs &a)
     }
     const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
     auto busy = [&](int percent) { return 100 * tiles >= percent * 256 * rounds; }; // of the CUs, over the rounds
-    const bool whole = K % 256 == 0, half = K % 128 == 0;
+    const bool whole = K % 256 == 0, half = K % 128 == 0, one_alu_round = groups <= 1280;
     if (a.batch == 2) return batch2_tile_pays(a);
     if (a.batch < 2) return false;
     if (a.batch >= 5) {
-        if (groups >= 640) return half || b < 7 || K <= 5632 || K > 8192 || rounds != 2 || busy(58);
+        if (groups >= 640) {
+            if (half || b < 7 || K <= 5632 || rounds != 2) return true;
+            if (K <= 8192 && !busy(58)) return false;
+            return !one_alu_round || (K > 8192 && K <= 12800) || K % 2048 < 256 * (33 - 2 * (b + a.batch));
+        }
+        if (b == 3 && a.batch == 8 && groups < 512 && K > 12288 && !whole && K % 2048 >= 1024) return false;
         if (groups >= 320) return K <= 4096 || b <= 4 || (K > 8192 && whole && (b <= 6 || K <= 12288));
         if (!whole) return groups >= 64 && K <= (b == 3 ? 1536 : 512);
         return groups >= 64 && K <= (b <= 4 ? 4096 : b == 6 ? 512 : 2048);
     }
     if (b == 3) {
-        if (groups >= 640) return whole || K <= 5632 || K > 8192 || rounds != 2 || busy(60);
+        if (groups >= 640) return whole || K <= 5632 || K > 8192 || rounds != 2 || !one_alu_round;
         if (groups >= 64 && K <= 512) return true;
         return whole && groups >= 64 && (K <= 2048 || (groups >= 320 && (K <= 4096 || (K > 8192 && K <= 13824))));
     }
