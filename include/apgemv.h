@@ -109,8 +109,9 @@ ap_status ap_unpack(const ap_matrix *h, uint8_t *idx_host_out, void *stream);
  *   x_dev  device, batch*K binary16 row-major, 16-byte aligned
  *   y_dev  device, batch*M binary16 row-major, 2-byte aligned; must not overlap x_dev or the blob
  *   batch  1..16 (the paper switches to a dequantise + dense GEMM path above about 16, Section 6.2).
- *          Batches 9..16 run as one launch on matrices of about 2048 rows or more (1024 at b <= 5 and up to 12288
- *          columns, 512 at up to 1024 columns), else (and with a tuning override) as two passes on the stream, the first over rows 0..7
+ *          Batches 9..16 run as one launch on matrices of 1277 rows or more, and from 253 rows on where the rows are shorter than a
+ *          limit by b and batch (5632 columns at b = 8, batch 9), else (and with a tuning override) as two passes on the stream,
+ *          the first over rows 0..7
  * Products are exact in binary32, accumulation is binary32, the result is rounded to binary16
  * (round to nearest even).  Asynchronous on `stream`; allocates nothing, synchronises nothing,
  * never repacks; the bit-width is chosen per call.  Results are deterministic (no atomics).
@@ -160,15 +161,18 @@ typedef enum {
 ap_status ap_set_option(ap_matrix *h, int option, int value);
 
 /*
- * Several GEMVs of the same bit-width in ONE launch: y_i = W_i,b * x_i for i < count (1..8), e.g. the
+ * Several GEMVs of the same bit-width in ONE launch (two in the one case named below): y_i = W_i,b * x_i for i < count (1..8), e.g. the
  * q/k/v or the gate/up projections of a decoder layer (Section 6.3 measures whole-model decoding,
  * where the per-launch cost of 224 small GEMVs per token matters).  Every matrix needs a table for b;
  * M may differ; at batch >= 2 all matrices must have the same K (AP_ERR_SHAPE otherwise), at batch 1
- * any shapes go together; x_dev/y_dev may be shared or distinct per item (outputs must not overlap).
- * At batch 1 and 2 each output is bit-identical to the one ap_gemv produces with default options (same
- * kernel per row group); at larger batches ap_gemv may pick another variant with a different
+ * any shapes go together (one launch per number of waves that their rows take); x_dev/y_dev may be shared or distinct per item
+ * (outputs must not overlap).
+ * At batch 1 and 2 each output is bit-identical to the one ap_gemv produces with default options if the FIRST item's handle has
+ * AP_VARIANT_AUTO; at larger batches ap_gemv may pick another variant with a different
  * summation order, and both meet the same tolerance.  The kernel is chosen from the launch as a whole
- * (b, batch, K, the sum of the rows); of the per-handle options only AP_OPT_VARIANT of the FIRST item's
+ * (b, batch, K, the sum of the rows), except at batch 2, b = 4, where it is that of single calls: matrices of 2^27 weights and
+ * more (K >= 7168, K % 256 == 0) go to the matrix-core kernel on tiles, and other matrices of the same call to a launch of their own.
+ * Of the per-handle options only AP_OPT_VARIANT of the FIRST item's
  * handle is looked at (AP_VARIANT_TILE forces the matrix-core kernel on tiles when K % 256 == 0, any
  * other value than AP_VARIANT_AUTO keeps the launch on the ALU kernel).  batch 1..8 here.  Same argument
  * rules and error codes as ap_gemv.
@@ -206,7 +210,7 @@ ap_status ap_gemv_list(const ap_gemv_list_item *items, int count, void *stream);
  * x_i (batch x K_i) * W_i,b_i^T, the decode step of `batch` queries that run at the same precision
  * (Section 6.2 measures the kernel up to batch 8).  batch 1 is ap_gemv_list.  At batch 2 the items go into
  * list launches of the kernels that single calls use (any shapes and bit-widths together, up to 32 per launch;
- * large 4-bit products in launches of their own; bit-identical to separate ap_gemv calls).  At batch >= 3 the items
+ * 4-bit products of 2^27 weights and more in launches of their own; bit-identical to separate ap_gemv calls).  At batch >= 3 the items
  * that the matrix-core kernel on tiles of 16 rows can take (K_i % 256 == 0) are launched together per
  * bit-width and class of row length, up to 32 per launch, whenever such a group has at least two
  * items and 1024 groups of 4 rows in total; every other item runs as its own

@@ -124,16 +124,20 @@ inline bool static_dense_pays(const GemvArgs &a)
 }
 
 // Whether a product at batch 2 without options runs on the kernel on tiles of 16 rows rather than on the batch-1/2 kernel, in a single call as in
-// a list or fused launch (which give its bits: rows of 3072 columns and more have 4 waves, from 12288 on 8, in both).  Large
-// products in pairs of centroids (b = 4, where the lookups of the ALU kernel cost most): 8192x8192 12.2 -> 9.4 us, 13824x5120 14.0 -> 11.4,
-// 28672x8192 37.9 -> 28.8, ALU kernel over tile kernel 14336x12288 1.28, 4096x16384 1.35, 8192x28672 1.61, but 5120x13824 1.01 (320 tiles,
-// 62 % of two rounds) and 28672x2048 0.94.  Smaller single calls would gain as well (11008x4096 9.3 -> 7.9, 4096x11008 9.9 -> 7.7), but mixed
-// work lists of them pay for the further launches: the 18 products of three 7B shapes at every b 103 -> 109.  b = 3 is level
-// up to 8192 columns, b = 5 to 8 within 5 % or behind.
+// a list or fused launch (which give its bits: rows of 3072 columns and more have 4 waves, from 12288 on 8, in both).  In pairs of
+// centroids (b = 4, where the lookups of the ALU kernel cost most) the tile kernel is ahead from about 2^25 weights on, but where a list or a
+// fused launch holds other products as well it is one launch more, 3 to 4 us.  The line lies where that is paid for: alone / with two
+// of 1024 rows in one call / with the products of a 13B layer at b = 5, ALU kernel / tile kernel, us:
+//   28672x8192 38 / 29, 37.1 / 32.5, 77.0 / 71.9; 16384x8192 22.0 / 16.5, 23.9 / 22.5, 63.8 / 61.2; 20480x7168 23.1 / 18.9, 24.4 / 23.9,
+//   64.1 / 63.4; 12288x11264 22.3 / 17.0, 24.7 / 24.7, 63.0 / 61.5; 8192x28672 45 / 28, -, 85.8 / 69.4
+//   smaller: 8192x8192 12.2 / 9.4, 14.3 / 16.5, 54.7 / 55.6; 13824x5120 14.0 / 11.4, 15.3 / 17.5, 55.3 / 56.8; 14336x8192 -, 20.6 / 22.1, 61.9 / 60.8
+//   short rows: 28672x6144 26.2 / 21.8, 26.9 / 26.6, 67.0 / 66.2; 28672x5120 23.5 / 20.2, 24.3 / 24.8, 65.1 / 64.6; 32768x4096 20.4 / 17.8, 20.8 / 22.5
+//   last round of tiles (% of the CUs over all rounds): 8704x16384 (71 %) 21.3 / 20.5, 25.5 / 28.9, 61.9 / 65.6; 11008x12288 (90 %) 21.8 / 18.2,
+//   24.5 / 26.2, 61.1 / 63.6
 inline bool batch2_tile_pays(const GemvArgs &a)
 {
     const long long tiles = (a.M + 15) / 16, rounds = (tiles + 255) / 256;
-    return a.b == 4 && a.K % 256 == 0 && a.K >= 3072 && (long long)a.M * a.K >= 1 << 26 && 100 * tiles >= 69 * 256 * rounds;
+    return a.b == 4 && a.K % 256 == 0 && a.K >= 7168 && (long long)a.M * a.K >= 1 << 27 && 100 * tiles >= 91 * 256 * rounds;
 }
 
 constexpr int kMaxMulti = 8;

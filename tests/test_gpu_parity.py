@@ -906,10 +906,11 @@ def test_small_and_ragged_matrices_at_batches(B, batch):
 
 
 def test_batch_2_on_the_tile_kernel_same_bits_in_lists_and_fused_launches(B):
-    # b = 4 at batch 2 goes to the tile kernel from 2^26 weights on (4 and 8 waves, one and two tiles per workgroup); list and fused
-    # launches of such matrices, among others that stay on the batch-1/2 kernel, give the bits of single calls
+    # b = 4 at batch 2 goes to the tile kernel from 2^27 weights on (the last three shapes: 4 and 8 waves, one and two tiles per workgroup);
+    # list and fused launches of such matrices, among others that stay on the batch-1/2 kernel, give the bits of single calls
     import torch
-    shapes = [(8192, 8192), (8192, 7936), (4096, 16384), (6150, 11008), (16384, 4096), (8205, 16640), (2050, 4096), (70, 2048 + 96)]
+    shapes = [(8192, 8192), (8192, 7936), (4096, 16384), (6150, 11008), (16384, 4096), (8205, 16640), (2050, 4096), (70, 2048 + 96),
+              (16384, 8192), (12283, 11008), (8179, 16640)]
     mats = []
     for k, (M, K) in enumerate(shapes):
         idx, luts, x = inputs.make_case(42, M, K, batch=2, salt=k, bit_widths=[4, 5], sigma=0.01)
@@ -927,7 +928,7 @@ def test_batch_2_on_the_tile_kernel_same_bits_in_lists_and_fused_launches(B):
         assert torch.equal(y.view(torch.int16), single[k, b].view(torch.int16)), (shapes[k], b)
     out = [torch.full((2, shapes[k][0]), -5.0, dtype=torch.float16, device="cuda") for k in range(len(mats))]
     for b in (4, 5):
-        for group in ([4, 6], [0], [6]):                             # equal row length
+        for group in ([4, 6], [0], [6], [8, 0], [8], [5, 10]):        # equal row length
             B.ap_gemv_multi([(mats[k][3], mats[k][4], out[k]) for k in group], b)
             for k in group:
                 assert torch.equal(out[k].view(torch.int16), single[k, b].view(torch.int16)), (shapes[k], b)
