@@ -254,10 +254,7 @@ extern "C" ap_status ap_gemv_list(const ap_gemv_list_item *items, int count, voi
 // list launches of the batch-1/2 kernel and, per class of row length, of the tile kernel.  A launch goes out when its list is full.
 class Batch2List {
 public:
-    explicit Batch2List(hipStream_t stream) : stream_(stream)
-    {
-        for (ListArgs &la : lists_) la.count = 0;
-    }
+    explicit Batch2List(hipStream_t stream) : stream_(stream) { std::memset(lists_, 0, sizeof(lists_)); }
     bool add(const ap_matrix *h, int b, const void *x_dev, void *y_dev)
     {
         GemvArgs a;

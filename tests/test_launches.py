@@ -55,3 +55,12 @@ def test_work_lists_at_batch_2(launches):
     assert launches("list", 2, at(4, LAYER_13B) * 6)[0] == ["alu_list:32", "alu_list:10"]
     layer = [(8192, 8192)] * 2 + [(1024, 8192)] * 2 + [(28672, 8192)] * 2 + [(8192, 28672)]
     assert sorted(launches("list", 2, at(4, layer))[0]) == ["alu_list:4", "tile_list:1", "tile_list:2"]
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3])
+def test_unused_items_of_a_work_list_are_zero(launches, batch):
+    # a list goes to the device whole, as the argument of the kernel
+    items = at(4, [(4096, 4096), (1024, 4096), (28672, 8192), (8192, 28672)])
+    for kind in ("list", "fused") if batch == 2 else ("list",):
+        out, clean = launches(kind, batch, items[:3] if kind == "list" else items[2:3])
+        assert clean, (kind, out)
