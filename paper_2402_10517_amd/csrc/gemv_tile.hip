@@ -689,7 +689,8 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
 }
 
 // Waves per workgroup of a list or fused launch whose shortest row has min_pairs pairs of octets: as single calls on this kernel by option, but
-// with the smaller tables (b = 5, 6, 7) no more than that row has pairs.  At b = 3, 4, 8 waves without columns help to build the tables
+// at b = 5, 6, 7, where waves without columns were slower in single calls (tile_waves), no more than that row has pairs: one short row
+// then leaves the longer ones of the launch with few waves.  At b = 3, 4, 8 waves without columns help to build the tables
 // (a sum of zero waves more: the bits are the same).  One wave per pair / with helpers, us: 8 of
 // 8192 x 512 batch 4 b = 3 14.7 / 12.1, b = 4 56.3 / 16.7, b = 8 28.4 / 22.4, 8 of 8192 x 1024 b = 4 41.6 / 18.4, 6 of 4096 x 1536 16.8 / 10.3, 4 of
 // 2048 x 512 15.0 / 6.2; b = 8 with four tiles per CU, 8 of 2048 x 1024 7.4 / 8.2: not there, as in single calls (tile_waves).

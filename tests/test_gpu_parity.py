@@ -938,19 +938,40 @@ def test_batch_2_on_the_tile_kernel_same_bits_in_lists_and_fused_launches(B):
 
 @pytest.mark.parametrize("b", ALL_BITS)
 def test_short_rows_in_list_and_fused_launches(B, b):
-    # rows of 1, 2 and 3 pairs of octets, where a launch has waves without columns at b = 3, 4, 8; total rows on both sides of what a list
-    # launch takes (1024 groups) and of the 768..1024 tiles at b = 8
+    # rows of 1, 2 and 3 pairs of octets, where a launch has waves without columns at b = 3, 4, 8; of 513 row groups and 129 tiles each: one (fewer
+    # groups than a list or fused launch on tiles takes), and launches below, inside and above the 768..1024 tiles at b = 8
     import torch
-    for K, counts in ((256, (4, 7)), (768, (4,)), (1280, (4,))):
+    for K in (256, 768, 1280):
         idx, luts, x = inputs.make_case(43, 2050, K, batch=5, bit_widths=[b], sigma=0.01)
         pm, xd = B.ap_pack(idx, luts), torch.from_numpy(x).cuda()
-        for count in counts:
+        for count in (1, 4, 7, 8):
             out = [torch.full((5, pm.M), -5.0, dtype=torch.float16, device="cuda") for _ in range(2 * count)]
             B.ap_gemv_list_batch([(pm, b, xd, y) for y in out[:count]], 5)
             B.ap_gemv_multi([(pm, xd, y) for y in out[count:]], b)
-            check_against_oracle(out[0].cpu().numpy(), idx, luts[b], b, x)
-            for y in out[1:]:
-                assert torch.equal(y.view(torch.int16), out[0].view(torch.int16))
+            for y in (out[0], out[-1]):
+                check_against_oracle(y.cpu().numpy(), idx, luts[b], b, x)
+            for k in range(2 * count):
+                first = out[0] if k < count else out[count]
+                assert torch.equal(out[k].view(torch.int16), first.view(torch.int16))
+                if count > 1:                                        # the same kernel and number of waves in both
+                    assert torch.equal(out[k].view(torch.int16), out[0].view(torch.int16))
+        pm.close()
+
+
+@pytest.mark.parametrize("b", [5, 6, 7])
+def test_short_and_long_rows_in_one_work_list(B, b):
+    # the shortest row sets the waves of a list launch at these bit-widths (one of 256 columns: a single wave takes all columns of the others)
+    import torch
+    shapes = [(2050, 256), (4099, 4096), (515, 11008), (2050, 1280)]
+    mats = []
+    for k, (M, K) in enumerate(shapes):
+        idx, luts, x = inputs.make_case(47, M, K, batch=4, salt=k, bit_widths=[b], sigma=0.01)
+        mats.append((idx, luts, x, B.ap_pack(idx, luts), torch.from_numpy(x).cuda()))
+    out = [torch.full((4, M), -5.0, dtype=torch.float16, device="cuda") for M, K in shapes]
+    B.ap_gemv_list_batch([(m[3], b, m[4], y) for m, y in zip(mats, out)], 4)
+    for (idx, luts, x, pm, xd), y in zip(mats, out):
+        rows = np.unique(np.r_[0:20, pm.M - 20:pm.M])
+        check_against_oracle(y.cpu().numpy(), idx, luts[b], b, x, rows=rows)
         pm.close()
 
 
