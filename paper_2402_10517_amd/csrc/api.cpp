@@ -395,10 +395,10 @@ extern "C" ap_status ap_gemv_multi(const ap_gemv_item *items, int count, int b, 
     m.batch = batch;
     // The matrix-core kernel on tiles of 16 rows when the launch as a whole is large enough for it (1024 row
     // groups in total at batch 5..8, 2048 at batch 3, 4) or when the first handle asks for it
-    // (AP_VARIANT_TILE).  Measured on the 7B projections (q,k,v: 3 x 4096x4096; gate,up: 2 x 11008x4096)
-    // against the ALU kernel of this launch: batch 5..8 9.8 / 11.5 / 16.7 us against 17.7 / 19.7 / 23.7
-    // (q,k,v; b = 3, 4, 8) and 15.0 / 19.0 / 28.4 against 27.7 / 31.2 / 35.9 (gate,up); batch 3..4 level
-    // to 10 % faster.
+    // (AP_VARIANT_TILE).  ALU kernel / tile kernel of this launch at b = 3, 4, 5, 8, us: 3 x 4096x4096 batch 4 11.0/7.7 13.5/8.8 14.7/11.1
+    // 17.1/14.8, batch 8 18.2/8.3 20.9/9.1 21.1/11.9 24.1/15.0; 2 x 11008x4096 batch 4 16.7/11.5 22.3/14.2 24.6/19.0 26.3/24.4, batch 8 28.6/13.4
+    // 34.3/15.6 34.7/20.3 37.2/25.2; 1024 row groups (2 x 2048x4096) batch 5 8.4/5.3 9.5/5.8 9.5/6.7 10.9/7.7, batch 3 6.0/5.4 6.5/5.8 7.0/6.9
+    // 8.5/7.8 (where the line at 2048 groups, older than these times, keeps the ALU kernel).
     const int first_variant = items[0].h->variant;
     const bool tile = m.K % 256 == 0 &&
                       (first_variant == AP_VARIANT_TILE ||

@@ -161,7 +161,7 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
 
     // Octet o of a row = chunks 8 o .. 8 o + 7 (span o / 8); the waves split the row's pairs of octets
     // evenly.  The loads of an octet are issued before the arithmetic of the octet before it (two
-    // register sets).  Every pass of the loop issues the same loads and has no exit in the middle, so the
+    // register sets; REFILL: the activations have one, see launch_tile_r).  Every pass of the loop issues the same loads and has no exit in the middle, so the
     // wait before the arithmetic leaves exactly the newer loads in flight: a row with an odd number of
     // octets gets one more (the last one again, activations out of range), and the loads issued in the
     // last pass for the pass after it repeat a valid octet and are dropped.  The products of that padding
@@ -319,8 +319,8 @@ __device__ __forceinline__ void gemv_tile_body(const uint8_t *__restrict__ slice
     int p = first_pair(npairs, wave, reciprocal); // < npairs, also for a wave without pairs
     // The wave's first octet.  Waves without pairs (short rows at b = 3, 4, 8: they help to build the tables) would load and drop one, in the way
     // of the others at the vector L1: at b = 3, 4 they leave it out, at b = 8, where a branch costs the longer rows 1 %, their activations
-    // ask for no memory.  Loaded / left out, us: 18532 x 512 batch 14 b = 3 7.15 / 6.8, 8592 x 480 batch 16 b = 4 6.15 / 5.5.  Not where
-    // several workgroups share a CU and rows are long (SKIP): no such waves in single calls.
+    // ask for no memory.  Loaded / left out, us: 18532 x 512 batch 14 b = 3 7.1 / 6.1, 8592 x 480 batch 16 b = 4 6.1 / 5.3.  Not where
+    // several workgroups share a CU and rows are long (SKIP): no such waves in single calls, and list and fused launches, which have them, load.
     auto load_first = [&]() {
         constexpr bool kBranch = !SKIP && (B == 3 || B == 4);
         if (!kBranch || p < p1) issue(2 * p, SKIP || B != 8 || p < p1, XA, QA, std::true_type());
@@ -637,7 +637,7 @@ template <int B, int R, bool WIDE> static hipError_t launch_tile_r(const GemvArg
         // 24352 x 1920 b = 6 batch 9 19.3 / 16.9, 10816 x 2240 b = 5 batch 13 12.8 / 10.0, 11008 x 4096 b = 4 batch 16 10.6 / 10.1, 28672 x
         // 8192 b = 5 47.8 / 44.6.  Where every workgroup has a CU to itself or rows are short, b = 3, 4 have as many waves as they need
         // either way and the loads of two sets are further ahead (two sets over one: up to 4096 rows 0.98, 2101 x 26624 0.83); on long
-        // whole rows that outweighs the wave at b = 5 to 8 as well (2870 x 27648 b = 5 30.4 / 33, 16k columns and more 0.96 to 0.99).
+        // whole rows that outweighs the wave at b = 5 to 8 as well (16k columns and more 0.96 to 0.99, 2870 x 27648 b = 5 0.93).
         const std::bool_constant<(B >= 5)> many;
         if (skip) a.K % 256 ? launch(yes, yes, yes) : launch(no, yes, yes);
         else if (a.K % 256) launch(yes, no, many);
