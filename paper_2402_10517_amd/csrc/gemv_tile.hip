@@ -671,19 +671,21 @@ template <int B> static hipError_t launch_tile_b(const GemvArgs &a, hipStream_t 
     //   1025..1280          1.01 0.94/0.85 /0.82    1.22 1.16/1.04 /0.92    1.12 1.09/1.00 /0.94    1.31 1.23/1.10 /1.01
     //   1281..1536          0.86 0.82/0.75 /0.71    1.14 1.05/0.92 /0.82    1.00 0.98/0.89 /0.82    1.20 1.09/0.96 /0.88
     //   1537..1792          1.04 0.99/0.85 /0.80    1.11 1.03/0.92 /0.86    1.12 1.09/0.97 /0.93    1.19 1.14/1.00 /0.94
-    // (rows of 1537 to 2048 columns, one pair of octets for every wave, 0.80 to 1.01 at batch 16 and 1281 to 1536 tiles.)  Over another 3780
-    // calls the rule is 0.3 to 1.0 % behind the better form of each, by b, at worst 1.28 where it keeps one tile on fewer than 448 (5261 x
-    // 24576 b = 3 batch 15).
+    // (rows of 1537 to 2048 columns, one pair of octets for every wave, 0.80 to 1.01 at batch 16 and 1281 to 1536 tiles; the lines between
+    // the classes come from single calls: 24895 x 1696 b = 8 batch 16 30.8 / 28.0 us, 12300 x 1024 b = 3 batch 16 6.3 / 5.6, 8000 x 9344 b = 4
+    // batch 11 18.4 / 19.5.)  Over another 3780 calls the rule is 0.3 to 1.0 % behind the better form of each, by b, at worst 1.28 where it
+    // keeps one tile on fewer than 448 (5261 x 24576 b = 3 batch 15).
     const bool many = a.batch >= 11;
     const int k = a.K % 64 ? a.K + a.K / 2 : a.K, never = 1 << 30;
     int from; // columns from which two tiles are ahead
     if (tiles < 448) from = never;
-    else if (tiles <= 768) from = many ? (B <= 4 || (tiles <= 512 && a.K % 256) ? 8192 : never) : tiles <= 512 && a.K % 64 ? 24576 : never;
-    else if (tiles <= 1024) from = many || B <= 4 ? 1537 : 6144;
+    else if (tiles <= 512) from = many ? (B == 3 ? 6144 : B == 4 || a.K % 256 ? 8192 : never) : a.K % 64 ? 24576 : never;
+    else if (tiles <= 768) from = a.batch >= 13 && B <= 4 ? (B == 3 ? 6144 : 8192) : never;
+    else if (tiles <= 1024) from = many && B == 3 ? 1025 : many || B <= 4 ? 1537 : 6144;
     else if (tiles <= 1280) from = B == 3 ? (many ? 1537 : 4096) : many && B <= 6 ? (B == 4 ? 6144 : 8192) : never;
-    else if (tiles <= 1536) from = B == 3 ? 0 : B == 5 || B == 6 || (many && a.K <= 2048) ? 1537 : many ? 4096 : 8192;
+    else if (tiles <= 1536) from = B == 3 ? 0 : B == 5 || B == 6 || (many && a.K <= 2048) ? 1537 : many ? 3584 : 8192;
     else if (B == 3) from = a.K % 256 ? 0 : 1537;
-    else from = many ? (B <= 6 ? 4096 : 6144) : B == 4 ? 8192 : never;
+    else from = many ? (a.K <= 2048 && a.K % 256 ? 1537 : B <= 6 ? 4096 : 6144) : B == 4 ? 8192 : never;
     const bool wide_two = k >= from;
     return wide_two ? launch_tile_r<B, 2, true>(a, stream) : launch_tile_r<B, 1, true>(a, stream);
 }
